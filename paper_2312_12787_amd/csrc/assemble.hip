@@ -15,24 +15,6 @@ namespace {
 
 constexpr double PI = 3.14159265358979323846;
 constexpr double EULER = 0.57721566490153286061;
-// Assembly kernels: minimum waves per SIMD of the far-element and of the
-// near-element launch (the latter reads its series coefficients by scalar
-// loads) and Gauss points unrolled together (measured on gfx950, kite of 4096
-// elements: one Gauss point at a time is 6 % faster than two in FP64, equal
-// in FP32, and unrolling the near-element loop by 2 or 8 gains nothing; four
-// waves per SIMD no faster than two; a third near-element wave makes the
-// complex Burton-Miller variant spill).  The source elements per near-element
-// workgroup, NEAR_PART, are set with the shared layout constants.
-#ifndef ASM_FAR_WAVES
-#define ASM_FAR_WAVES 2
-#endif
-#ifndef ASM_NEAR_WAVES
-#define ASM_NEAR_WAVES 2
-#endif
-#ifndef ASM_GAUSS_UNROLL
-#define ASM_GAUSS_UNROLL 1
-#endif
-
 template <class T>
 __device__ __forceinline__ const T* tab(const char* g, size_t off) { return reinterpret_cast<const T*>(g + off); }
 template <class T>
@@ -54,9 +36,9 @@ __device__ __forceinline__ cd csqrt_(cd z)
 __device__ __forceinline__ cd clog_(cd z) { return {log(hypot(z.re, z.im)), atan2(z.im, z.re)}; }
 
 // ---------------------------------------------------------------------------
-// Element table and the Gauss points of every element (Secs. 4, 7).
+// Element table (Secs. 4, 7).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void setup_element(char* g, const GeomLayout& L, int e, int q)
+__device__ __forceinline__ void setup_element(char* g, const GeomLayout& L, int e)
 {
     const double2* nodes = tab<double2>(g, L.nodes);
     const int2 ab = tab<int2>(g, L.elnodes)[e];
@@ -76,23 +58,6 @@ __device__ __forceinline__ void setup_element(char* g, const GeomLayout& L, int 
     E.ny = E.tx;
     for (int k = 0; k < 5; ++k) E.pad[k] = 0.0;
     tabw<ElemRec>(g, L.elem)[e] = E;
-    GaussRec G;
-    GaussRec32 G32;
-    for (int k = 0; k < QMAX; ++k) {
-        if (k < q) {
-            const double s = 0.5 * E.h * GAUSS_X[q - 1][k];
-            G.x[k] = E.cx + s * E.tx;
-            G.y[k] = E.cy + s * E.ty;
-            G.w[k] = 0.5 * E.h * GAUSS_W[q - 1][k];
-        } else {
-            G.x[k] = G.y[k] = G.w[k] = 0.0;
-        }
-        G32.x[k] = (float)G.x[k];
-        G32.y[k] = (float)G.y[k];
-        G32.w[k] = (float)G.w[k];
-    }
-    tabw<GaussRec>(g, L.gauss)[e] = G;
-    tabw<GaussRec32>(g, L.gauss32)[e] = G32;
 }
 
 // ---------------------------------------------------------------------------
@@ -115,13 +80,9 @@ __device__ void build_wave(cd k, WaveConst& W)
     const cd sq = csqrt_(cdiv({2.0 / PI, 0.0}, k));  // sqrt(2/(pi k))
     W.ampr = sq.re;
     W.ampi = sq.im;
-    W.rs = HANKEL_XS_F64 / ak;
-    W.rs32 = HANKEL_XS_F32 / ak;
-    const double c4 = 0.70710678118654752440;
-    W.a0r = sq.re * c4 + sq.im * c4;  // * e^{-i pi/4} = (1 - i)/sqrt2
-    W.a0i = sq.im * c4 - sq.re * c4;
-    W.a1r = -sq.re * c4 + sq.im * c4;  // * e^{-3 i pi/4} = (-1 - i)/sqrt2
-    W.a1i = -sq.im * c4 - sq.re * c4;
+    const cd tk = cdiv({2.0, 0.0}, k);
+    W.tkr = tk.re;
+    W.tki = tk.im;
     const cd h = cscale(k, 0.5);
     W.hr = h.re;
     W.hi = h.im;
@@ -134,26 +95,6 @@ __device__ void build_wave(cd k, WaveConst& W)
     const cd y1 = cdiv({-2.0 / PI, 0.0}, k);
     W.y1r = y1.re;
     W.y1i = y1.im;
-}
-
-__device__ void build_wave32(cd k, WaveConst32& W)
-{
-    const double ak = hypot(k.re, k.im);
-    W.r2_small = (float)((HANKEL_XS_F32 / ak) * (HANKEL_XS_F32 / ak));
-    const cd xk = cdiv({HANKEL_XS_F32, 0.0}, k);
-    W.ur = (float)xk.re;
-    W.ui = (float)xk.im;
-    const cd w = cmul(xk, xk);
-    W.wr = (float)w.re;
-    W.wi = (float)w.im;
-    const cd sq = csqrt_(cdiv({2.0 / PI, 0.0}, k));
-    W.ampr = (float)sq.re;
-    W.ampi = (float)sq.im;
-    const double c4 = 0.70710678118654752440;
-    W.a0r = (float)(sq.re * c4 + sq.im * c4);
-    W.a0i = (float)(sq.im * c4 - sq.re * c4);
-    W.a1r = (float)(-sq.re * c4 + sq.im * c4);
-    W.a1i = (float)(-sq.im * c4 - sq.re * c4);
 }
 
 __device__ __forceinline__ void setup_domain(char* g, const GeomLayout& L, int d)
@@ -188,7 +129,6 @@ __device__ __forceinline__ void setup_domain(char* g, const GeomLayout& L, int d
     D.pad = 0;
     tabw<DomConst>(g, L.dom)[d] = D;
     build_wave(k, tabw<WaveConst>(g, L.wave)[d]);
-    build_wave32(k, tabw<WaveConst32>(g, L.wave32)[d]);
 }
 
 // ---------------------------------------------------------------------------
@@ -238,14 +178,101 @@ __device__ __forceinline__ void setup_self(char* g, const GeomLayout& L, int N, 
     tabw<double2>(g, L.self)[(size_t)d * N + e] = make_double2(s.re, s.im);
 }
 
+// 1/n, n = 1 .. 47 (the series below multiply by them instead of dividing)
+struct Reciprocals {
+    double v[48];
+};
+constexpr Reciprocals make_reciprocals()
+{
+    Reciprocals r{};
+    for (int n = 1; n < 48; ++n) r.v[n] = 1.0 / n;
+    return r;
+}
+static __device__ const Reciprocals g_rcp = make_reciprocals();
+
+// sum_j (-1)^j y^{2j+m} / (j! (m+j)!) W_{2j+m}: J_m(2 y) with W = 1 (mom null);
+// with the moments W_n of the Gauss rule (n even: mom[n/2]) the rule's value
+// of the integral of J_m(2 y x) over x in [-1, 1].  |y| <= EXP_KA_MAX / 2.
+__device__ __forceinline__ cd bessel_sum(int m, cd y, const double* __restrict__ mom)
+{
+    cd t = {1.0, 0.0};
+    for (int n = 1; n <= m; ++n) t = cscale(cmul(t, y), g_rcp.v[n]);
+    const cd y2 = cmul(y, y);
+    cd s = {0.0, 0.0};
+    for (int j = 0; j < EXP_NTERMS; ++j) {
+        const double w = mom ? mom[min(j + m / 2, GAUSS_NMOM - 1)] : 1.0;
+        s.re = fma(t.re, w, s.re);
+        s.im = fma(t.im, w, s.im);
+        t = cscale(cmul(t, y2), -g_rcp.v[j + 1] * g_rcp.v[m + j + 1]);
+    }
+    return s;
+}
+
+// The expansion record of one element in the domain on one side of it, order m
+// of it (and the head with order 0); see ExpHead.
+__device__ __forceinline__ void setup_expansion(char* g, const GeomLayout& L, int N, int q, int e, int side, int m)
+{
+    const double2* nodes = tab<double2>(g, L.nodes);
+    const int2 ab = tab<int2>(g, L.elnodes)[e];
+    const IfacePlan P = tab<IfacePlan>(g, L.iface)[tab<int>(g, L.elif)[e]];
+    const int d = side ? P.dr : P.dl;
+    const DomIn* in = tab<DomIn>(g, L.dom_in);
+    const cd k = {in[d].k[0], in[d].k[1]};
+    const double dx = nodes[ab.y].x - nodes[ab.x].x, dy = nodes[ab.y].y - nodes[ab.x].y;
+    const double a = 0.5 * sqrt(dx * dx + dy * dy);
+    const double ak = hypot(k.re, k.im), ka = ak * a;
+    const cd y = cscale(k, 0.5 * a);
+    double* rec = tabw<double>(g, L.expn) + ((size_t)side * N + e) * L.exp_stride;
+    if (m == 0) {
+        const double inf = __longlong_as_double(0x7ff0000000000000ll);
+        const bool ok = ka >= EXP_KA_MIN && ka <= EXP_KA_MAX;
+        auto sq = [](double v) { return v * v; };
+        auto lim = [&](double x, double kamax) { return ok && ka <= kamax ? sq(a / x) : inf; };
+        ExpHead* H = reinterpret_cast<ExpHead*>(rec);
+        H->close2 = lim(EXP_X20, EXP_KA_MAX);
+        H->near64 = fmax(H->close2, sq(HANKEL_XS_F64 / ak));
+        H->lim8 = lim(EXP_X8, EXP_KA8);
+        H->lim10 = lim(EXP_X10, EXP_KA10);
+        H->lim12 = lim(EXP_X12, EXP_KA12);
+        H->lim16 = lim(EXP_X16, EXP_KA16);
+        H->near32 = fmax(lim(EXP32_X16, EXP_KA_MAX), sq(HANKEL_XS_F32 / ak));
+        H->lim32_4 = lim(EXP32_X4, EXP32_KA4);
+        H->lim32_6 = lim(EXP32_X6, EXP32_KA6);
+        H->lim32_8 = lim(EXP32_X8, EXP32_KA8);
+    }
+    const int cw = L.exp_cplx ? 2 : 1;  // doubles per coefficient
+    double* c = rec + EXP_HEAD + cw * exp_pos(m);
+    auto put = [&](int i, cd v) {
+        c[cw * i] = v.re;
+        if (cw == 2) c[cw * i + 1] = v.im;
+    };
+    const double* mom = GAUSS_MOM[q - 1];
+    if (m & 1) {
+        const cd u0 = cscale(bessel_sum(m - 1, y, mom), a), u1 = cscale(bessel_sum(m + 1, y, mom), a);
+        put(0, {u0.re - u1.re, u0.im - u1.im});
+        put(1, {u0.re + u1.re, u0.im + u1.im});
+    } else {
+        put(0, cscale(bessel_sum(m, y, mom), m ? 2.0 * a : a));
+        const cd v1 = bessel_sum(m + 1, y, nullptr);
+        if (m == 0) {
+            put(1, cscale(v1, -2.0));
+        } else {
+            const cd v0 = bessel_sum(m - 1, y, nullptr);
+            put(1, {2.0 * (v0.re - v1.re), 2.0 * (v0.im - v1.im)});
+            put(2, {2.0 * (v0.re + v1.re), 2.0 * (v0.im + v1.im)});
+        }
+    }
+}
+
 // All device tables of a problem in one launch: they depend on the uploaded
 // inputs alone (a lane forms the element length or the wavenumber it needs
 // again), so nothing has to wait for another table.  Block 0 takes the
-// domains and the Gauss rule, then come the elements, then the self terms of
-// both sides.  Bound by one lane's chain of dependent operations, not by the
-// work.  Measured with the assembly of 777 elements behind it: 346 us while
-// four launches ran in turn (one of them, 39 us, a Newton iteration for the
-// Gauss rule), 288 us with this one and the rule as a table.
+// domains and the Gauss rule, then come the elements, the self terms of both
+// sides and the expansion records, one order of one record per lane.  Bound by
+// one lane's chain of dependent operations, not by the work.  Measured with
+// the assembly of 777 elements behind it: 346 us while four launches ran in
+// turn (one of them, 39 us, a Newton iteration for the Gauss rule), 288 us
+// with this one and the rule as a table.
 constexpr int SETUP_BS = 64;
 __global__ __launch_bounds__(SETUP_BS) void k_setup(char* g, GeomLayout L, int N, int n_dom, int q, int eblocks)
 {
@@ -261,51 +288,56 @@ __global__ __launch_bounds__(SETUP_BS) void k_setup(char* g, GeomLayout L, int N
         return;
     }
     b -= 1;
-    if (b < eblocks) {
-        const int e = b * SETUP_BS + t;
-        if (e < N) setup_element(g, L, e, q);
-        return;
-    }
-    b -= eblocks;
-    const int side = b >= eblocks;
-    const int e = (b - side * eblocks) * SETUP_BS + t;
-    if (e < N) setup_self(g, L, N, e, side);
+    const int part = b / eblocks, e = (b - part * eblocks) * SETUP_BS + t;
+    if (e >= N) return;
+    if (part == 0)
+        setup_element(g, L, e);
+    else if (part <= 2)
+        setup_self(g, L, N, e, part - 1);
+    else
+        setup_expansion(g, L, N, q, e, (part - 3) & 1, (part - 3) >> 1);
 }
 
 // ---------------------------------------------------------------------------
 // Fused assembly of one equation block (one side of an interface) against the
 // elements of one interface.  Operators (eqs. (stmp)-(ddtmp)) of domain d
-// between collocation point x_i and element j:
+// between collocation point x_i and element j, by the q-point Gauss rule:
 //   S  = (i/4)   sum_g w_g H0(k r_g)
 //   D  = (ik/4)  sum_g w_g H1(k r_g) (r_g . n_j)/r_g
 //   D* = -(ik/4) sum_g w_g H1(k r_g) (r_g . n_i)/r_g
 //   N  = k^2 (n_i.n_j) S + (ik/4)[E(b_j) - E(a_j)],  E(p) = H1(k|x_i-p|) t_i.(x_i-p)/|x_i-p|
 // (N by the identity d2G/dnx dny = k^2 (nx.ny) G - d2G/dtx dty, exact on a
-// flat element; E at the shared end nodes is carried from element to element).
+// flat element).
 // Block entries (sigma = +1 if the normal leaves domain d, eps = eps_d):
 //   standard row, scale s:  A[row, u_j] = s (delta/2 + sigma D),   A[row, w_j] = -s sigma eps S
 //   Burton-Miller row, c:   A[row, u_j] = delta/2 + sigma (D + c N),
 //                           A[row, w_j] = -sigma eps S + c (eps delta/2 - sigma eps D*)
-// One lane per collocation row (a workgroup: ROW_TILE rows against a chunk of
-// COL_CHUNK source elements).  The chunk's Gauss points and element data are
-// staged in LDS once per workgroup; each wave then splits the chunk by a
-// wave-uniform test: an element whose every point lies at least XS/|k| from
-// all of the wave's collocation points is "far" and takes the large-argument
-// Hankel form alone (hankel01_far: no series, no per-lane branch); the rest
-// (the element itself, its neighbours, close parts of a non-convex curve)
-// take the general per-lane evaluation.  The far elements are walked first,
-// the near ones after, so that the series coefficients are not live in the
-// far loop.  Stores are coalesced column-major (consecutive lanes = rows).
+//
+// All four sums come from ONE evaluation of H0 and H1, at the element's
+// midpoint: with r = |x_i - c_j|, phi the angle of x_i - c_j to the element's
+// tangent, s the position on the element, Graf's addition theorem gives
+//   H0(k |x_i - c_j - s t_j|) = sum_{m in Z} J_m(k s) H_m(k r) cos(m phi),   |s| < r,
+// so that the rule's sums, whatever its order, are
+//   sum_g w_g H0                 = sum_{m even} mu_m H_m cos m phi,   mu_m = sum_g w_g J_m(k s_g)
+//   sum_g w_g H1 (r_g.t_j)/r_g   = sum_{p odd > 0} (mu_{p-1} - mu_{p+1}) H_p cos p phi
+//   sum_g w_g H1 (r_g.n_j)/r_g   = sum_{p odd > 0} (mu_{p-1} + mu_{p+1}) H_p sin p phi
+// (odd moments vanish, the rule is symmetric; the two vector sums are -1/k
+// times the gradient of the first), and with nu_m = 2 J_m(k h/2) the
+// components along t_j and n_j of the end-point difference are
+//   sum_{p even >= 0} (nu_{p-1} - nu_{p+1}) H_p cos p phi   (p = 0: -nu_1 H_0)
+//   sum_{p even > 0}  (nu_{p-1} + nu_{p+1}) H_p sin p phi
+// without the cancellation of the two end values.  H_2, H_3, ... follow by
+// the upward recurrence (stable: it follows the growing solution), cos m phi
+// and sin m phi by the Chebyshev recurrence.  The coefficients are a record
+// per (side, element), made with the geometry tables.  Orders up to L leave a
+// relative remainder of (h/(2r))^L (and (kh/4)^L/(L+1)! for large r); each
+// record holds the distances beyond which L = 8, 10, 12, 16 and 20 leave less
+// than 4e-17.  Closer than that (a few element lengths), or for elements
+// longer than about 0.8 wavelengths, the Gauss points are evaluated one by
+// one.
 // ---------------------------------------------------------------------------
-static_assert(XS_SERIES_F64 == HANKEL_XS_F64 && XS_SERIES_F32 == HANKEL_XS_F32,
-              "the host's near-pair lists use the series radii of the device evaluator");
 
-struct GaussL {
-    double x, y, w, pad;
-};
-struct ElemL {
-    double nx, ny, ax, ay, bx, by, cx, cy, hh, pad;  // normal, nodes, midpoint, h/2
-};
+typedef const __attribute__((address_space(4))) double* ScalarPtr;  // wave-uniform addresses: scalar loads
 
 // Per-block combination constants of one equation block (see the entries above).
 struct BlockConst {
@@ -334,537 +366,395 @@ __device__ __forceinline__ BlockConst block_const(const DomConst& Dm, int sg)
     return B;
 }
 
-// End-point value E(p) = H1(k|x_i - p|) t_i.(x_i - p)/|x_i - p| (without the ik/4).
-template <bool CPLX, bool FAR>
-__device__ __forceinline__ cd end_value(const WaveConst& W, double xi, double yi, double tix, double tiy, double px,
-                                        double py)
-{
-    const double dx = xi - px, dy = yi - py;
-    cd h0, h1;
-    double rinv;
-    if (FAR) {
-        rinv = hankel01_far<CPLX, false>(W, dx, dy, h0, h1);
-    } else {
-        const double r2 = dx * dx + dy * dy;
-        double r;
-        sqrt_rsqrt(r2, r, rinv);
-        h1 = hankel1_only<CPLX, true>(W, r, r2, rinv, rsqrt_nr(r));
-    }
-    return cscale(h1, (tix * dx + tiy * dy) * rinv);
-}
+// Waves per SIMD that the far and near kernels leave room for.
+constexpr int FAR_WAVES = 3, NEAR_WAVES = 2;
 
-// One matrix entry pair (u column, w column) of row i against element j.
-template <int Q, bool CPLX, bool BM, bool FAR>
-__device__ __forceinline__ void element_entries(const WaveConst& W, const BlockConst& B, const ElemRec& Ei,
-                                                const ElemL& Ej, const GaussL* __restrict__ gp, int q_rt,
-                                                bool diag, cd selfS, cd& Ea, bool carry, cd& au, cd& aw)
-{
-    const int q = Q > 0 ? Q : q_rt;
-    const double xi = Ei.cx, yi = Ei.cy;
-    cd sS = {0.0, 0.0}, sD = {0.0, 0.0}, sDs = {0.0, 0.0};
-    if (FAR || !diag) {
-#pragma unroll ASM_GAUSS_UNROLL
-        for (int g = 0; g < (Q > 0 ? Q : QMAX); ++g) {
-            if (Q == 0 && g >= q) break;
-            const GaussL P = gp[g];
-            const double rx = xi - P.x, ry = yi - P.y;
-            cd h0, h1;
-            double rinv;
-            if (FAR) {
-                rinv = hankel01_far<CPLX, true>(W, rx, ry, h0, h1);
-            } else {
-                const double r2 = fma(rx, rx, ry * ry);
-                double r;
-                sqrt_rsqrt(r2, r, rinv);
-                hankel01<CPLX, true>(W, r, r2, rinv, rsqrt_nr(r), h0, h1);
-            }
-            sS.re = fma(P.w, h0.re, sS.re);
-            sS.im = fma(P.w, h0.im, sS.im);
-            const double wr = P.w * rinv;
-            const double wd = wr * fma(rx, Ej.nx, ry * Ej.ny);
-            sD.re = fma(wd, h1.re, sD.re);
-            sD.im = fma(wd, h1.im, sD.im);
-            if (BM) {
-                const double ws = wr * fma(rx, Ei.nx, ry * Ei.ny);
-                sDs.re = fma(ws, h1.re, sDs.re);
-                sDs.im = fma(ws, h1.im, sDs.im);
-            }
-        }
-    }
-    if (FAR || !diag) {
-        au = cmul(B.cD, sD);
-        aw = cmul(B.cS, sS);
-    } else {
-        // self term: D = D* = 0 on a flat element, S analytic; sS carries S / (i/4)
-        sS = cdiv(selfS, B.iq);
-        au = B.du;
-        aw = cmul(B.cS, sS);
-        if (BM) aw = cadd(aw, B.dw);
-    }
-    if (BM) {
-        if (!carry) Ea = end_value<CPLX, FAR>(W, xi, yi, Ei.tx, Ei.ty, Ej.ax, Ej.ay);
-        const cd Eb = end_value<CPLX, FAR>(W, xi, yi, Ei.tx, Ei.ty, Ej.bx, Ej.by);
-        const double ninj = Ei.nx * Ej.nx + Ei.ny * Ej.ny;
-        au = cadd(au, cadd(cscale(cmul(B.cNS, sS), ninj), cmul(B.cNE, {Eb.re - Ea.re, Eb.im - Ea.im})));
-        aw = cadd(aw, cmul(B.cDs, sDs));
-        Ea = Eb;  // E(b_j) = E(a_{j+1}): carried to the next element of the same walk
-    }
-}
-
-// ---------------------------------------------------------------------------
-// FP32 assembly (precision path).  Entries are stored as complex64.  What
-// decides the accuracy stays in FP64: the distance r and the phase k r (FP32
-// would put an error of |k r| 6e-8 into every far entry), the ascending
-// series for |k r| < 4, the self terms.  The amplitude polynomials of
-// |k r| >= 4 (degree 6 in w), sin/cos of the phase reduced to [-pi, pi] and
-// the quadrature sums run in FP32.
-// ---------------------------------------------------------------------------
-struct cf {
-    float re, im;
+// The sums of one (row, element) pair without their i/4, i k/4 factors.
+struct PairSums {
+    cd S;       // sum w H0
+    cd Gt, Gn;  // sum w H1 r/|r| along t_j and n_j
+    cd Tt, Tn;  // end-point difference along t_j and n_j
 };
-__device__ __forceinline__ cf cmulf(cf a, cf b) { return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
 
+__device__ __forceinline__ void add_scaled(cd& s, double c, double f, cd v)
+{
+    const double w = c * f;
+    s.re = fma(w, v.re, s.re);
+    s.im = fma(w, v.im, s.im);
+}
+__device__ __forceinline__ void add_scaled(cd& s, cd c, double f, cd v)
+{
+    const cd w = {c.re * f, c.im * f};
+    s.re = fma(w.re, v.re, fma(-w.im, v.im, s.re));
+    s.im = fma(w.re, v.im, fma(w.im, v.re, s.im));
+}
+
+// coefficient i of a record (cw doubles each: 2 where some domain of the
+// problem is lossy)
 template <bool CPLX>
-__device__ __forceinline__ void hankel_far32_body(const WaveConst& W64, const WaveConst32& W, double r, float& h0r,
-                                                  float& h0i, float& h1r, float& h1i);
+struct Coef;
+template <>
+struct Coef<false> {
+    typedef double T;
+    static __device__ __forceinline__ double get(ScalarPtr c, int cw, int i) { return c[cw * i]; }
+};
+template <>
+struct Coef<true> {
+    typedef cd T;
+    static __device__ __forceinline__ cd get(ScalarPtr c, int, int i) { return {c[2 * i], c[2 * i + 1]}; }
+};
 
-// H0, H1 at k r with r given in FP64; result in FP32.
-template <bool CPLX, bool MEM = false>
-__device__ __forceinline__ void hankel01_mixed(const WaveConst& W64, const WaveConst32& W, double r, cf& h0, cf& h1)
+// The expansion up to order Lo (even, >= BASE, uniform over the wave; orders
+// up to BASE are unrolled): hz = H0, h1 = H1 at the midpoint distance, c1, s1
+// = cos phi, sin phi, tz = 2/(k r).
+template <bool CPLX, bool BM, int BASE>
+__device__ __forceinline__ PairSums expand(ScalarPtr c, int cw, int Lo, cd hz, cd h1, double c1, double s1, cd tz)
 {
-    // one write of h0, h1 after the join (as in hankel01)
-    float h0r, h0i, h1r, h1i;
-    if (r * r < (double)W.r2_small) {
-        const double r2 = r * r, rinv = 1.0 / r, sr = sqrt(rinv);
-        cd a0, a1;
-        hankel01<CPLX, MEM>(W64, r, r2, rinv, sr, a0, a1);
-        h0r = (float)a0.re;
-        h0i = (float)a0.im;
-        h1r = (float)a1.re;
-        h1i = (float)a1.im;
-    } else {
-        hankel_far32_body<CPLX>(W64, W, r, h0r, h0i, h1r, h1i);
-    }
-    h0 = {h0r, h0i};
-    h1 = {h1r, h1i};
-}
-
-// The large-argument branch of hankel01_mixed.
-template <bool CPLX>
-__device__ __forceinline__ void hankel_far32_body(const WaveConst& W64, const WaveConst32& W, double r, float& h0r,
-                                                  float& h0i, float& h1r, float& h1i)
-{
-    cf h0, h1;
-    constexpr double TWO_PI = 6.283185307179586476925;
-    constexpr double INV_TWO_PI = 0.159154943091895335769;
-    const double ph = W64.kr * r;
-    const double red = fma(-rint(ph * INV_TWO_PI), TWO_PI, ph);  // |red| <= pi (+ rounding)
-    float sn, cs;
-    sincosf((float)red, &sn, &cs);
-    const float rf = (float)r;
-    const float rinv = 1.0f / rf;
-    const float rho = rinv * rinv;
-    const float srinv = sqrtf(rinv);
-    if (!CPLX) {
-        const float w = W.wr * rho;
-        const float m0 = poly_real(HANKEL_M0_F32, w), n0 = poly_real(HANKEL_N0_F32, w);
-        const float m1 = poly_real(HANKEL_M1_F32, w), n1 = poly_real(HANKEL_N1_F32, w);
-        const float u = W.ur * rinv;
-        const cf e = {cs * srinv, sn * srinv};
-        h0 = cmulf(cmulf(e, {W.a0r, W.a0i}), {m0, u * n0});
-        h1 = cmulf(cmulf(e, {W.a1r, W.a1i}), {m1, u * n1});
-    } else {
-        const float x = W.wr * rho, y = W.wi * rho;
-        const float R = 2.0f * x, S = fmaf(x, x, y * y);
-        cf m0, n0, m1, n1;
-        poly_cplx(HANKEL_M0_F32, x, y, R, S, m0.re, m0.im);
-        poly_cplx(HANKEL_N0_F32, x, y, R, S, n0.re, n0.im);
-        poly_cplx(HANKEL_M1_F32, x, y, R, S, m1.re, m1.im);
-        poly_cplx(HANKEL_N1_F32, x, y, R, S, n1.re, n1.im);
-        const cf u = {W.ur * rinv, W.ui * rinv};
-        const cf un0 = cmulf(u, n0), un1 = cmulf(u, n1);
-        const float damp = (float)exp(-W64.ki * r) * srinv;
-        const cf e = {cs * damp, sn * damp};
-        h0 = cmulf(cmulf(e, {W.a0r, W.a0i}), {m0.re - un0.im, m0.im + un0.re});
-        h1 = cmulf(cmulf(e, {W.a1r, W.a1i}), {m1.re - un1.im, m1.im + un1.re});
-    }
-    h0r = h0.re;
-    h0i = h0.im;
-    h1r = h1.re;
-    h1i = h1.im;
-}
-
-// FP32 large-argument form for |k r| >= XS_F32 (no series, no per-lane
-// branch): distance, phase and its reduction by pi/2 in FP64, the reduced
-// angle's sine and cosine, the amplitude polynomials and the products in FP32.
-// Returns 1/r.
-__device__ __forceinline__ void sincos_cw32(double x, float& s, float& c)
-{
-    constexpr double TWO_OVER_PI = 0x1.45f306dc9c883p-1;
-    constexpr double P1 = 0x1.921fb54442d18p+0;
-    constexpr double P2 = 0x1.1a62633145c07p-54;
-    const double n = rint(x * TWO_OVER_PI);
-    const float t = (float)fma(-n, P2, fma(-n, P1, x));
-    const float u = t * t;
-    // Taylor series on |t| <= pi/4: sin to t^9 (truncation < 2e-9), cos to t^10 (< 2e-10)
-    const float st = fmaf(t * u, fmaf(u, fmaf(u, fmaf(u, 1.0f / 362880.0f, -1.0f / 5040.0f), 1.0f / 120.0f),
-                                      -1.0f / 6.0f), t);
-    const float ct = fmaf(u, fmaf(u, fmaf(u, fmaf(u, fmaf(u, -1.0f / 3628800.0f, 1.0f / 40320.0f), -1.0f / 720.0f),
-                                          1.0f / 24.0f), -0.5f), 1.0f);
-    const unsigned q = (unsigned)(int)n;
-    const float a = (q & 1u) ? ct : st;
-    const float b = (q & 1u) ? st : ct;
-    s = __uint_as_float(__float_as_uint(a) ^ ((q & 2u) << 30));
-    c = __uint_as_float(__float_as_uint(b) ^ (((q + 1u) & 2u) << 30));
-}
-
-template <bool CPLX, bool WANT_H0>
-__device__ __forceinline__ float hankel01_far32(const WaveConst& W64, const WaveConst32& W, double rx, double ry,
-                                                cf& h0, cf& h1)
-{
-    constexpr double PI_4 = 0x1.921fb54442d18p-1;
-    const double r2 = fma(rx, rx, ry * ry);
-    double r, rinv;
-    sqrt_rsqrt(r2, r, rinv);
-    float sn, cs;
-    sincos_cw32(fma(W64.kr, r, -PI_4), sn, cs);
-    const float ri = (float)rinv;
-    const float sr = __builtin_amdgcn_rsqf((float)r);
-    const float rho = ri * ri;
-    if (!CPLX) {
-        const float w = W.wr * rho;
-        const float u = W.ur * ri;
-        const float a = W.ampr * sr;
-        const float er = cs * a, ei = sn * a;
-        const float m1 = poly_real(HANKEL_M1_F32, w), un1 = u * poly_real(HANKEL_N1_F32, w);
-        h1 = {fmaf(er, un1, ei * m1), fmaf(ei, un1, -er * m1)};
-        if (WANT_H0) {
-            const float m0 = poly_real(HANKEL_M0_F32, w), un0 = u * poly_real(HANKEL_N0_F32, w);
-            h0 = {fmaf(er, m0, -ei * un0), fmaf(er, un0, ei * m0)};
-        }
-    } else {
-        const float x = W.wr * rho, y = W.wi * rho;
-        const float R = 2.0f * x, S = fmaf(x, x, y * y);
-        const cf u = {W.ur * ri, W.ui * ri};
-        const float damp = expf((float)(-W64.ki * r)) * sr;
-        const cf e = cmulf({cs * damp, sn * damp}, {W.ampr, W.ampi});
-        cf m1, n1;
-        poly_cplx(HANKEL_M1_F32, x, y, R, S, m1.re, m1.im);
-        poly_cplx(HANKEL_N1_F32, x, y, R, S, n1.re, n1.im);
-        const cf un1 = cmulf(u, n1);
-        h1 = cmulf(e, {m1.im + un1.re, un1.im - m1.re});
-        if (WANT_H0) {
-            cf m0, n0;
-            poly_cplx(HANKEL_M0_F32, x, y, R, S, m0.re, m0.im);
-            poly_cplx(HANKEL_N0_F32, x, y, R, S, n0.re, n0.im);
-            const cf un0 = cmulf(u, n0);
-            h0 = cmulf(e, {m0.re - un0.im, m0.im + un0.re});
-        }
-    }
-    return ri;
-}
-
-template <bool CPLX, bool FAR>
-__device__ __forceinline__ cf end_value32(const WaveConst& W64, const WaveConst32& W, double xi, double yi, double tix,
-                                          double tiy, double px, double py)
-{
-    const double dx = xi - px, dy = yi - py;
-    cf h0, h1;
-    double rinv;
-    if (FAR) {
-        rinv = hankel01_far32<CPLX, false>(W64, W, dx, dy, h0, h1);
-    } else {
-        const double r = sqrt(dx * dx + dy * dy);
-        hankel01_mixed<CPLX, true>(W64, W, r, h0, h1);
-        rinv = 1.0 / r;
-    }
-    const float f = (float)((tix * dx + tiy * dy) * rinv);
-    return {h1.re * f, h1.im * f};
-}
-
-// FP32 sums over the Gauss points; the combination into entries runs in FP64.
-template <int Q, bool CPLX, bool BM, bool FAR>
-__device__ __forceinline__ void element_entries_f32(const WaveConst& W64, const WaveConst32& W, const BlockConst& B,
-                                                    const ElemRec& Ei, const ElemL& Ej, const GaussL* __restrict__ gp,
-                                                    int q_rt, bool diag, cd selfS, cf& Ea, bool carry, cd& au,
-                                                    cd& aw)
-{
-    const int q = Q > 0 ? Q : q_rt;
-    const double xi = Ei.cx, yi = Ei.cy;
-    const float njx = (float)Ej.nx, njy = (float)Ej.ny, nix = (float)Ei.nx, niy = (float)Ei.ny;
-    cf sS = {0.0f, 0.0f}, sD = {0.0f, 0.0f}, sDs = {0.0f, 0.0f};
-    if (FAR || !diag) {
-#pragma unroll ASM_GAUSS_UNROLL
-        for (int g = 0; g < (Q > 0 ? Q : QMAX); ++g) {
-            if (Q == 0 && g >= q) break;
-            const GaussL P = gp[g];
-            const double rx = xi - P.x, ry = yi - P.y;
-            cf h0, h1;
-            float ri;
-            if (FAR) {
-                ri = hankel01_far32<CPLX, true>(W64, W, rx, ry, h0, h1);
-            } else {
-                const double r = sqrt(fma(rx, rx, ry * ry));
-                hankel01_mixed<CPLX, true>(W64, W, r, h0, h1);
-                ri = (float)(1.0 / r);
-            }
-            const float wg = (float)P.w;
-            sS.re = fmaf(wg, h0.re, sS.re);
-            sS.im = fmaf(wg, h0.im, sS.im);
-            const float rxf = (float)rx, ryf = (float)ry, wr = wg * ri;
-            const float wd = wr * fmaf(rxf, njx, ryf * njy);
-            sD.re = fmaf(wd, h1.re, sD.re);
-            sD.im = fmaf(wd, h1.im, sD.im);
-            if (BM) {
-                const float ws = wr * fmaf(rxf, nix, ryf * niy);
-                sDs.re = fmaf(ws, h1.re, sDs.re);
-                sDs.im = fmaf(ws, h1.im, sDs.im);
-            }
-        }
-    }
-    cd sS64 = {(double)sS.re, (double)sS.im};
-    if (FAR || !diag) {
-        au = cmul(B.cD, {(double)sD.re, (double)sD.im});
-        aw = cmul(B.cS, sS64);
-    } else {
-        sS64 = cdiv(selfS, B.iq);
-        au = B.du;
-        aw = cmul(B.cS, sS64);
-        if (BM) aw = cadd(aw, B.dw);
-    }
-    if (BM) {
-        if (!carry) Ea = end_value32<CPLX, FAR>(W64, W, xi, yi, Ei.tx, Ei.ty, Ej.ax, Ej.ay);
-        const cf Eb = end_value32<CPLX, FAR>(W64, W, xi, yi, Ei.tx, Ei.ty, Ej.bx, Ej.by);
-        const double ninj = Ei.nx * Ej.nx + Ei.ny * Ej.ny;
-        au = cadd(au, cadd(cscale(cmul(B.cNS, sS64), ninj),
-                           cmul(B.cNE, {(double)Eb.re - (double)Ea.re, (double)Eb.im - (double)Ea.im})));
-        aw = cadd(aw, cmul(B.cDs, {(double)sDs.re, (double)sDs.im}));
-        Ea = Eb;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// The assembly kernels.  F32 = false: FP64 entries into A (double2) and, when
-// A32 is given, the same entries rounded to FP32 into A32 in the same pass
-// (the mixed path's inner products use that copy, its refinement residuals
-// the FP64 matrix).  F32 = true: FP32 entries into A (float2).
-// ---------------------------------------------------------------------------
-// sub < 0: the workgroup's ROW_TILE threads cover the row tile and share the
-// staged chunk (far launch).  sub >= 0: this wave alone covers rows
-// [64 sub, 64 sub + 64) of the tile and stages its own part of the chunk in
-// its own gp / ell (near launch: one list item per wave, so that waves whose
-// rows have no near element are not launched at all).  Every wave of the
-// workgroup reaches the one barrier, item or not (act).
-template <int Q, bool CPLX, bool BM, bool F32, bool NEAR>
-__device__ __forceinline__ void assemble_chunk(const char* __restrict__ g, const GeomLayout& L, int N, int n_if,
-                                               int q_rt, int tile, int sub, int chunk, int part, int side, void* Av,
-                                               size_t lda, float2* __restrict__ A32, size_t lda32,
-                                               GaussL* __restrict__ gp, ElemL* __restrict__ ell, bool act)
-{
-    static_assert(COL_CHUNK <= 32, "the near-element mask is one 32-bit word");
-    constexpr int QS = Q > 0 ? Q : QMAX;
-    const int nst = sub < 0 ? ROW_TILE : 64;
-    const int li_st = sub < 0 ? (int)threadIdx.x : (int)(threadIdx.x & 63);
-    const int li = sub < 0 ? (int)threadIdx.x : sub * 64 + (int)(threadIdx.x & 63);
-    Tile rt{}, cc{};
-    int d = 0, sg = 0;
-    IfacePlan P{};
-    if (act) {
-        rt = tab<Tile>(g, L.rtiles)[tile];
-        cc = tab<Tile>(g, L.cchunks)[chunk];
-        if (part >= 0) {  // near launch: NEAR_PART elements of the chunk
-            cc.start += part * NEAR_PART;
-            cc.count = min(NEAR_PART, cc.count - part * NEAR_PART);
-        }
-        P = tab<IfacePlan>(g, L.iface)[rt.iface];
-        d = side ? P.dr : P.dl;
-        sg = tab<int>(g, L.sigma)[d * n_if + cc.iface];
-    }
-    const int i = rt.start + li;
-    const size_t row = (size_t)((side ? P.row_r : P.row_l) + (i - P.off));
-    const int cnt = cc.count;
-    auto store = [&](int j, cd au, cd aw) {
-        if (F32) {
-            float2* A = static_cast<float2*>(Av);
-            A[row + (size_t)j * lda] = make_float2((float)au.re, (float)au.im);
-            A[row + (size_t)(N + j) * lda] = make_float2((float)aw.re, (float)aw.im);
-        } else {
-            double2* A = static_cast<double2*>(Av);
-            A[row + (size_t)j * lda] = make_double2(au.re, au.im);
-            A[row + (size_t)(N + j) * lda] = make_double2(aw.re, aw.im);
-            if (A32) {
-                A32[row + (size_t)j * lda32] = make_float2((float)au.re, (float)au.im);
-                A32[row + (size_t)(N + j) * lda32] = make_float2((float)aw.re, (float)aw.im);
-            }
+    using K = Coef<CPLX>;
+    PairSums P;
+    P.S = P.Gt = P.Gn = P.Tt = P.Tn = {0.0, 0.0};
+    add_scaled(P.S, K::get(c, cw, 0), 1.0, hz);
+    if (BM) add_scaled(P.Tt, K::get(c, cw, 1), 1.0, hz);
+    cd Hp = hz, H = h1, q = {0.0, 0.0};
+    double cp = 1.0, cc = c1, sp = 0.0, ss = s1;
+    const double c2 = c1 + c1;
+    auto next = [&]() {  // order m -> m + 1
+        q.re += tz.re;
+        if (CPLX) q.im += tz.im;  // q = m tz
+        cd Hn;
+        if (CPLX)
+            Hn = {fma(q.re, H.re, fma(-q.im, H.im, -Hp.re)), fma(q.re, H.im, fma(q.im, H.re, -Hp.im))};
+        else
+            Hn = {fma(q.re, H.re, -Hp.re), fma(q.re, H.im, -Hp.im)};
+        Hp = H;
+        H = Hn;
+        const double cn = fma(c2, cc, -cp), sn = fma(c2, ss, -sp);
+        cp = cc;
+        cc = cn;
+        sp = ss;
+        ss = sn;
+    };
+    auto two = [&](int p) {  // orders p (odd) and p + 1
+        const int o = exp_pos(p);
+        if (BM) add_scaled(P.Gt, K::get(c, cw, o), cc, H);
+        add_scaled(P.Gn, K::get(c, cw, o + 1), ss, H);
+        next();
+        add_scaled(P.S, K::get(c, cw, o + 2), cc, H);
+        if (BM) {
+            add_scaled(P.Tt, K::get(c, cw, o + 3), cc, H);
+            add_scaled(P.Tn, K::get(c, cw, o + 4), ss, H);
         }
     };
-    if (!NEAR && sg == 0) {  // uniform over the workgroup; the far launch writes the zero block
-        if (li >= rt.count) return;
-        for (int jj = 0; jj < cnt; ++jj) store(cc.start + jj, {0.0, 0.0}, {0.0, 0.0});
+    two(1);
+#pragma unroll
+    for (int p = 3; p < BASE; p += 2) {
+        next();
+        two(p);
+    }
+    for (int p = BASE + 1; p < Lo; p += 2) {
+        next();
+        two(p);
+    }
+    return P;
+}
+
+// Entries of the u and w columns from the sums (tt = t_i.t_j, tn = t_i.n_j;
+// in the plane n_i.n_j = tt and n_i.t_j = -tn).
+template <bool BM>
+__device__ __forceinline__ void combine(const BlockConst& B, const PairSums& P, double tt, double tn, cd& au, cd& aw)
+{
+    au = cmul(B.cD, P.Gn);
+    aw = cmul(B.cS, P.S);
+    if (BM) {
+        const cd Ds = {fma(tt, P.Gn.re, -tn * P.Gt.re), fma(tt, P.Gn.im, -tn * P.Gt.im)};
+        const cd T = {fma(tt, P.Tt.re, tn * P.Tn.re), fma(tt, P.Tt.im, tn * P.Tn.im)};
+        au = cadd(au, cadd(cscale(cmul(B.cNS, P.S), tt), cmul(B.cNE, T)));
+        aw = cadd(aw, cmul(B.cDs, Ds));
+    }
+}
+
+__device__ __forceinline__ void store_entry(double2* A, size_t lda, float2* A32, size_t row, int j, int N, cd au, cd aw)
+{
+    A[row + (size_t)j * lda] = make_double2(au.re, au.im);
+    A[row + (size_t)(N + j) * lda] = make_double2(aw.re, aw.im);
+    if (A32) {
+        A32[row + (size_t)j * lda] = make_float2((float)au.re, (float)au.im);
+        A32[row + (size_t)(N + j) * lda] = make_float2((float)aw.re, (float)aw.im);
+    }
+}
+__device__ __forceinline__ void store_entry(float2* A, size_t lda, float2*, size_t row, int j, int N, cd au, cd aw)
+{
+    A[row + (size_t)j * lda] = make_float2((float)au.re, (float)au.im);
+    A[row + (size_t)(N + j) * lda] = make_float2((float)aw.re, (float)aw.im);
+}
+
+// Squared distance of a collocation point and a midpoint.  The far and the
+// near launch compare it, formed by the same operations, with the same limit,
+// so each element of a wave is taken by exactly one of them.
+__device__ __forceinline__ double pair_r2(double rx, double ry) { return fma(rx, rx, ry * ry); }
+
+// Element records through scalar loads: position of each field in ElemRec
+constexpr int E_CX = 0, E_CY = 1, E_TX = 2, E_TY = 3;
+static_assert(offsetof(ElemRec, cx) == 0 && offsetof(ElemRec, tx) == 16 && offsetof(ElemRec, nx) == 32,
+              "scalar reads of the element records");
+
+// A table entry at a wave-uniform address, read by scalar loads once (stores
+// to the matrix do not make the compiler read it again).
+template <class T>
+__device__ __forceinline__ T scalar_copy(const T* p)
+{
+    static_assert(sizeof(T) % sizeof(double) == 0, "copied as doubles");
+    T out;
+    ScalarPtr src = (ScalarPtr)p;
+    double* dst = reinterpret_cast<double*>(&out);
+#pragma unroll
+    for (size_t k = 0; k < sizeof(T) / sizeof(double); ++k) dst[k] = src[k];
+    return out;
+}
+
+// What a launch needs besides its rows.
+template <class T2>
+struct AsmArgs {
+    const char* g;
+    GeomLayout L;
+    int N, n_if, q, side;
+    T2* A;
+    float2* A32;  // FP32 copy of an FP64 matrix, or null
+    size_t lda;
+};
+
+// ---------------------------------------------------------------------------
+// Far launch: every element whose midpoint is, for all rows of the wave, at
+// least XS/|k| away and within reach of the expansion.  One lane per row, one
+// wave per (64 rows, `per` elements of a column chunk); the element's data are
+// wave-uniform (scalar loads), so there is no LDS and no barrier, and a wave
+// skips the elements that the near launch takes by one ballot.
+// Bound by FP64 VALU issue: about 360 instructions per pair of a
+// Burton-Miller row and 270 of a standard row (real k, FP64), of which the
+// Hankel evaluation is 150 (point by point the q-point rule took q + 1 of
+// them).  Distance, phase and recurrences are FP64 in the FP32 assembly too
+// (an FP64 FMA issues as fast as an FP32 one); that path takes the shorter
+// amplitude polynomials and fewer orders.  Measured, geometry tables and
+// assembly, against point-by-point sums: kite of 4096 elements, one lossy
+// wavenumber, 2019 -> 645 us; 8192 elements in FP32 3280 -> 1106 us, the
+// entries' error against 32-digit values 2 to 5 times smaller; 777 elements at
+// k h = 0.8 288 -> 68 us; three sectors, 1900 elements, 1005 -> 185 us.
+// Entries in FP64 are as close to 32-digit values as before (the phase k r,
+// once averaged over q points, is formed from a compensated distance).
+// ---------------------------------------------------------------------------
+template <bool CPLX, bool BM, class T2>
+__global__ __launch_bounds__(ROW_TILE, FAR_WAVES) void k_assemble_far(const AsmArgs<T2> P, const int* __restrict__ tiles,
+                                                                      int per)
+{
+    constexpr bool LOW = sizeof(T2) == sizeof(float2);
+    constexpr int BASE = LOW ? 4 : 8;
+    const Tile rt = tab<Tile>(P.g, P.L.rtiles)[tiles[blockIdx.x]];
+    const int parts = COL_CHUNK / per;
+    const Tile cc = tab<Tile>(P.g, P.L.cchunks)[blockIdx.y / parts];
+    const int j0 = (int)(blockIdx.y % parts) * per;
+    const int j1 = min(j0 + per, cc.count);
+    const int li = threadIdx.x;
+    if (li >= rt.count || j0 >= j1) return;
+    const IfacePlan F = tab<IfacePlan>(P.g, P.L.iface)[rt.iface];
+    const int d = P.side ? F.dr : F.dl;
+    const int sg = tab<int>(P.g, P.L.sigma)[d * P.n_if + cc.iface];
+    const int i = rt.start + li;
+    const size_t row = (size_t)((P.side ? F.row_r : F.row_l) + (i - F.off));
+    if (sg == 0) {  // this domain does not touch the interface
+        for (int jj = j0; jj < j1; ++jj) store_entry(P.A, P.lda, P.A32, row, cc.start + jj, P.N, {0.0, 0.0}, {0.0, 0.0});
         return;
     }
-    act = act && sg != 0;
-    // stage the chunk: Gauss points (x, y, weight) and element data
-    if (act) {
-        const int q = Q > 0 ? Q : q_rt;
-        const GaussRec* gq = tab<GaussRec>(g, L.gauss);
-        for (int t = li_st; t < cnt * q; t += nst) {
-            const int e = t / q, gg = t - e * q;
-            const GaussRec& G = gq[cc.start + e];
-            gp[e * QS + gg] = GaussL{G.x[gg], G.y[gg], G.w[gg], 0.0};
+    // the record of an element holds both of its sides: take the one in domain d
+    const int jside = tab<IfacePlan>(P.g, P.L.iface)[cc.iface].dr == d ? 1 : 0;
+    const WaveConst W = scalar_copy(tab<WaveConst>(P.g, P.L.wave) + d);
+    const BlockConst B = block_const<BM>(tab<DomConst>(P.g, P.L.dom)[d], sg);
+    const ElemRec* Ei = tab<ElemRec>(P.g, P.L.elem) + i;
+    const double xi = Ei->cx, yi = Ei->cy, tix = Ei->tx, tiy = Ei->ty;
+    const cd tk = {W.tkr, W.tki};
+    const int cw = P.L.exp_cplx ? 2 : 1;
+    for (int jj = j0; jj < j1; ++jj) {
+        const int j = cc.start + jj;
+        ScalarPtr Ej = (ScalarPtr)(tab<ElemRec>(P.g, P.L.elem) + j);
+        ScalarPtr rec = (ScalarPtr)(tab<double>(P.g, P.L.expn) + ((size_t)jside * P.N + j) * P.L.exp_stride);
+        const double cx = Ej[E_CX], cy = Ej[E_CY], tx = Ej[E_TX], ty = Ej[E_TY];
+        const double rx = xi - cx, ry = yi - cy;
+        const double r2 = pair_r2(rx, ry);
+        auto closer = [&](double lim2) { return __builtin_amdgcn_ballot_w64(r2 < lim2) != 0; };
+        if (closer(rec[LOW ? EXP_H_NEAR32 : EXP_H_NEAR64])) continue;
+        int Lo = BASE;
+        if (LOW) {
+            if (closer(rec[EXP_H_LIM32]))
+                Lo = !closer(rec[EXP_H_LIM32 + 1]) ? 6 : !closer(rec[EXP_H_LIM32 + 2]) ? 8 : 16;
+        } else if (closer(rec[EXP_H_LIM])) {
+            Lo = !closer(rec[EXP_H_LIM + 1]) ? 10 : !closer(rec[EXP_H_LIM + 2]) ? 12 : !closer(rec[EXP_H_LIM + 3]) ? 16 : 20;
         }
-        const ElemRec* el = tab<ElemRec>(g, L.elem);
-        for (int t = li_st; t < cnt; t += nst) {
-            const ElemRec& E = el[cc.start + t];
-            ell[t] = ElemL{E.nx, E.ny, E.ax, E.ay, E.bx, E.by, E.cx, E.cy, 0.5 * E.h, 0.0};
+        // the rounding of the two differences, for the phase
+        const double ex = diff_error(xi, cx, rx), ey = diff_error(yi, cy, ry);
+        cd h0, h1;
+        const double rinv = hankel01_far<CPLX, LOW>(W, rx, ry, ex, ey, r2, h0, h1);
+        const double c1 = fma(rx, tx, ry * ty) * rinv, s1 = fma(ry, tx, -rx * ty) * rinv;
+        const PairSums sums =
+            expand<CPLX, BM, BASE>(rec + EXP_HEAD, cw, Lo, h0, h1, c1, s1, {tk.re * rinv, CPLX ? tk.im * rinv : 0.0});
+        cd au, aw;
+        combine<BM>(B, sums, fma(tix, tx, tiy * ty), fma(tiy, tx, -tix * ty), au, aw);
+        store_entry(P.A, P.lda, P.A32, row, j, P.N, au, aw);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Near launch: the elements the far launch leaves, over the host's list of
+// (row tile and its 64-row wave, column chunk, part of NEAR_PART elements)
+// items that may hold one; one wave, one workgroup per `per` elements of an
+// item.  Lanes beyond the expansion's reach take it with the general Hankel
+// evaluation (series or large-argument form per lane).  The others, a few
+// element lengths away or on the diagonal, go to a list in LDS and are then
+// evaluated point by point, one Gauss point or end point of one pair per lane:
+// with 64 consecutive rows against one element only a handful of lanes are
+// that close, and a chain of q + 2 Hankel evaluations is what a small problem
+// waits for.  Bound by that chain (small problems) and by FP64 VALU issue.
+// Measured, Burton-Miller rows: disk of 256 elements 51 us with every element
+// evaluated point by point by all lanes, 30 us with one close pair per lane,
+// 15 us with one point per lane; kite of 4096 elements 296 -> 121 us.
+// ---------------------------------------------------------------------------
+template <bool CPLX, bool BM, class T2>
+__global__ __launch_bounds__(64, NEAR_WAVES) void k_assemble_near(const AsmArgs<T2> P, const int* __restrict__ items,
+                                                                  int per)
+{
+    constexpr bool LOW = sizeof(T2) == sizeof(float2);
+    constexpr int NV = BM ? 8 : 4;  // partial sums of a point: S, D and, Burton-Miller rows, D*, E
+    __shared__ unsigned char todo[64 * NEAR_PART];
+    __shared__ double part[NV][64];
+    static_assert(64 * NEAR_PART <= 256, "a list entry is one byte");
+    const int parts = NEAR_PART / per;
+    const int* it = items + 3 * (blockIdx.x / parts);
+    const Tile rt = tab<Tile>(P.g, P.L.rtiles)[it[0] >> 2];
+    const Tile cc = tab<Tile>(P.g, P.L.cchunks)[it[1]];
+    const int j0 = it[2] * NEAR_PART + (int)(blockIdx.x % parts) * per, cnt = min(per, cc.count - j0);
+    const int lane = threadIdx.x, l0 = (it[0] & 3) * 64;
+    const IfacePlan F = tab<IfacePlan>(P.g, P.L.iface)[rt.iface];
+    const int d = P.side ? F.dr : F.dl;
+    const int sg = tab<int>(P.g, P.L.sigma)[d * P.n_if + cc.iface];
+    const int jside = tab<IfacePlan>(P.g, P.L.iface)[cc.iface].dr == d ? 1 : 0;
+    const WaveConst W = scalar_copy(tab<WaveConst>(P.g, P.L.wave) + d);
+    const BlockConst B = block_const<BM>(tab<DomConst>(P.g, P.L.dom)[d], sg);
+    const ElemRec* el = tab<ElemRec>(P.g, P.L.elem);
+    const int row0 = (P.side ? F.row_r : F.row_l) - F.off;
+    const bool valid = l0 + lane < rt.count;
+    const int i = rt.start + (valid ? l0 + lane : 0);
+    int ntodo = 0;  // uniform
+    {
+        const double xi = el[i].cx, yi = el[i].cy, tix = el[i].tx, tiy = el[i].ty;
+        const cd tk = {W.tkr, W.tki};
+        const int cw = P.L.exp_cplx ? 2 : 1;
+        for (int jj = 0; jj < cnt; ++jj) {
+            const int j = cc.start + j0 + jj;
+            ScalarPtr Ej = (ScalarPtr)(el + j);
+            ScalarPtr rec = (ScalarPtr)(tab<double>(P.g, P.L.expn) + ((size_t)jside * P.N + j) * P.L.exp_stride);
+            const double cx = Ej[E_CX], cy = Ej[E_CY], tx = Ej[E_TX], ty = Ej[E_TY];
+            const double rx = xi - cx, ry = yi - cy;
+            const double r2 = pair_r2(rx, ry);
+            if (__builtin_amdgcn_ballot_w64(valid && r2 < rec[LOW ? EXP_H_NEAR32 : EXP_H_NEAR64]) == 0) continue;
+            const bool close = valid && r2 < rec[EXP_H_CLOSE];
+            const bool rest = valid && !close;
+            if (__builtin_amdgcn_ballot_w64(rest) != 0) {
+                auto closer = [&](double lim2) { return __builtin_amdgcn_ballot_w64(rest && r2 < lim2) != 0; };
+                const int Lo = !closer(rec[EXP_H_LIM]) ? 8 : !closer(rec[EXP_H_LIM + 1]) ? 10 : !closer(rec[EXP_H_LIM + 2]) ? 12
+                               : !closer(rec[EXP_H_LIM + 3]) ? 16 : 20;
+                if (rest) {
+                    double r, rinv;
+                    sqrt_rsqrt(r2, r, rinv);
+                    const double rlo = sqrt_error(rx, ry, diff_error(xi, cx, rx), diff_error(yi, cy, ry), r, rinv);
+                    cd h0, h1;
+                    hankel01<CPLX, true>(W, r, r2, rinv, rsqrt_nr(r), h0, h1, rlo);
+                    const double c1 = fma(rx, tx, ry * ty) * rinv, s1 = fma(ry, tx, -rx * ty) * rinv;
+                    const PairSums sums = expand<CPLX, BM, 8>(rec + EXP_HEAD, cw, Lo, h0, h1, c1, s1,
+                                                              {tk.re * rinv, CPLX ? tk.im * rinv : 0.0});
+                    cd au, aw;
+                    combine<BM>(B, sums, fma(tix, tx, tiy * ty), fma(tiy, tx, -tix * ty), au, aw);
+                    store_entry(P.A, P.lda, P.A32, (size_t)(row0 + i), j, P.N, au, aw);
+                }
+            }
+            const unsigned long long m = __builtin_amdgcn_ballot_w64(close);
+            if (close) todo[ntodo + __popcll(m & ((1ull << lane) - 1ull))] = (unsigned char)(lane * NEAR_PART + jj);
+            ntodo += __popcll(m);
         }
     }
     __syncthreads();
-    if (!act || li >= rt.count) return;
-    const WaveConst& W = tab<WaveConst>(g, L.wave)[d];
-    const DomConst Dm = tab<DomConst>(g, L.dom)[d];
-    const ElemRec Ei = tab<ElemRec>(g, L.elem)[i];
-    const BlockConst B = block_const<BM>(Dm, sg);
-    cd selfS = {0.0, 0.0};
-    if (i >= cc.start && i < cc.start + cnt) {
-        const double2 sv = tab<double2>(g, L.self)[(size_t)d * N + i];
-        selfS = {sv.x, sv.y};
+    // close pairs: np points each (the Gauss points, then the two end points)
+    const double* gl = tab<double>(P.g, P.L.gl);
+    const int q = P.q, np = q + (BM ? 2 : 0), nb = 64 / np;
+    const int my = lane / np, pt = lane - my * np;  // this lane's pair of the batch and point of it
+    for (int t0 = 0; t0 < ntodo; t0 += nb) {
+        const int nt = min(nb, ntodo - t0);
+        if (my < nt) {
+            const int pr = todo[t0 + my];
+            const ElemRec& Ei = el[rt.start + l0 + pr / NEAR_PART];
+            const ElemRec& Ej = el[cc.start + j0 + pr % NEAR_PART];
+            const bool end = BM && pt >= q;
+            double px, py, w = 0.0;
+            if (end) {
+                px = pt == q ? Ej.ax : Ej.bx;
+                py = pt == q ? Ej.ay : Ej.by;
+            } else {
+                const double s = 0.5 * Ej.h * gl[pt];
+                w = 0.5 * Ej.h * gl[QMAX + pt];
+                px = Ej.cx + s * Ej.tx;
+                py = Ej.cy + s * Ej.ty;
+            }
+            const double rx = Ei.cx - px, ry = Ei.cy - py;
+            // a lane on the diagonal may sit on its own point: any distance
+            // will do there, its sums are not used
+            const double r2 = fmax(fma(rx, rx, ry * ry), 1e-300);
+            double r, rinv;
+            sqrt_rsqrt(r2, r, rinv);
+            cd h0, h1;
+            hankel01<CPLX, true>(W, r, r2, rinv, rsqrt_nr(r), h0, h1);
+            const double wr = w * rinv;
+            const double wd = wr * fma(rx, Ej.nx, ry * Ej.ny);
+            part[0][lane] = w * h0.re;
+            part[1][lane] = w * h0.im;
+            part[2][lane] = wd * h1.re;
+            part[3][lane] = wd * h1.im;
+            if constexpr (BM) {
+                const double ws = wr * fma(rx, Ei.nx, ry * Ei.ny);
+                part[4][lane] = ws * h1.re;
+                part[5][lane] = ws * h1.im;
+                const double we = end ? fma(rx, Ei.tx, ry * Ei.ty) * (pt == q ? -rinv : rinv) : 0.0;
+                part[6][lane] = we * h1.re;
+                part[7][lane] = we * h1.im;
+            }
+        }
+        __syncthreads();
+        if (lane < nt) {
+            const int pr = todo[t0 + lane];
+            const int ii = rt.start + l0 + pr / NEAR_PART, j = cc.start + j0 + pr % NEAR_PART;
+            double v[NV];
+#pragma unroll
+            for (int k = 0; k < NV; ++k) v[k] = 0.0;
+            for (int g = 0; g < np; ++g)
+#pragma unroll
+                for (int k = 0; k < NV; ++k) v[k] += part[k][lane * np + g];
+            cd sS = {v[0], v[1]}, au, aw;
+            if (ii != j) {
+                au = cmul(B.cD, {v[2], v[3]});
+                aw = cmul(B.cS, sS);
+            } else {
+                // self term: D = D* = 0 on a flat element, S analytic; sS carries S / (i/4)
+                const double2 sv = tab<double2>(P.g, P.L.self)[(size_t)d * P.N + ii];
+                sS = cdiv({sv.x, sv.y}, B.iq);
+                au = B.du;
+                aw = cmul(B.cS, sS);
+                if (BM) aw = cadd(aw, B.dw);
+            }
+            if constexpr (BM) {
+                const double ninj = el[ii].nx * el[j].nx + el[ii].ny * el[j].ny;
+                au = cadd(au, cadd(cscale(cmul(B.cNS, sS), ninj), cmul(B.cNE, {v[6], v[7]})));
+                if (ii != j) aw = cadd(aw, cmul(B.cDs, {v[4], v[5]}));
+            }
+            store_entry(P.A, P.lda, P.A32, (size_t)(row0 + ii), j, P.N, au, aw);
+        }
+        __syncthreads();
     }
-    // near mask: bit jj when some collocation point of this wave lies within
-    // the series radius of a point of element jj (the element's points lie
-    // within h/2 of its midpoint).  The near launch widens the radius by a
-    // relative 1e-9, so that no element escapes both launches through a
-    // rounding difference; an element both take is written by the near
-    // launch, which runs second.
-    const double rs = (F32 ? W.rs32 : W.rs) * (NEAR ? 1.0 + 1e-9 : 1.0);
-    unsigned nearm = 0;
-    for (int jj = 0; jj < cnt; ++jj) {
-        const double dx = Ei.cx - ell[jj].cx, dy = Ei.cy - ell[jj].cy;
-        const double lim = rs + ell[jj].hh;
-        if (__builtin_amdgcn_ballot_w64(fma(dx, dx, dy * dy) < lim * lim) != 0) nearm |= 1u << jj;
-    }
-    const unsigned all = cnt >= 32 ? 0xffffffffu : (1u << cnt) - 1u;
-    if (F32) {
-        const WaveConst32& W32 = tab<WaveConst32>(g, L.wave32)[d];
-        cf Ea = {0.0f, 0.0f};
-        int prev = -2;
-        for (unsigned m = NEAR ? 0u : all & ~nearm; m != 0; m &= m - 1) {
-            const int jj = __builtin_ctz(m);
-            cd au, aw;
-            element_entries_f32<Q, CPLX, BM, true>(W, W32, B, Ei, ell[jj], gp + jj * QS, q_rt, false, selfS, Ea,
-                                                   jj == prev + 1, au, aw);
-            prev = jj;
-            store(cc.start + jj, au, aw);
-        }
-        prev = -2;
-        for (unsigned m = NEAR ? nearm : 0u; m != 0; m &= m - 1) {
-            const int jj = __builtin_ctz(m);
-            const int j = cc.start + jj;
-            cd au, aw;
-            element_entries_f32<Q, CPLX, BM, false>(W, W32, B, Ei, ell[jj], gp + jj * QS, q_rt, j == i, selfS, Ea,
-                                                    jj == prev + 1, au, aw);
-            prev = jj;
-            store(j, au, aw);
-        }
-    } else {
-        cd Ea = {0.0, 0.0};
-        int prev = -2;
-        for (unsigned m = NEAR ? 0u : all & ~nearm; m != 0; m &= m - 1) {
-            const int jj = __builtin_ctz(m);
-            cd au, aw;
-            element_entries<Q, CPLX, BM, true>(W, B, Ei, ell[jj], gp + jj * QS, q_rt, false, selfS, Ea,
-                                               jj == prev + 1, au, aw);
-            prev = jj;
-            store(cc.start + jj, au, aw);
-        }
-        prev = -2;
-        for (unsigned m = NEAR ? nearm : 0u; m != 0; m &= m - 1) {
-            const int jj = __builtin_ctz(m);
-            const int j = cc.start + jj;
-            cd au, aw;
-            element_entries<Q, CPLX, BM, false>(W, B, Ei, ell[jj], gp + jj * QS, q_rt, j == i, selfS, Ea,
-                                                jj == prev + 1, au, aw);
-            prev = jj;
-            store(j, au, aw);
-        }
-    }
-}
-
-// Far elements (the bulk; no series code, so two waves fit per SIMD) over the
-// grid (row tiles of the variant) x (column chunks), and near elements (the
-// general per-lane evaluation) over the variant's list of (row tile and its
-// 64-row wave, column chunk, part of NEAR_PART elements) items whose bounding
-// boxes come within the series radius, one item per wave.
-template <int Q, bool CPLX, bool BM>
-__global__ __launch_bounds__(ROW_TILE, ASM_FAR_WAVES) void k_assemble_f64(const char* __restrict__ g, GeomLayout L,
-                                                                           int N, int n_if, int q_rt,
-                                                                           const int* __restrict__ tiles, int side,
-                                                                           double2* __restrict__ A, size_t lda,
-                                                                           float2* __restrict__ A32, size_t lda32)
-{
-    __shared__ GaussL gp[COL_CHUNK * (Q > 0 ? Q : QMAX)];
-    __shared__ ElemL ell[COL_CHUNK];
-    assemble_chunk<Q, CPLX, BM, false, false>(g, L, N, n_if, q_rt, tiles[blockIdx.x], -1, blockIdx.y, -1, side, A, lda,
-                                              A32, lda32, gp, ell, true);
-}
-
-constexpr int NEAR_WAVES = ROW_TILE / 64;  // list items per near-element workgroup
-static_assert(NEAR_WAVES == 4, "a near item packs the wave of its row tile in two bits");
-
-// The list item of this wave: (row tile * 4 + wave of the tile, chunk, part).
-__device__ __forceinline__ bool near_item(const int* __restrict__ items, int count, int& tile, int& sub, int& chunk,
-                                          int& part)
-{
-    const int k = blockIdx.x * NEAR_WAVES + (int)(threadIdx.x >> 6);
-    if (k >= count) return false;
-    const int tw = items[3 * k];
-    tile = tw >> 2;
-    sub = tw & 3;
-    chunk = items[3 * k + 1];
-    part = items[3 * k + 2];
-    return true;
-}
-
-template <int Q, bool CPLX, bool BM>
-__global__ __launch_bounds__(ROW_TILE, ASM_NEAR_WAVES) void k_assemble_near_f64(const char* __restrict__ g, GeomLayout L, int N,
-                                                                   int n_if, int q_rt, const int* __restrict__ items,
-                                                                   int count, int side, double2* __restrict__ A,
-                                                                   size_t lda, float2* __restrict__ A32, size_t lda32)
-{
-    __shared__ GaussL gp[NEAR_WAVES][NEAR_PART * (Q > 0 ? Q : QMAX)];
-    __shared__ ElemL ell[NEAR_WAVES][NEAR_PART];
-    int tile = 0, sub = 0, chunk = 0, part = 0;
-    const bool act = near_item(items, count, tile, sub, chunk, part);
-    const int w = threadIdx.x >> 6;
-    assemble_chunk<Q, CPLX, BM, false, true>(g, L, N, n_if, q_rt, tile, sub, chunk, part, side, A, lda, A32, lda32,
-                                             gp[w], ell[w], act);
-}
-
-template <int Q, bool CPLX, bool BM>
-__global__ __launch_bounds__(ROW_TILE, ASM_FAR_WAVES) void k_assemble_f32(const char* __restrict__ g, GeomLayout L,
-                                                                           int N, int n_if, int q_rt,
-                                                                           const int* __restrict__ tiles, int side,
-                                                                           float2* __restrict__ A, size_t lda)
-{
-    __shared__ GaussL gp[COL_CHUNK * (Q > 0 ? Q : QMAX)];
-    __shared__ ElemL ell[COL_CHUNK];
-    assemble_chunk<Q, CPLX, BM, true, false>(g, L, N, n_if, q_rt, tiles[blockIdx.x], -1, blockIdx.y, -1, side, A, lda,
-                                             nullptr, 0, gp, ell, true);
-}
-
-template <int Q, bool CPLX, bool BM>
-__global__ __launch_bounds__(ROW_TILE, ASM_NEAR_WAVES) void k_assemble_near_f32(const char* __restrict__ g, GeomLayout L, int N,
-                                                                   int n_if, int q_rt, const int* __restrict__ items,
-                                                                   int count, int side, float2* __restrict__ A,
-                                                                   size_t lda)
-{
-    __shared__ GaussL gp[NEAR_WAVES][NEAR_PART * (Q > 0 ? Q : QMAX)];
-    __shared__ ElemL ell[NEAR_WAVES][NEAR_PART];
-    int tile = 0, sub = 0, chunk = 0, part = 0;
-    const bool act = near_item(items, count, tile, sub, chunk, part);
-    const int w = threadIdx.x >> 6;
-    assemble_chunk<Q, CPLX, BM, true, true>(g, L, N, n_if, q_rt, tile, sub, chunk, part, side, A, lda, nullptr, 0,
-                                            gp[w], ell[w], act);
 }
 }  // namespace
 
@@ -874,38 +764,43 @@ __global__ __launch_bounds__(ROW_TILE, ASM_NEAR_WAVES) void k_assemble_near_f32(
 hipError_t launch_setup(char* g, const GeomLayout& L, int N, int n_dom, int q, hipStream_t s)
 {
     const int eblocks = (N + SETUP_BS - 1) / SETUP_BS;
-    hipLaunchKernelGGL(k_setup, dim3(1 + 3 * eblocks), dim3(SETUP_BS), 0, s, g, L, N, n_dom, q, eblocks);
+    hipLaunchKernelGGL(k_setup, dim3(1 + (3 + 2 * (EXP_LMAX + 1)) * eblocks), dim3(SETUP_BS), 0, s, g, L, N, n_dom, q, eblocks);
     return hipGetLastError();
+}
+
+namespace {
+
+// Elements per wave: a whole chunk (far) or part (near) unless that leaves the
+// chip's 1024 SIMDs short of waves; a wave's set-up costs about one element.
+int elements_per_wave(int most, int least, long long waves, long long wanted)
+{
+    int per = most;
+    while (per > least && waves * (most / per) < wanted) per /= 2;
+    return per;
 }
 
 // One launch per variant (side of the interface, row type, complex wavenumber)
 // over the row tiles of that variant; lists[v] / counts[v] are device / host.
-template <class T2, bool F64, int Q>
-void launch_variants(const char* g, const GeomLayout& L, int N, int n_if, int n_cchunks, int q,
-                     const int* const* lists, const int* counts, const int* const* pairs, const int* pair_counts,
-                     T2* A, size_t lda, float2* A32, size_t lda32, hipStream_t s0, hipStream_t s1)
+// Variants write disjoint rows: they alternate over the two streams.
+template <class T2>
+hipError_t launch_variants(AsmArgs<T2> P, int n_cchunks, const int* const* lists, const int* counts,
+                           const int* const* pairs, const int* pair_counts, hipStream_t s0, hipStream_t s1)
 {
-    int k = 0;  // variants write disjoint rows: alternate them over the two streams
+    const int per = elements_per_wave(COL_CHUNK, 2, (long long)((P.N + 63) / 64) * n_cchunks, 4096);
+    int k = 0;
     for (int v = 0; v < ASM_VARIANTS; ++v) {
         if (counts[v] == 0) continue;
         const hipStream_t s = (k++ & 1) ? s1 : s0;
-        const int side = v >> 2 & 1, bm = v >> 1 & 1, cplx = v & 1;
-        const dim3 grid(counts[v], n_cchunks, 1), ngrid((pair_counts[v] + NEAR_WAVES - 1) / NEAR_WAVES, 1, 1);
-#define BEM_ASM_LAUNCH(C_, B_)                                                                                    \
-    if (cplx == C_ && bm == B_) {                                                                                 \
-        if constexpr (F64) {                                                                                      \
-            hipLaunchKernelGGL((k_assemble_f64<Q, C_, B_>), grid, dim3(ROW_TILE), 0, s, g, L, N, n_if, q, lists[v],   \
-                               side, reinterpret_cast<double2*>(A), lda, A32, lda32);                              \
-            if (pair_counts[v] > 0)                                                                               \
-                hipLaunchKernelGGL((k_assemble_near_f64<Q, C_, B_>), ngrid, dim3(ROW_TILE), 0, s, g, L, N, n_if, q,   \
-                                   pairs[v], pair_counts[v], side, reinterpret_cast<double2*>(A), lda, A32, lda32);\
-        } else {                                                                                                  \
-            hipLaunchKernelGGL((k_assemble_f32<Q, C_, B_>), grid, dim3(ROW_TILE), 0, s, g, L, N, n_if, q, lists[v],   \
-                               side, reinterpret_cast<float2*>(A), lda);                                           \
-            if (pair_counts[v] > 0)                                                                               \
-                hipLaunchKernelGGL((k_assemble_near_f32<Q, C_, B_>), ngrid, dim3(ROW_TILE), 0, s, g, L, N, n_if, q,   \
-                                   pairs[v], pair_counts[v], side, reinterpret_cast<float2*>(A), lda);             \
-        }                                                                                                         \
+        const int bm = v >> 1 & 1, cplx = v & 1;
+        P.side = v >> 2 & 1;
+        const dim3 grid(counts[v], n_cchunks * (COL_CHUNK / per));
+        const int nper = elements_per_wave(NEAR_PART, 1, pair_counts[v], 4096);
+#define BEM_ASM_LAUNCH(C_, B_)                                                                             \
+    if (cplx == C_ && bm == B_) {                                                                          \
+        if (pair_counts[v] > 0)                                                                            \
+            hipLaunchKernelGGL((k_assemble_near<C_, B_, T2>), dim3(pair_counts[v] * (NEAR_PART / nper)), dim3(64), 0, \
+                               s, P, pairs[v], nper);                                                      \
+        hipLaunchKernelGGL((k_assemble_far<C_, B_, T2>), grid, dim3(ROW_TILE), 0, s, P, lists[v], per);     \
     }
         BEM_ASM_LAUNCH(false, false)
         BEM_ASM_LAUNCH(true, false)
@@ -913,39 +808,26 @@ void launch_variants(const char* g, const GeomLayout& L, int N, int n_if, int n_
         BEM_ASM_LAUNCH(true, true)
 #undef BEM_ASM_LAUNCH
     }
+    return hipGetLastError();
 }
+
+}  // namespace
 
 hipError_t launch_assemble_f64(const char* g, const GeomLayout& L, int N, int n_if, int n_cchunks, int q,
                                const int* const* lists, const int* counts, const int* const* pairs,
-                               const int* pair_counts, double2* A, size_t lda, float2* A32, size_t lda32,
-                               hipStream_t s, hipStream_t s1)
+                               const int* pair_counts, double2* A, size_t lda, float2* A32, hipStream_t s,
+                               hipStream_t s1)
 {
-    if (q == 8)
-        launch_variants<double2, true, 8>(g, L, N, n_if, n_cchunks, q, lists, counts, pairs, pair_counts, A, lda, A32,
-                                          lda32, s, s1);
-    else if (q == 10)
-        launch_variants<double2, true, 10>(g, L, N, n_if, n_cchunks, q, lists, counts, pairs, pair_counts, A, lda,
-                                           A32, lda32, s, s1);
-    else
-        launch_variants<double2, true, 0>(g, L, N, n_if, n_cchunks, q, lists, counts, pairs, pair_counts, A, lda, A32,
-                                          lda32, s, s1);
-    return hipGetLastError();
+    return launch_variants(AsmArgs<double2>{g, L, N, n_if, q, 0, A, A32, lda}, n_cchunks, lists, counts, pairs,
+                           pair_counts, s, s1);
 }
 
 hipError_t launch_assemble_f32(const char* g, const GeomLayout& L, int N, int n_if, int n_cchunks, int q,
                                const int* const* lists, const int* counts, const int* const* pairs,
                                const int* pair_counts, float2* A, size_t lda, hipStream_t s, hipStream_t s1)
 {
-    if (q == 8)
-        launch_variants<float2, false, 8>(g, L, N, n_if, n_cchunks, q, lists, counts, pairs, pair_counts, A, lda,
-                                          nullptr, 0, s, s1);
-    else if (q == 10)
-        launch_variants<float2, false, 10>(g, L, N, n_if, n_cchunks, q, lists, counts, pairs, pair_counts, A, lda,
-                                           nullptr, 0, s, s1);
-    else
-        launch_variants<float2, false, 0>(g, L, N, n_if, n_cchunks, q, lists, counts, pairs, pair_counts, A, lda,
-                                          nullptr, 0, s, s1);
-    return hipGetLastError();
+    return launch_variants(AsmArgs<float2>{g, L, N, n_if, q, 0, A, nullptr, lda}, n_cchunks, lists, counts, pairs,
+                           pair_counts, s, s1);
 }
 
 }  // namespace bemk

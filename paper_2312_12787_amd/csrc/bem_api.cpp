@@ -184,12 +184,13 @@ GeomLayout make_layout(const bem_problem* p)
     size_t upload_end = off;
     (void)upload_end;
     L.elem = take((size_t)p->N * sizeof(bemk::ElemRec));
-    L.gauss = take((size_t)p->N * sizeof(bemk::GaussRec));
-    L.gauss32 = take((size_t)p->N * sizeof(bemk::GaussRec32));
+    L.exp_cplx = 0;
+    for (const auto& kd : p->k) L.exp_cplx |= kd.imag() != 0.0;
+    L.exp_stride = bemk::EXP_HEAD + (L.exp_cplx ? 2 : 1) * bemk::EXP_NCOEF;
+    L.expn = take((size_t)2 * p->N * L.exp_stride * sizeof(double));
     L.gl = take(2 * bemk::QMAX * sizeof(double));
     L.dom = take((size_t)p->n_dom * sizeof(bemk::DomConst));
     L.wave = take((size_t)p->n_dom * sizeof(bemk::WaveConst));
-    L.wave32 = take((size_t)p->n_dom * sizeof(bemk::WaveConst32));
     L.self = take((size_t)p->n_dom * p->N * sizeof(double2));
     L.total = off;
     return L;
@@ -423,17 +424,18 @@ bem_status bem_create(const bem_desc* desc, bem_problem** out)
         }
         // Near list of each variant: (row tile * 4 + 64-row wave of the tile,
         // column chunk, part) triples -- a part being NEAR_PART consecutive
-        // elements of the chunk -- whose bounding boxes (collocation points;
-        // element midpoints widened by the largest half length) come within
-        // the series radius XS/|k_d| of the rows' domain (the larger FP64
-        // radius; relative margin 1e-6).  Only these can hold an element the
-        // assembly's per-wave test calls near, so the near-element launch runs
-        // over them alone, one wave per item.
+        // elements of the chunk -- whose bounding boxes (collocation points,
+        // element midpoints) come within the near radius of the part in the
+        // rows' domain (relative margin 1e-6): the series radius XS/|k_d| or
+        // the expansion's reach of the part's longest element, or any distance
+        // where an element is too long or too short for the expansion.  Only
+        // these can hold an element that the far launch leaves, so the near
+        // launch runs over them alone, one wave per item.
         struct Box {
-            double x0, x1, y0, y1, hh;
+            double x0, x1, y0, y1, hh, hmin;  // midpoints, largest and smallest half length
         };
         auto box = [&](int e0, int cnt) {
-            Box b{1e300, -1e300, 1e300, -1e300, 0.0};
+            Box b{1e300, -1e300, 1e300, -1e300, 0.0, 1e300};
             for (int e = e0; e < e0 + cnt; ++e) {
                 const int a = p->elnodes[2 * e], c = p->elnodes[2 * e + 1];
                 const double ax = p->xy[2 * a], ay = p->xy[2 * a + 1], cx = p->xy[2 * c], cy = p->xy[2 * c + 1];
@@ -442,7 +444,9 @@ bem_status bem_create(const bem_desc* desc, bem_problem** out)
                 b.x1 = std::max(b.x1, mx);
                 b.y0 = std::min(b.y0, my);
                 b.y1 = std::max(b.y1, my);
-                b.hh = std::max(b.hh, 0.5 * std::hypot(cx - ax, cy - ay));
+                const double hh = 0.5 * std::hypot(cx - ax, cy - ay);
+                b.hh = std::max(b.hh, hh);
+                b.hmin = std::min(b.hmin, hh);
             }
             return b;
         };
@@ -452,12 +456,12 @@ bem_status bem_create(const bem_desc* desc, bem_problem** out)
         for (size_t t = 0; t < p->rtiles.size(); ++t)
             for (int w = 0; w < NW; ++w) {
                 const int s0 = 64 * w, cnt = std::min(64, p->rtiles[t].count - s0);
-                rb[t * NW + w] = cnt > 0 ? box(p->rtiles[t].start + s0, cnt) : Box{1e300, 1e300, 1e300, 1e300, 0.0};
+                rb[t * NW + w] = cnt > 0 ? box(p->rtiles[t].start + s0, cnt) : Box{1e300, 1e300, 1e300, 1e300, 0.0, 1e300};
             }
         for (size_t c = 0; c < p->cchunks.size(); ++c)
             for (int q = 0; q < NP; ++q) {
                 const int s0 = q * bemk::NEAR_PART, cnt = std::min(bemk::NEAR_PART, p->cchunks[c].count - s0);
-                cb[c * NP + q] = cnt > 0 ? box(p->cchunks[c].start + s0, cnt) : Box{1e300, 1e300, 1e300, 1e300, 0.0};
+                cb[c * NP + q] = cnt > 0 ? box(p->cchunks[c].start + s0, cnt) : Box{1e300, 1e300, 1e300, 1e300, 0.0, 1e300};
             }
         for (int v = 0; v < bemk::ASM_VARIANTS; ++v) {
             p->noff[v] = (int)p->npairs.size() / 3;
@@ -465,7 +469,8 @@ bem_status bem_create(const bem_desc* desc, bem_problem** out)
             for (int t : lists[v]) {
                 const IfacePlan& P = p->iface[p->rtiles[t].iface];
                 const int d = side ? P.dr : P.dl;
-                const double rs = std::max(bemk::XS_SERIES_F64, bemk::XS_SERIES_F32) / std::abs(p->k[d]);
+                const double ak = std::abs(p->k[d]);
+                const double rs = std::max(bemk::XS_SERIES_F64, bemk::XS_SERIES_F32) / ak;
                 for (int w = 0; w < NW && 64 * w < p->rtiles[t].count; ++w)
                     for (size_t c = 0; c < p->cchunks.size(); ++c) {
                         if (p->sigma[(size_t)d * p->n_if + p->cchunks[c].iface] == 0) continue;
@@ -474,8 +479,9 @@ bem_status bem_create(const bem_desc* desc, bem_problem** out)
                             const Box &a = rb[t * NW + w], &b = cb[c * NP + q];
                             const double dx = std::max(0.0, std::max(a.x0 - b.x1, b.x0 - a.x1));
                             const double dy = std::max(0.0, std::max(a.y0 - b.y1, b.y0 - a.y1));
-                            const double lim = (rs + b.hh) * (1.0 + 1e-6) + 1e-12;
-                            if (dx * dx + dy * dy < lim * lim) {
+                            const double lim = std::max(rs, b.hh / bemk::EXP_X20) * (1.0 + 1e-6);
+                            if (dx * dx + dy * dy < lim * lim ||
+                                ak * b.hh * (1.0 + 1e-6) > bemk::EXP_KA_MAX || ak * b.hmin < bemk::EXP_KA_MIN * (1.0 + 1e-6)) {
                                 p->npairs.push_back(t * NW + w);
                                 p->npairs.push_back((int)c);
                                 p->npairs.push_back(q);
@@ -668,7 +674,7 @@ bem_status bem_assemble(bem_problem* p, int prec, void* A_dev, size_t lda, hipSt
                                          p->ncount, static_cast<float2*>(A_dev), lda, stream, side));
     else
         HIP_OK(bemk::launch_assemble_f64(p->geom, p->L, p->N, p->n_if, ncc, p->quad, lists, p->vcount, pairs,
-                                         p->ncount, static_cast<double2*>(A_dev), lda, A32, lda, stream, side));
+                                         p->ncount, static_cast<double2*>(A_dev), lda, A32, stream, side));
     if (side != stream) {
         HIP_OK(hipEventRecord(p->asm_ev[1], side));
         HIP_OK(hipStreamWaitEvent(stream, p->asm_ev[1], 0));

@@ -4,9 +4,8 @@
 // estimate and fused multiply-adds only: no IEEE special-case fix-ups, no
 // table lookups, every constant a compile-time literal.
 //
-// Domains: sqrt_rsqrt / rsqrt_nr take normal x > 0; sincos_cw takes
-// |x| < 2^30 (the reduction below is exact there; the rounding of x itself,
-// one ulp of k r, is the dominant error of any phase evaluation).
+// Domains: sqrt_rsqrt / rsqrt_nr take normal x > 0; sincos_phase takes
+// k r < 2^30 (the reduction below is exact there).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -43,44 +42,74 @@ __device__ __forceinline__ double rsqrt_nr(double x)
     return y;
 }
 
-// sin x and cos x.  Cody and Waite's additive reduction x = n pi/2 + t with
-// pi/2 split into P1 = pi/2 rounded to double and P2 = pi/2 - P1 rounded:
-// with a fused multiply-add, x - n P1 is exact (both are integer multiples of
-// 2^-52 below 2 in magnitude once |x| >= 1, and n = 0 below), and n P2 leaves
-// an error of about n 1.5e-33.  On |t| <= pi/4 (+ rounding) the Taylor series
-//   sin t = t - t^3/3! + ... - t^15/15! + t^17/17!   (truncation < 1e-19)
-//   cos t = 1 - t^2/2! + ... + t^16/16!              (truncation < 3e-18)
+// a - b = s + diff_error(a, b, s) exactly, s = a - b rounded (Knuth's two-sum).
+__device__ __forceinline__ double diff_error(double a, double b, double s)
+{
+    const double bv = a - s;
+    return (a - (s + bv)) + (bv - b);
+}
+
+// What r lacks of the distance sqrt((rx + ex)^2 + (ry + ey)^2), r being about
+// sqrt(rx^2 + ry^2) and rinv 1/r:  (rx^2 + ry^2 - r^2 + 2 rx ex + 2 ry ey) / (2r),
+// the squares of the larger component and of r subtracted first (they cancel)
+// with the larger one's rounding kept.  Leaves about a tenth of an ulp of r.
+__device__ __forceinline__ double sqrt_error(double rx, double ry, double ex, double ey, double r, double rinv)
+{
+    const double hi = fmax(fabs(rx), fabs(ry)), lo = fmin(fabs(rx), fabs(ry));
+    const double hh = hi * hi;
+    const double d = fma(lo, lo, fma(-r, r, hh)) + fma(hi, hi, -hh);
+    return rinv * fma(0.5, d, fma(rx, ex, ry * ey));
+}
+
+// sin and cos of k (r + rlo) - pi/4, 0 < k r < 2^30 (LOW: to about 1e-10
+// instead of an ulp).  The product k r is kept to twice the precision, so the
+// phase is as good as r + rlo.  Cody and Waite's additive reduction x = k r =
+// (n + 1/2) pi/2 + t, the -pi/4 of the Hankel functions being the 1/2, with
+// pi/2 split into P1 = pi/2 rounded to double and P2 = pi/2 - P1 rounded: with
+// a fused multiply-add, x - (n + 1/2) P1 is exact, and (n + 1/2) P2 leaves an
+// error of about n 1.5e-33.  On |t| <= pi/4 (+ rounding) the Taylor series
+//   sin t = t - t^3/3! + ... - t^15/15! + t^17/17!   (truncation < 1e-19; LOW: t^11, 7e-12)
+//   cos t = 1 - t^2/2! + ... + t^16/16!              (truncation < 3e-18; LOW: t^12, 4e-13)
 // in u = t^2, then the quadrant n mod 4 swaps and negates.
-__device__ __forceinline__ void sincos_cw(double x, double& s, double& c)
+template <bool LOW>
+__device__ __forceinline__ void sincos_phase(double k, double r, double rlo, double& s, double& c)
 {
     constexpr double TWO_OVER_PI = 0x1.45f306dc9c883p-1;  // 2/pi
     constexpr double P1 = 0x1.921fb54442d18p+0;           // pi/2 rounded to double
     constexpr double P2 = 0x1.1a62633145c07p-54;          // pi/2 - P1 rounded to double
-    const double n = rint(x * TWO_OVER_PI);
-    double t = fma(-n, P1, x);
-    t = fma(-n, P2, t);
+    const double x = k * r;
+    const double n = rint(fma(x, TWO_OVER_PI, -0.5));
+    const double nh = n + 0.5;
+    const double e = fma(k, rlo, fma(k, r, -x));
+    const double t = fma(-nh, P1, x) + fma(-nh, P2, e);
     const double u = t * t;
-    // (-1)^m / (2m+1)!, m = 1..8, and (-1)^m / (2m)!, m = 1..8 (factorials exact in double)
-    double ps = 1.0 / 355687428096000.0;   // 1/17!
-    ps = fma(ps, u, -1.0 / 1307674368000.0);  // 1/15!
-    ps = fma(ps, u, 1.0 / 6227020800.0);      // 1/13!
-    ps = fma(ps, u, -1.0 / 39916800.0);       // 1/11!
-    ps = fma(ps, u, 1.0 / 362880.0);          // 1/9!
-    ps = fma(ps, u, -1.0 / 5040.0);           // 1/7!
-    ps = fma(ps, u, 1.0 / 120.0);             // 1/5!
-    ps = fma(ps, u, -1.0 / 6.0);              // 1/3!
-    double pc = 1.0 / 20922789888000.0;    // 1/16!
-    pc = fma(pc, u, -1.0 / 87178291200.0);    // 1/14!
-    pc = fma(pc, u, 1.0 / 479001600.0);       // 1/12!
-    pc = fma(pc, u, -1.0 / 3628800.0);        // 1/10!
-    pc = fma(pc, u, 1.0 / 40320.0);           // 1/8!
-    pc = fma(pc, u, -1.0 / 720.0);            // 1/6!
-    pc = fma(pc, u, 1.0 / 24.0);              // 1/4!
-    pc = fma(pc, u, -0.5);                    // 1/2!
+    // (-1)^m / (2m+1)! and (-1)^m / (2m)! (factorials exact in double)
+    double ps, pc;
+    if (LOW) {
+        ps = -1.0 / 39916800.0;
+        pc = 1.0 / 479001600.0;
+    } else {
+        ps = 1.0 / 355687428096000.0;             // 1/17!
+        ps = fma(ps, u, -1.0 / 1307674368000.0);  // 1/15!
+        ps = fma(ps, u, 1.0 / 6227020800.0);      // 1/13!
+        ps = fma(ps, u, -1.0 / 39916800.0);       // 1/11!
+        pc = 1.0 / 20922789888000.0;              // 1/16!
+        pc = fma(pc, u, -1.0 / 87178291200.0);    // 1/14!
+        pc = fma(pc, u, 1.0 / 479001600.0);       // 1/12!
+    }
+    ps = fma(ps, u, 1.0 / 362880.0);  // 1/9!
+    ps = fma(ps, u, -1.0 / 5040.0);   // 1/7!
+    ps = fma(ps, u, 1.0 / 120.0);     // 1/5!
+    ps = fma(ps, u, -1.0 / 6.0);      // 1/3!
+    pc = fma(pc, u, -1.0 / 3628800.0);  // 1/10!
+    pc = fma(pc, u, 1.0 / 40320.0);     // 1/8!
+    pc = fma(pc, u, -1.0 / 720.0);      // 1/6!
+    pc = fma(pc, u, 1.0 / 24.0);        // 1/4!
+    pc = fma(pc, u, -0.5);              // 1/2!
     const double st = fma(t * u, ps, t);
     const double ct = fma(u, pc, 1.0);
-    // x = n pi/2 + t:  q = n mod 4;  sin x = (q odd ? cos t : sin t) (-1)^[q in {2,3}],
-    //                                cos x = (q odd ? sin t : cos t) (-1)^[q in {1,2}]
+    // x - pi/4 = n pi/2 + t:  q = n mod 4;  sin = (q odd ? cos t : sin t) (-1)^[q in {2,3}],
+    //                                       cos = (q odd ? sin t : cos t) (-1)^[q in {1,2}]
     // (two's complement: the low bits of a negative n are n mod 4 as well)
     const unsigned q = (unsigned)(int)n;
     const double a = (q & 1u) ? ct : st;

@@ -101,82 +101,100 @@ __device__ __forceinline__ HankelTabsPtr hankel_tabs_fresh()
 // first.  The accumulator is the only register each step overwrites (Horner's
 // rule overwrites a copy of the constant instead).  Used where 0 < w <= 1 and
 // the |c[m]| of m >= 1 are small, so the order costs no accuracy.
-template <int N, class T>
-__device__ __forceinline__ T poly_pow(const T (&c)[N], const T (&p)[N])
+template <int N, class C>
+__device__ __forceinline__ double poly_pow(const C& c, const double* p)
 {
-    T acc = c[N - 1] * p[N - 1];
+    double acc = (double)c[N - 1] * p[N - 1];
 #pragma unroll
-    for (int m = N - 2; m >= 1; --m) acc = fma(c[m], p[m], acc);
-    return acc + c[0];
+    for (int m = N - 2; m >= 1; --m) acc = fma((double)c[m], p[m], acc);
+    return acc + (double)c[0];
 }
 
-// Large-argument form for |k r| >= XS, from r, 1/r and r^{-1/2}.  The phase
-// phi = Re(k) r - pi/4 is reduced once for both orders:
+// The amplitude polynomials: LOW = false the FP64 fits (|k r| >= 6, 2e-16),
+// LOW = true the short ones (|k r| >= 4, 7e-10) of the FP32 assembly; both
+// evaluated in FP64.
+template <bool LOW>
+struct Amp;
+template <>
+struct Amp<false> {
+    static constexpr int N = HANKEL_NC_F64;
+    static constexpr double SCALE = 1.0;
+    static constexpr const double (&m0)[N] = HANKEL_M0_F64, (&n0)[N] = HANKEL_N0_F64, (&m1)[N] = HANKEL_M1_F64,
+                                  (&n1)[N] = HANKEL_N1_F64;
+};
+template <>
+struct Amp<true> {
+    static constexpr int N = HANKEL_NC_F32;
+    static constexpr double SCALE = HANKEL_XS_F32 / HANKEL_XS_F64;
+    static constexpr const float (&m0)[N] = HANKEL_M0_F32, (&n0)[N] = HANKEL_N0_F32, (&m1)[N] = HANKEL_M1_F32,
+                                 (&n1)[N] = HANKEL_N1_F32;
+};
+
+// Large-argument form for |k r| >= XS, from r (+ rlo, the part of the distance
+// that r lacks), 1/r and r^{-1/2}.  The phase phi = Re(k) r - pi/4 is reduced
+// once for both orders:
 //   H0 = A r^{-1/2} e^{i phi} (m0 + i u n0),
 //   H1 = A r^{-1/2} e^{i phi} (-i) (m1 + i u n1),   u = XS/(k r),
-// A = sqrt(2/(pi k)), times e^{-Im(k) r} for complex k.  H0 is skipped when
-// only H1 is wanted.
-template <bool CPLX, bool WANT_H0>
-__device__ __forceinline__ void hankel_asym(const WaveConst& W, double r, double rinv, double sr, cd& h0, cd& h1)
+// A = sqrt(2/(pi k)), times e^{-Im(k) r} for complex k.
+template <bool CPLX, bool LOW>
+__device__ __forceinline__ void hankel_asym(const WaveConst& W, double r, double rlo, double rinv, double sr, cd& h0,
+                                            cd& h1)
 {
-    constexpr double PI_4 = 0x1.921fb54442d18p-1;
+    using A = Amp<LOW>;
     double sn, cs;
-    sincos_cw(fma(W.kr, r, -PI_4), sn, cs);
-    const double rho = rinv * rinv;
+    sincos_phase<LOW>(W.kr, r, rlo, sn, cs);
+    const double ri = rinv * A::SCALE;
+    const double rho = ri * ri;
     if (!CPLX) {
         // w = (XS/(k r))^2 <= 1; its powers are shared by the four amplitude polynomials
-        double p[HANKEL_NC_F64];
+        double p[A::N];
         p[1] = W.wr * rho;
 #pragma unroll
-        for (int m = 2; m < HANKEL_NC_F64; ++m) p[m] = p[m / 2] * p[m - m / 2];
-        const double u = W.ur * rinv;
+        for (int m = 2; m < A::N; ++m) p[m] = p[m / 2] * p[m - m / 2];
+        const double u = W.ur * ri;
         const double a = W.ampr * sr;
         const double er = cs * a, ei = sn * a;
-        const double m1 = poly_pow(HANKEL_M1_F64, p), un1 = u * poly_pow(HANKEL_N1_F64, p);
+        const double m1 = poly_pow<A::N>(A::m1, p), un1 = u * poly_pow<A::N>(A::n1, p);
         h1 = {fma(er, un1, ei * m1), fma(ei, un1, -er * m1)};
-        if (WANT_H0) {
-            const double m0 = poly_pow(HANKEL_M0_F64, p), un0 = u * poly_pow(HANKEL_N0_F64, p);
-            h0 = {fma(er, m0, -ei * un0), fma(er, un0, ei * m0)};
-        }
+        const double m0 = poly_pow<A::N>(A::m0, p), un0 = u * poly_pow<A::N>(A::n0, p);
+        h0 = {fma(er, m0, -ei * un0), fma(er, un0, ei * m0)};
     } else {
         const double x = W.wr * rho, y = W.wi * rho;
         const double R = 2.0 * x, S = fma(x, x, y * y);
-        const cd u = {W.ur * rinv, W.ui * rinv};
+        const cd u = {W.ur * ri, W.ui * ri};
         const double damp = exp(-W.ki * r) * sr;
         const cd e = cmul({cs * damp, sn * damp}, {W.ampr, W.ampi});
-        cd m1, n1;
-        poly_cplx(HANKEL_M1_F64, x, y, R, S, m1.re, m1.im);
-        poly_cplx(HANKEL_N1_F64, x, y, R, S, n1.re, n1.im);
-        const cd un1 = cmul(u, n1);
-        h1 = cmul(e, {m1.im + un1.re, un1.im - m1.re});
-        if (WANT_H0) {
-            cd m0, n0;
-            poly_cplx(HANKEL_M0_F64, x, y, R, S, m0.re, m0.im);
-            poly_cplx(HANKEL_N0_F64, x, y, R, S, n0.re, n0.im);
-            const cd un0 = cmul(u, n0);
-            h0 = cmul(e, {m0.re - un0.im, m0.im + un0.re});
-        }
+        cd m, n;
+        poly_cplx_n<A::N>(A::m1, x, y, R, S, m.re, m.im);
+        poly_cplx_n<A::N>(A::n1, x, y, R, S, n.re, n.im);
+        const cd un1 = cmul(u, n);
+        h1 = cmul(e, {m.im + un1.re, un1.im - m.re});
+        poly_cplx_n<A::N>(A::m0, x, y, R, S, m.re, m.im);
+        poly_cplx_n<A::N>(A::n0, x, y, R, S, n.re, n.im);
+        const cd un0 = cmul(u, n);
+        h0 = cmul(e, {m.re - un0.im, m.im + un0.re});
     }
 }
 
 // H0(k r) and H1(k r) when |k r| >= XS is known for the pair (no per-lane
-// branch, no series), from the offset (rx, ry) = x - y; returns 1/r.
-template <bool CPLX, bool WANT_H0>
-__device__ __forceinline__ double hankel01_far(const WaveConst& W, double rx, double ry, cd& h0, cd& h1)
+// branch, no series), from the offset x - y = (rx + ex, ry + ey) and r2 = rx^2
+// + ry^2; returns 1/r.
+template <bool CPLX, bool LOW>
+__device__ __forceinline__ double hankel01_far(const WaveConst& W, double rx, double ry, double ex, double ey,
+                                               double r2, cd& h0, cd& h1)
 {
-    const double r2 = fma(rx, rx, ry * ry);
     double r, rinv;
     sqrt_rsqrt(r2, r, rinv);
-    hankel_asym<CPLX, WANT_H0>(W, r, rinv, rsqrt_nr(r), h0, h1);
+    hankel_asym<CPLX, LOW>(W, r, sqrt_error(rx, ry, ex, ey, r, rinv), rinv, rsqrt_nr(r), h0, h1);
     return rinv;
 }
 
-// H0(k r), H1(k r).  r2 = r^2, rinv = 1/r, srinv = r^{-1/2}.  Below XS the
+// H0(k r), H1(k r).  r2 = r^2, rinv = 1/r, srinv = r^{-1/2}, rlo as above.  Below XS the
 // ascending series (MEM: its coefficients from g_hankel_tabs by scalar loads
 // instead of immediates), above it hankel_asym.
 template <bool CPLX, bool MEM = false>
 __device__ __forceinline__ void hankel01(const WaveConst& W, double r, double r2, double rinv, double srinv, cd& h0,
-                                         cd& h1)
+                                         cd& h1, double rlo = 0.0)
 {
     HankelTabsPtr T = nullptr;
     if (MEM) T = hankel_tabs_fresh();
@@ -235,7 +253,7 @@ __device__ __forceinline__ void hankel01(const WaveConst& W, double r, double r2
         }
     } else {
         cd a0, a1;
-        hankel_asym<CPLX, true>(W, r, rinv, srinv, a0, a1);
+        hankel_asym<CPLX, false>(W, r, rlo, rinv, srinv, a0, a1);
         h0r = a0.re;
         h0i = a0.im;
         h1r = a1.re;

@@ -14,10 +14,7 @@ namespace bemk {
 constexpr int QMAX = 16;      // largest Gauss rule
 constexpr int ROW_TILE = 256; // collocation rows per assembly workgroup
 constexpr int COL_CHUNK = 32; // source elements per assembly workgroup
-#ifndef ASM_NEAR_PART
-#define ASM_NEAR_PART 4  // 2.24 ms against 2.36 ms at 8 and 2.51 ms at 16 (FP64 kite of 4096 elements)
-#endif
-constexpr int NEAR_PART = ASM_NEAR_PART;  // source elements per workgroup of the near-element launch
+constexpr int NEAR_PART = 4;  // source elements per workgroup of the near-element launch
 // |k r| below which the device Hankel evaluator uses the ascending series
 // (FP64 and FP32 amplitude paths; the same values as in hankel_tables.h)
 constexpr double XS_SERIES_F64 = 6.0, XS_SERIES_F32 = 4.0;
@@ -37,14 +34,38 @@ struct ElemRec {
     double pad[5];
 };
 
-// Gauss points of one element and their weights (h/2) w_g.
-struct GaussRec {
-    double x[QMAX], y[QMAX], w[QMAX];
+// Expansion record of one element in the domain on one side of it (the sums of
+// its Gauss rule from one Hankel evaluation at its midpoint, assemble.hip):
+// EXP_HEAD doubles of squared distance limits (infinite where the element is
+// too long against the wavelength), then the coefficients by order: order 0
+// has (S, Tt), an odd order (Gt, Gn), an even one (S, Tt, Tn).
+constexpr int EXP_HEAD = 12, EXP_LMAX = 20, EXP_NCOEF = 52, EXP_NTERMS = 14;
+__host__ __device__ constexpr int exp_pos(int m)
+{
+    return m == 0 ? 0 : (m & 1) ? 2 + 5 * (m / 2) : 4 + 5 * (m / 2 - 1);
+}
+static_assert(exp_pos(EXP_LMAX) + 3 == EXP_NCOEF, "coefficients of the orders 0 .. EXP_LMAX");
+struct ExpHead {
+    double close2;                     // below it: no expansion (order 20 leaves more than 4e-17)
+    double near64;                     // below it: near launch of the FP64 assembly (close2, series radius)
+    double lim8, lim10, lim12, lim16;  // beyond it: order 8, 10, 12, 16 suffices
+    double near32;                     // the same for the FP32 assembly (remainder 1e-9)
+    double lim32_4, lim32_6, lim32_8;
+    double pad[2];
 };
-
-struct GaussRec32 {
-    float x[QMAX], y[QMAX], w[QMAX];
-};
+constexpr int EXP_H_CLOSE = 0, EXP_H_NEAR64 = 1, EXP_H_LIM = 2, EXP_H_NEAR32 = 6, EXP_H_LIM32 = 7;
+static_assert(sizeof(ExpHead) == EXP_HEAD * sizeof(double), "head of an expansion record");
+// With x = (h/2)/r the remainder of order L is about x^L, and about
+// (kh/4)^L / (L+1)! where kr is large: the largest x and |k| h/2 at which the
+// remainder of every sum, relative to its leading term, stays below 4e-17
+// (FP32: 1e-9), found by evaluating the dropped terms over r, phi and k h.
+constexpr double EXP_X8 = 0.0087, EXP_X10 = 0.0223, EXP_X12 = 0.0415, EXP_X16 = 0.0855, EXP_X20 = 0.128;
+constexpr double EXP_KA8 = 0.074, EXP_KA10 = 0.228, EXP_KA12 = 0.495, EXP_KA16 = 1.36, EXP_KA_MAX = 2.55;
+constexpr double EXP32_X4 = 0.0054, EXP32_X6 = 0.0306, EXP32_X8 = 0.0725, EXP32_X16 = 0.2;
+constexpr double EXP32_KA4 = 0.026, EXP32_KA6 = 0.206, EXP32_KA8 = 0.615;
+// Shorter elements take the Gauss rule: H_m and the coefficients would leave
+// the range of a double.
+constexpr double EXP_KA_MIN = 1e-8;
 
 // Inputs of a domain as given by the caller (complex numbers as re, im).
 struct DomIn {
@@ -78,22 +99,12 @@ struct WaveConst {
     double r2_small;            // (XS / |k|)^2: below it the ascending series
     double wr, wi;              // (XS / k)^2
     double ur, ui;              // XS / k
-    double a0r, a0i, a1r, a1i;  // sqrt(2/(pi k)) e^{-i pi/4}, sqrt(2/(pi k)) e^{-3 i pi/4}
     double tr, ti;              // (k / 2)^2
     double hr, hi;              // k / 2
     double lkr, lki;            // ln(k / 2)
     double y1r, y1i;            // -2 / (pi k)
     double ampr, ampi;          // sqrt(2 / (pi k))
-    double rs;                  // XS / |k|: the ascending series below this distance
-    double rs32;                // the same for the FP32 amplitude evaluation (WaveConst32)
-};
-
-// FP32 amplitude evaluation (|k r| >= 4); the series below it runs in FP64.
-struct WaveConst32 {
-    float r2_small;
-    float wr, wi, ur, ui;
-    float a0r, a0i, a1r, a1i;
-    float ampr, ampi;  // sqrt(2 / (pi k))
+    double tkr, tki;            // 2 / k
 };
 
 // Interface plan (host-computed integer bookkeeping).
@@ -111,8 +122,9 @@ struct Tile {
 };
 
 struct GeomLayout {
-    size_t nodes, elnodes, elem, gauss, gauss32, gl, dom_in, glob_in, dom, wave, wave32, self,
+    size_t nodes, elnodes, elem, expn, gl, dom_in, glob_in, dom, wave, self,
         iface, rtiles, cchunks, sigma, elif, vtiles, npairs, total;
+    int exp_stride, exp_cplx;  // doubles per expansion record; 1 if some wavenumber is complex
 };
 
 }  // namespace bemk

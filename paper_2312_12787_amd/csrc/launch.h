@@ -38,8 +38,8 @@ constexpr int ASM_VARIANTS = 8;
 // Variants go alternately to s and s1 (they write disjoint rows; s1 may be s).
 hipError_t launch_assemble_f64(const char* g, const GeomLayout& L, int N, int n_if, int n_cchunks, int q,
                                const int* const* lists, const int* counts, const int* const* pairs,
-                               const int* pair_counts, double2* A, size_t lda, float2* A32, size_t lda32,
-                               hipStream_t s, hipStream_t s1);
+                               const int* pair_counts, double2* A, size_t lda, float2* A32, hipStream_t s,
+                               hipStream_t s1);
 hipError_t launch_assemble_f32(const char* g, const GeomLayout& L, int N, int n_if, int n_cchunks, int q,
                                const int* const* lists, const int* counts, const int* const* pairs,
                                const int* pair_counts, float2* A, size_t lda, hipStream_t s, hipStream_t s1);
