@@ -3,6 +3,7 @@
 // of the Calderon-ordered Burton-Miller system (Secs. 3-7 of arXiv 2312.12787).
 #include <hip/hip_runtime.h>
 
+#include "expansion_dev.h"
 #include "gauss_tables.h"
 #include "hankel_dev.h"
 #include "hankel_tables.h"
@@ -35,6 +36,14 @@ __device__ __forceinline__ cd csqrt_(cd z)
 }
 __device__ __forceinline__ cd clog_(cd z) { return {log(hypot(z.re, z.im)), atan2(z.im, z.re)}; }
 
+// Squared distance beyond which an expansion order with the limits x and kamax
+// serves an element of half length a at |k| = ak (internal.h); infinite if none.
+__device__ __forceinline__ double expansion_limit(double a, double ak, double x, double kamax)
+{
+    const double ka = ak * a, v = a / x;
+    return ka >= EXP_KA_MIN && ka <= kamax ? v * v : __longlong_as_double(0x7ff0000000000000ll);
+}
+
 // ---------------------------------------------------------------------------
 // Element table (Secs. 4, 7).
 // ---------------------------------------------------------------------------
@@ -56,7 +65,13 @@ __device__ __forceinline__ void setup_element(char* g, const GeomLayout& L, int 
     E.ty = dy / E.h;
     E.nx = -E.ty;
     E.ny = E.tx;
-    for (int k = 0; k < 5; ++k) E.pad[k] = 0.0;
+    for (int k = 0; k < 3; ++k) E.pad[k] = 0.0;
+    const IfacePlan P = tab<IfacePlan>(g, L.iface)[tab<int>(g, L.elif)[e]];
+    const DomIn* in = tab<DomIn>(g, L.dom_in);
+    for (int side = 0; side < 2; ++side) {
+        const int d = side ? P.dr : P.dl;
+        E.close2[side] = expansion_limit(0.5 * E.h, hypot(in[d].k[0], in[d].k[1]), EXP_X20, EXP_KA_MAX);
+    }
     tabw<ElemRec>(g, L.elem)[e] = E;
 }
 
@@ -220,14 +235,12 @@ __device__ __forceinline__ void setup_expansion(char* g, const GeomLayout& L, in
     const cd k = {in[d].k[0], in[d].k[1]};
     const double dx = nodes[ab.y].x - nodes[ab.x].x, dy = nodes[ab.y].y - nodes[ab.x].y;
     const double a = 0.5 * sqrt(dx * dx + dy * dy);
-    const double ak = hypot(k.re, k.im), ka = ak * a;
+    const double ak = hypot(k.re, k.im);
     const cd y = cscale(k, 0.5 * a);
     double* rec = tabw<double>(g, L.expn) + ((size_t)side * N + e) * L.exp_stride;
     if (m == 0) {
-        const double inf = __longlong_as_double(0x7ff0000000000000ll);
-        const bool ok = ka >= EXP_KA_MIN && ka <= EXP_KA_MAX;
         auto sq = [](double v) { return v * v; };
-        auto lim = [&](double x, double kamax) { return ok && ka <= kamax ? sq(a / x) : inf; };
+        auto lim = [&](double x, double kamax) { return expansion_limit(a, ak, x, kamax); };
         ExpHead* H = reinterpret_cast<ExpHead*>(rec);
         H->close2 = lim(EXP_X20, EXP_KA_MAX);
         H->near64 = fmax(H->close2, sq(HANKEL_XS_F64 / ak));
@@ -314,30 +327,10 @@ __global__ __launch_bounds__(SETUP_BS) void k_setup(char* g, GeomLayout L, int N
 //                           A[row, w_j] = -sigma eps S + c (eps delta/2 - sigma eps D*)
 //
 // All four sums come from ONE evaluation of H0 and H1, at the element's
-// midpoint: with r = |x_i - c_j|, phi the angle of x_i - c_j to the element's
-// tangent, s the position on the element, Graf's addition theorem gives
-//   H0(k |x_i - c_j - s t_j|) = sum_{m in Z} J_m(k s) H_m(k r) cos(m phi),   |s| < r,
-// so that the rule's sums, whatever its order, are
-//   sum_g w_g H0                 = sum_{m even} mu_m H_m cos m phi,   mu_m = sum_g w_g J_m(k s_g)
-//   sum_g w_g H1 (r_g.t_j)/r_g   = sum_{p odd > 0} (mu_{p-1} - mu_{p+1}) H_p cos p phi
-//   sum_g w_g H1 (r_g.n_j)/r_g   = sum_{p odd > 0} (mu_{p-1} + mu_{p+1}) H_p sin p phi
-// (odd moments vanish, the rule is symmetric; the two vector sums are -1/k
-// times the gradient of the first), and with nu_m = 2 J_m(k h/2) the
-// components along t_j and n_j of the end-point difference are
-//   sum_{p even >= 0} (nu_{p-1} - nu_{p+1}) H_p cos p phi   (p = 0: -nu_1 H_0)
-//   sum_{p even > 0}  (nu_{p-1} + nu_{p+1}) H_p sin p phi
-// without the cancellation of the two end values.  H_2, H_3, ... follow by
-// the upward recurrence (stable: it follows the growing solution), cos m phi
-// and sin m phi by the Chebyshev recurrence.  The coefficients are a record
-// per (side, element), made with the geometry tables.  Orders up to L leave a
-// relative remainder of (h/(2r))^L (and (kh/4)^L/(L+1)! for large r); each
-// record holds the distances beyond which L = 8, 10, 12, 16 and 20 leave less
-// than 4e-17.  Closer than that (a few element lengths), or for elements
+// midpoint (expansion_dev.h).  A few element lengths away, or for elements
 // longer than about 0.8 wavelengths, the Gauss points are evaluated one by
 // one.
 // ---------------------------------------------------------------------------
-
-typedef const __attribute__((address_space(4))) double* ScalarPtr;  // wave-uniform addresses: scalar loads
 
 // Per-block combination constants of one equation block (see the entries above).
 struct BlockConst {
@@ -368,95 +361,6 @@ __device__ __forceinline__ BlockConst block_const(const DomConst& Dm, int sg)
 
 // Waves per SIMD that the far and near kernels leave room for.
 constexpr int FAR_WAVES = 3, NEAR_WAVES = 2;
-
-// The sums of one (row, element) pair without their i/4, i k/4 factors.
-struct PairSums {
-    cd S;       // sum w H0
-    cd Gt, Gn;  // sum w H1 r/|r| along t_j and n_j
-    cd Tt, Tn;  // end-point difference along t_j and n_j
-};
-
-__device__ __forceinline__ void add_scaled(cd& s, double c, double f, cd v)
-{
-    const double w = c * f;
-    s.re = fma(w, v.re, s.re);
-    s.im = fma(w, v.im, s.im);
-}
-__device__ __forceinline__ void add_scaled(cd& s, cd c, double f, cd v)
-{
-    const cd w = {c.re * f, c.im * f};
-    s.re = fma(w.re, v.re, fma(-w.im, v.im, s.re));
-    s.im = fma(w.re, v.im, fma(w.im, v.re, s.im));
-}
-
-// coefficient i of a record (cw doubles each: 2 where some domain of the
-// problem is lossy)
-template <bool CPLX>
-struct Coef;
-template <>
-struct Coef<false> {
-    typedef double T;
-    static __device__ __forceinline__ double get(ScalarPtr c, int cw, int i) { return c[cw * i]; }
-};
-template <>
-struct Coef<true> {
-    typedef cd T;
-    static __device__ __forceinline__ cd get(ScalarPtr c, int, int i) { return {c[2 * i], c[2 * i + 1]}; }
-};
-
-// The expansion up to order Lo (even, >= BASE, uniform over the wave; orders
-// up to BASE are unrolled): hz = H0, h1 = H1 at the midpoint distance, c1, s1
-// = cos phi, sin phi, tz = 2/(k r).
-template <bool CPLX, bool BM, int BASE>
-__device__ __forceinline__ PairSums expand(ScalarPtr c, int cw, int Lo, cd hz, cd h1, double c1, double s1, cd tz)
-{
-    using K = Coef<CPLX>;
-    PairSums P;
-    P.S = P.Gt = P.Gn = P.Tt = P.Tn = {0.0, 0.0};
-    add_scaled(P.S, K::get(c, cw, 0), 1.0, hz);
-    if (BM) add_scaled(P.Tt, K::get(c, cw, 1), 1.0, hz);
-    cd Hp = hz, H = h1, q = {0.0, 0.0};
-    double cp = 1.0, cc = c1, sp = 0.0, ss = s1;
-    const double c2 = c1 + c1;
-    auto next = [&]() {  // order m -> m + 1
-        q.re += tz.re;
-        if (CPLX) q.im += tz.im;  // q = m tz
-        cd Hn;
-        if (CPLX)
-            Hn = {fma(q.re, H.re, fma(-q.im, H.im, -Hp.re)), fma(q.re, H.im, fma(q.im, H.re, -Hp.im))};
-        else
-            Hn = {fma(q.re, H.re, -Hp.re), fma(q.re, H.im, -Hp.im)};
-        Hp = H;
-        H = Hn;
-        const double cn = fma(c2, cc, -cp), sn = fma(c2, ss, -sp);
-        cp = cc;
-        cc = cn;
-        sp = ss;
-        ss = sn;
-    };
-    auto two = [&](int p) {  // orders p (odd) and p + 1
-        const int o = exp_pos(p);
-        if (BM) add_scaled(P.Gt, K::get(c, cw, o), cc, H);
-        add_scaled(P.Gn, K::get(c, cw, o + 1), ss, H);
-        next();
-        add_scaled(P.S, K::get(c, cw, o + 2), cc, H);
-        if (BM) {
-            add_scaled(P.Tt, K::get(c, cw, o + 3), cc, H);
-            add_scaled(P.Tn, K::get(c, cw, o + 4), ss, H);
-        }
-    };
-    two(1);
-#pragma unroll
-    for (int p = 3; p < BASE; p += 2) {
-        next();
-        two(p);
-    }
-    for (int p = BASE + 1; p < Lo; p += 2) {
-        next();
-        two(p);
-    }
-    return P;
-}
 
 // Entries of the u and w columns from the sums (tt = t_i.t_j, tn = t_i.n_j;
 // in the plane n_i.n_j = tt and n_i.t_j = -tn).

@@ -25,13 +25,14 @@ constexpr double MAX_TAN_ARG_K = 0.17632698070846498;
 // One boundary element (128 bytes).  Normal = left normal of the travel
 // direction a -> b.
 struct ElemRec {
-    double cx, cy;  // midpoint = collocation point
-    double tx, ty;  // unit tangent (b - a) / h
-    double nx, ny;  // unit normal (-ty, tx)
-    double h;       // length |b - a|
-    double ax, ay;  // first node
-    double bx, by;  // second node
-    double pad[5];
+    double cx, cy;     // midpoint = collocation point
+    double tx, ty;     // unit tangent (b - a) / h
+    double nx, ny;     // unit normal (-ty, tx)
+    double close2[2];  // ExpHead::close2 in the domains dom_left and dom_right
+    double h;          // length |b - a|
+    double ax, ay;     // first node
+    double bx, by;     // second node
+    double pad[3];
 };
 
 // Expansion record of one element in the domain on one side of it (the sums of
