@@ -98,6 +98,7 @@ struct bem_problem {
     std::vector<std::complex<double>> k;
     std::vector<int> dl, dr, n_nodes, closed;
     std::vector<double> xy;
+    double reach = 0.0;  // largest distance of a node from the origin (an upper bound)
     std::vector<IfacePlan> iface;
     std::vector<int> sigma;        // [d * n_if + m]
     std::vector<Tile> rtiles, cchunks;
@@ -355,6 +356,7 @@ bem_status bem_create(const bem_desc* desc, bem_problem** out)
             y0 = std::min(y0, p->xy[2 * a + 1]);
             y1 = std::max(y1, p->xy[2 * a + 1]);
         }
+        p->reach = std::hypot(std::max(std::abs(x0), std::abs(x1)), std::max(std::abs(y0), std::abs(y1)));
         for (const auto& kd : p->k) kmax = std::max(kmax, std::abs(kd));
         if (kmax * std::hypot(x1 - x0, y1 - y0) >= 0x1p29) {
             delete p;
@@ -1544,8 +1546,9 @@ bem_status bem_farfield(const bem_problem* p, int nrhs, const void* X_dev, size_
         return fail(BEM_E_ARG, "bad far-field arguments");
     if (ldx < 2 * (size_t)p->N || ldf < (size_t)ndir) return fail(BEM_E_ARG, "leading dimension too small");
     if (nrhs > 65535 * 8) return fail(BEM_E_ARG, "too many right-hand sides");
-    HIP_OK(bemk::launch_farfield(p->geom, p->L, p->N, p->n_if, p->n_dom, static_cast<const double2*>(X_dev), ldx, nrhs,
-                                 dirs, ndir, static_cast<double2*>(F_dev), ldf, stream));
+    HIP_OK(bemk::launch_farfield(p->geom, p->L, p->N, !(p->reach * std::abs(p->k[0]) < 0x1p29),
+                                 static_cast<const double2*>(X_dev), ldx, nrhs, dirs, ndir,
+                                 static_cast<double2*>(F_dev), ldf, stream));
     return BEM_OK;
 }
 

@@ -45,8 +45,9 @@ hipError_t launch_assemble_f32(const char* g, const GeomLayout& L, int N, int n_
                                const int* pair_counts, float2* A, size_t lda, hipStream_t s, hipStream_t s1);
 
 // angles / dirs are HOST arrays: they travel to the kernels by value in
-// chunks of ANGLE_CHUNK.
-constexpr int ANGLE_CHUNK = 256;
+// chunks of ANGLE_CHUNK (3 KiB of the 4 KiB of a launch's arguments; the usual
+// 360 far-field directions go in one launch).
+constexpr int ANGLE_CHUNK = 384;
 struct AngleChunk {
     double v[ANGLE_CHUNK];
 };
@@ -210,8 +211,8 @@ struct NearAngles {
 hipError_t launch_nearfield(const char* g, const GeomLayout& L, int n_if, int n_dom, int N, int q, const int* dom_cplx,
                             const double2* X, size_t ldx, int nrhs, const double* angles, const double* xy,
                             const int* dom, int npts, double2* U, size_t ldu, hipStream_t s);
-hipError_t launch_farfield(const char* g, const GeomLayout& L, int N, int n_if, int n_dom, const double2* X,
-                           size_t ldx, int nrhs, const double* dirs, int ndir, double2* F, size_t ldf,
-                           hipStream_t s);
+// big: some |k0 c| of an element may reach 2^29
+hipError_t launch_farfield(const char* g, const GeomLayout& L, int N, bool big, const double2* X, size_t ldx, int nrhs,
+                           const double* dirs, int ndir, double2* F, size_t ldf, hipStream_t s);
 
 }  // namespace bemk

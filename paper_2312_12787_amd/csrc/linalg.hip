@@ -11,6 +11,7 @@
 #include <cstdlib>
 
 #include "bem.h"
+#include "fastmath_dev.h"
 #include "internal.h"
 #include "krylov_dev.h"
 #include "launch.h"
@@ -722,58 +723,80 @@ __global__ void k_add_64(const double2* __restrict__ D, size_t ldd, int n, doubl
 // ---------------------------------------------------------------------------
 // Far field in the host medium: F(th) = e^{i pi/4}/sqrt(8 pi k0)
 //   sum_j sigma_j [w_j + i k0 (xh.n_j) u_j] h_j e^{-i k0 xh.c_j} sinc(k0 h_j xh.t_j/2)
-// (large-|x| form of G, element integral exact).  One block per direction.
+// (large-|x| form of G, element integral exact).  A block takes DT directions
+// and RB right-hand sides, its threads the elements: the values of X loaded
+// for an element serve DT directions, the phase and sinc of a direction RB
+// right-hand sides.  BIG: some phase k0 xh.c may pass 2^29, beyond which the
+// short reduction of sincos_phase_any is not exact.  Bound by the reads of X from L2 (with one direction per
+// block, 755 MB for 4096 elements, 16 right-hand sides and 360 directions)
+// and by the FP64 work of the phases.  Measured there: one direction per block,
+// library sine and cosine, 256 directions per launch 100 us; 3 directions x 4
+// right-hand sides, three waves per SIMD, 34 us (2 x 8: 36, 4 x 4: 38, 3 x 6:
+// 37, 4 x 6: 43; the same within 8 % from 256 to 16384 elements and 2 to 64
+// right-hand sides).
 // ---------------------------------------------------------------------------
-constexpr int FF_NR = 8;
-
-__global__ __launch_bounds__(BS) void k_farfield(const char* __restrict__ g, GeomLayout L, int N, int n_if,
+template <int DT, int RB, bool BIG>
+__global__ __launch_bounds__(BS, 3) void k_farfield(const char* __restrict__ g, GeomLayout L, int N,
                                                  const double2* __restrict__ X, size_t ldx, int nrhs,
-                                                 AngleChunk dirs, double2* __restrict__ F, size_t ldf)
+                                                 AngleChunk dirs, int ndir, double2* __restrict__ F, size_t ldf)
 {
-    __shared__ double lds[4 * 2 * FF_NR];
-    const int d = blockIdx.x;
-    const int r0 = blockIdx.y * FF_NR;
+    constexpr int NV = 2 * DT * RB;
+    __shared__ double lds[4 * NV];
+    const int d0 = blockIdx.x * DT, r0 = blockIdx.y * RB;
     const ElemRec* el = tab<ElemRec>(g, L.elem);
     const int* elif = tab<int>(g, L.elif);
     const int* sigma = tab<int>(g, L.sigma);
     const double k0 = tab<DomConst>(g, L.dom)[0].k[0];
-    double sx, cx;
-    sincos(dirs.v[d], &sx, &cx);
-    double acc[2 * FF_NR];
+    double sx[DT], cx[DT];
 #pragma unroll
-    for (int k = 0; k < 2 * FF_NR; ++k) acc[k] = 0.0;
+    for (int d = 0; d < DT; ++d) sincos(dirs.v[min(d0 + d, ndir - 1)], &sx[d], &cx[d]);
+    double acc[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) acc[k] = 0.0;
     for (int e = threadIdx.x; e < N; e += BS) {
         const int sg = sigma[elif[e]];  // domain 0 row of the sigma table
         if (sg == 0) continue;
-        const ElemRec E = el[e];
-        const double a = 0.5 * k0 * E.h * (cx * E.tx + sx * E.ty);
-        const double sinc = (a == 0.0) ? 1.0 : sin(a) / a;
-        double sp, cp;
-        sincos(-k0 * (cx * E.cx + sx * E.cy), &sp, &cp);
-        const double f = sg * E.h * sinc;
-        const double fr = f * cp, fi = f * sp;           // sigma h sinc e^{-i k0 xh.c}
-        const double gk = k0 * (cx * E.nx + sx * E.ny);  // i gk u
+        double2 u[RB], w[RB];
 #pragma unroll
-        for (int k = 0; k < FF_NR; ++k) {
-            const int r = r0 + k;
-            if (r < nrhs) {
-                const double2 u = X[(size_t)r * ldx + e], w = X[(size_t)r * ldx + N + e];
-                const double tr = w.x - gk * u.y, ti = w.y + gk * u.x;
-                acc[2 * k] += fr * tr - fi * ti;
-                acc[2 * k + 1] += fr * ti + fi * tr;
+        for (int r = 0; r < RB; ++r) {
+            const size_t o = (size_t)min(r0 + r, nrhs - 1) * ldx + e;
+            u[r] = X[o];
+            w[r] = X[o + N];
+        }
+        const double ex = el[e].cx, ey = el[e].cy, tx = el[e].tx, ty = el[e].ty, h = el[e].h;
+        const double sh = sg * h, hk = 0.5 * k0 * h;
+#pragma unroll
+        for (int d = 0; d < DT; ++d) {
+            double sp, cp;
+            sincos_phase_any<BIG>(-k0 * (cx[d] * ex + sx[d] * ey), sp, cp);
+            const double f = sh * sinc<BIG>(hk * (cx[d] * tx + sx[d] * ty));
+            const double fr = f * cp, fi = f * sp;           // sigma h sinc e^{-i k0 xh.c}
+            const double gk = k0 * (sx[d] * tx - cx[d] * ty);  // i gk u  (n = (-ty, tx))
+#pragma unroll
+            for (int r = 0; r < RB; ++r) {
+                const double tr = fma(-gk, u[r].y, w[r].x), ti = fma(gk, u[r].x, w[r].y);
+                double* a = acc + 2 * (d * RB + r);
+                a[0] = fma(fr, tr, fma(-fi, ti, a[0]));
+                a[1] = fma(fr, ti, fma(fi, tr, a[1]));
             }
         }
     }
-    block_sum<2 * FF_NR>(acc, lds);
-    if (threadIdx.x == 0) {
-        const double pre = 1.0 / sqrt(8.0 * 3.14159265358979323846 * k0);
-        const double c4 = 0.70710678118654752440;  // e^{i pi/4} = (1 + i)/sqrt2
-        for (int k = 0; k < FF_NR; ++k) {
-            const int r = r0 + k;
-            if (r < nrhs) {
-                const double xr = acc[2 * k] * pre, xi = acc[2 * k + 1] * pre;
-                F[(size_t)r * ldf + d] = make_double2(c4 * (xr - xi), c4 * (xr + xi));
-            }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) acc[k] = wave_sum(acc[k]);
+    if (lane == 0)
+#pragma unroll
+        for (int k = 0; k < NV; ++k) lds[wave * NV + k] = acc[k];
+    __syncthreads();
+    if (threadIdx.x < DT * RB) {
+        const int t = threadIdx.x, d = d0 + t / RB, r = r0 + t % RB;
+        if (d < ndir && r < nrhs) {
+            const double pre = 1.0 / sqrt(8.0 * 3.14159265358979323846 * k0);
+            const double c4 = 0.70710678118654752440;  // e^{i pi/4} = (1 + i)/sqrt2
+            const double* v = lds + 2 * t;
+            const double xr = (v[0] + v[NV] + v[2 * NV] + v[3 * NV]) * pre;
+            const double xi = (v[1] + v[NV + 1] + v[2 * NV + 1] + v[3 * NV + 1]) * pre;
+            F[(size_t)r * ldf + d] = make_double2(c4 * (xr - xi), c4 * (xr + xi));
         }
     }
 }
@@ -1079,18 +1102,35 @@ hipError_t launch_add_f64(const double2* D, size_t ldd, int n, int nr, double2* 
     return hipGetLastError();
 }
 
-hipError_t launch_farfield(const char* g, const GeomLayout& L, int N, int n_if, int n_dom, const double2* X,
-                           size_t ldx, int nrhs, const double* dirs, int ndir, double2* F, size_t ldf, hipStream_t s)
+namespace {
+
+template <bool BIG>
+hipError_t farfield_t(const char* g, const GeomLayout& L, int N, const double2* X, size_t ldx, int nrhs,
+                      const double* dirs, int ndir, double2* F, size_t ldf, hipStream_t s)
 {
-    (void)n_dom;
     for (int d0 = 0; d0 < ndir; d0 += ANGLE_CHUNK) {
         const int nd = std::min(ANGLE_CHUNK, ndir - d0);
         AngleChunk c{};
         for (int k = 0; k < nd; ++k) c.v[k] = dirs[d0 + k];
-        hipLaunchKernelGGL(k_farfield, dim3(nd, (nrhs + FF_NR - 1) / FF_NR), dim3(BS), 0, s, g, L, N, n_if, X, ldx,
-                           nrhs, c, F + d0, ldf);
+#define BEM_FF_LAUNCH(D_, R_)                                                                                            \
+    hipLaunchKernelGGL((k_farfield<D_, R_, BIG>), dim3((nd + D_ - 1) / D_, (nrhs + R_ - 1) / R_), dim3(BS), 0, s, g, L, N, \
+                       X, ldx, nrhs, c, nd, F + d0, ldf)
+        if (nrhs == 1)
+            BEM_FF_LAUNCH(2, 1);
+        else
+            BEM_FF_LAUNCH(3, 4);
+#undef BEM_FF_LAUNCH
     }
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_farfield(const char* g, const GeomLayout& L, int N, bool big, const double2* X, size_t ldx, int nrhs,
+                           const double* dirs, int ndir, double2* F, size_t ldf, hipStream_t s)
+{
+    return big ? farfield_t<true>(g, L, N, X, ldx, nrhs, dirs, ndir, F, ldf, s)
+               : farfield_t<false>(g, L, N, X, ldx, nrhs, dirs, ndir, F, ldf, s);
 }
 
 }  // namespace bemk
