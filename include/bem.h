@@ -328,7 +328,8 @@ bem_status bem_profile_read(bem_problem *p, bem_profile *out, int reset);
 /* Launch-shape autotuning of the products inside bem_solve (Sec. 3.2: every
  * Krylov step costs one product with the dense matrix).  bem_tune times each
  * candidate launch shape of that product -- rows per wave, columns in flight,
- * column splits, complex-product form -- with the problem's assembled matrix
+ * column splits, complex-product form, or (up to 16 right-hand sides) one
+ * launch by row blocks -- with the problem's assembled matrix
  * and nrhs right-hand sides (the FP64 matrix for BEM_F64; the FP32 matrix,
  * or the FP32 copy of BEM_MIXED, with FP64 vectors otherwise), `reps` timed
  * products each after one untimed (the four fastest twice more, each keeping
@@ -349,7 +350,8 @@ bem_status bem_profile_read(bem_problem *p, bem_profile *out, int reset);
  * synchronises the stream.  BEM_E_STATE: no matrix; BEM_E_ARG: bad sizes or
  * reps outside [1, 100]; BEM_E_NOMEM: work smaller than bem_sizes asks.      */
 typedef struct {
-    int rt, u, splits, g3;       /* chosen shape (vector kernel: rt = u = g3 = 0)       */
+    int rt, u, splits, g3;       /* chosen shape (vector kernel: rt = u = g3 = 0); one   */
+                                 /* launch by row blocks: rt = 1 (vector), g3 = 2 (16)   */
     int candidates;              /* shapes timed                                        */
     double best_ms, default_ms;  /* average product time: chosen shape, built-in shape  */
 } bem_tune_info;

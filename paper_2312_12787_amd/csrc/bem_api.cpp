@@ -765,8 +765,10 @@ bem_status bem_matvec_noalloc(const bem_problem* p, int nrhs, const void* X_dev,
     if (nrhs < 1 || !X_dev || !Y_dev) return fail(BEM_E_ARG, "bad matvec arguments");
     if (ldx < (size_t)n || ldy < (size_t)n) return fail(BEM_E_ARG, "leading dimension < n");
     const bool f64 = p->prec != BEM_F32;
-    const size_t need = bemk::matvec_part_elems_shaped(p->shapes, f64 ? 3 : 0, n, nrhs) *
-                        (f64 ? sizeof(double2) : sizeof(float2));
+    const size_t value = f64 ? sizeof(double2) : sizeof(float2);
+    const size_t need = value * bemk::matvec_part_elems_shaped(p->shapes, f64 ? 3 : 0, n, nrhs,
+                                                               bemk::blocks_overlap(X_dev, ldx * value, Y_dev,
+                                                                                    ldy * value, nrhs));
     if (need > SCRATCH_BYTES)
         return fail(BEM_E_ARG, "bem_matvec_noalloc: the product needs " + std::to_string(need) +
                                    " bytes of partial sums, more than the library's " +
@@ -910,10 +912,10 @@ struct Solver {
     float2* V32(int i) const { return at<float2>(W.V) + (size_t)i * nr * W.ldv; }
 };
 
-// The Krylov step's product Y = A v_j: with more than 4 right-hand sides the
-// matrix-core kernel reads v_j packed (written by the kernel that produced
-// v_j: the cycle start or the previous step's normalisation), with up to 4
-// the vector kernel reads v_j itself.  FP64 product, or the FP32 one on the
+// The Krylov step's product Y = A v_j: with more than 4 right-hand sides, or by
+// row blocks, the kernel reads v_j packed (written by the kernel that produced
+// v_j: the cycle start or the previous step's update), the split vector kernel
+// of up to 4 reads v_j itself.  FP64 product, or the FP32 one on the
 // complex64 basis (FP32 matrix, or the FP32 copy of a BEM_MIXED one), Y in
 // FP64 either way.
 bemk::ProductPlan step_plan(const Solver& c)
@@ -925,7 +927,7 @@ bem_status apply_basis(const Solver& c, int j, double2* Y, size_t ldy)
 {
     const bem_problem* p = c.p;
     const bemk::ProductPlan pl = step_plan(c);
-    if (pl.ng > 0) {
+    if (pl.packed) {
         // from step 1 on the packed inputs are w of the previous step, and the
         // product normalises them (the Arnoldi launches skip the normalisation)
         bemk::StepNorm sn{};
@@ -1173,7 +1175,7 @@ bem_status gmres_begin(GmItem& g, int ring, int nev)
     // the products read v_j packed (more than 4 right-hand sides), written by
     // the cycle start and the step's normalisation kernel
     g.xt = nullptr;
-    if (g.pl.ng > 0) {
+    if (g.pl.packed) {
         if (c.v32())
             g.xt = reinterpret_cast<float2*>(c.at<double2>(c.W.mv_part)) + g.pl.xt_offset;
         else

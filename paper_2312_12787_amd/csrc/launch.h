@@ -59,7 +59,10 @@ hipError_t launch_rhs(const char* g, const GeomLayout& L, int N, const double* a
 // the shapes given (types as in the shape classes below).
 size_t matvec_part_elems(int n, int nrhs);
 struct MvShapes;
-size_t matvec_part_elems_shaped(const MvShapes& sh, int types, int n, int nrhs);
+// (in_place: X and Y overlap, so no product may write Y while it reads X)
+size_t matvec_part_elems_shaped(const MvShapes& sh, int types, int n, int nrhs, bool in_place);
+// Whether two blocks of nrhs columns, xcol and ycol bytes apart, share memory.
+bool blocks_overlap(const void* X, size_t xcol, const void* Y, size_t ycol, int nrhs);
 
 // Launch shape of a product: row tiles per wave, column steps in flight,
 // column splits, 3-product form (the vector kernel uses splits only).  Shape
@@ -101,13 +104,14 @@ hipError_t launch_matvec_f32v(const float2* A, size_t lda, int n, const float2* 
                               const KernelHook* hook = nullptr, const MvShapes* shapes = nullptr);
 hipError_t launch_matvec_f32(const float2* A, size_t lda, int n, const float2* X, size_t ldx, int nrhs, float2* Y,
                              size_t ldy, float2* partial, hipStream_t s, const KernelHook* hook = nullptr, const MvShapes* shapes = nullptr);
-// The products of the Krylov steps with more than 4 right-hand sides: the
-// matrix-core kernel reads them packed at part + xt_offset (XT[c * xw + r],
+// The products of the Krylov steps with more than 4 right-hand sides, or by row
+// blocks: the kernel reads them packed at part + xt_offset (XT[c * xw + r],
 // zero for nr <= r < xw), written there by the kernel that produced the basis
-// vector (start of a cycle, end of the previous step), and its split partial
-// sums are added in split order into Y (FP64).
+// vector (start of a cycle, end of the previous step); split partial sums are
+// added in split order into Y (FP64).
 struct ProductPlan {
     MvShape shape;
+    bool row, packed;  // row-block product; inputs packed by the caller
     int ng, splits, xw;
     size_t xt_offset;  // in complex values of the accumulation type
 };

@@ -407,6 +407,302 @@ __global__ __launch_bounds__(BS, mfma_min_waves(sizeof(T), RT, NG)) void k_matve
     }
 }
 
+// ---------------------------------------------------------------------------
+// Row-block products: one workgroup owns 16 rows and ALL columns, its waves
+// take the column groups in turn and add their sums through LDS in wave order,
+// so a product is one launch: no split partial sums in memory, no reduction
+// pass, and (bem_matvec) X read where it lies instead of packed first.  For
+// systems small enough that launches and idle compute units, not HBM, set the
+// time: a product split over columns needs two to three launches, and its
+// built-in shapes fill 64 to 128 of 256 CUs at n = 1024 .. 2048.  The matrix
+// stays in the Infinity Cache, so its loads are ordinary ones (non-temporal
+// ones made the 16-right-hand-side product of n = 1554 25.3 instead of 20.8
+// us).  Bound by one CU's read and FP64 matrix rate (a block of 16 rows has
+// 1/97 of the work at n = 1554) and by the chain load - product - LDS sum -
+// store.
+// ---------------------------------------------------------------------------
+enum RowMode { ROW_PRODUCT, ROW_RESIDUAL, ROW_STEP };
+
+// What becomes of the sums: Y = A X, R = B - A X, or the Krylov step's product
+// with the previous vector's normalisation (see k_step_reduce).
+template <class TY, class TV>
+struct RowOut {
+    TY* Y;
+    size_t ldy;
+    const double2* B;
+    size_t ldb;
+    const double* nrm;
+    int nu;
+    TV* V;
+    size_t ldv;
+    double* hnorm;
+    int* active;
+};
+
+constexpr int ROW_MAX_WAVES = 16;
+
+// |w| of the step's right-hand sides: wave w takes r = w, w + nw; the loads go
+// out before the product, the sums are formed after it.
+struct StepScale {
+    double part[2];
+    template <class O>
+    __device__ __forceinline__ void load(const O& o, int wave, int nw, int nr)
+    {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            part[k] = 0.0;
+            const int r = wave + k * nw;
+            if (r < nr)
+                for (int b = threadIdx.x & 63; b < o.nu; b += 64) part[k] += o.nrm[(size_t)r * o.nu + b];
+        }
+    }
+    template <class O>
+    __device__ __forceinline__ void finish(const O& o, int wave, int nw, int nr, double* inv_s, int* act_s) const
+    {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int r = wave + k * nw;
+            if (r >= nr) continue;
+            const double beta = sqrt(dev::wave_sum(part[k]));
+            if ((threadIdx.x & 63) == 0) {
+                const int act = o.active[r];
+                inv_s[r] = dev::inv_beta(beta);
+                act_s[r] = act;
+                if (blockIdx.x == 0) {
+                    if (act == 1) o.hnorm[r] = beta;
+                    // every block of a marked column skips it, whether it reads the mark or the zero
+                    if (act == dev::STOPPING) o.active[r] = 0;
+                }
+            }
+        }
+    }
+};
+
+__device__ __forceinline__ void st_row(double2* p, double2 v) { *p = v; }
+__device__ __forceinline__ void st_row(float2* p, double2 v) { *p = make_float2((float)v.x, (float)v.y); }
+
+template <int MODE, class O>
+__device__ __forceinline__ void row_store(const O& o, int row, int r, double sr, double si, const double* inv_s,
+                                          const int* act_s)
+{
+    auto* y = o.Y + (size_t)r * o.ldy + row;
+    if (MODE == ROW_RESIDUAL) {
+        const double2 b = o.B[(size_t)r * o.ldb + row];
+        sr = b.x - sr;
+        si = b.y - si;
+    } else if (MODE == ROW_STEP) {
+        const double inv = inv_s[r];
+        const double2 w = make_double2(y->x, y->y);
+        if (act_s[r] == 1) st_row(o.V + (size_t)r * o.ldv + row, make_double2(w.x * inv, w.y * inv));
+        sr *= inv;
+        si *= inv;
+    }
+    st_row(y, make_double2(sr, si));
+}
+
+// Matrix-core form, 5 to 16 right-hand sides: operand layout, 3-product form
+// and result rows as k_matvec_mfma's; the loads of a wave's next 4U columns go
+// out before the products of the current ones.  PACKED: X is XT[c * 16 + r],
+// else column-major (ldx).
+template <class TA, class T, class TX, int U, bool PACKED, int MODE, class O>
+__global__ __launch_bounds__(64 * ROW_MAX_WAVES) void k_rowblock_mfma(const TA* __restrict__ A, size_t lda, int n,
+                                                                      const TX* __restrict__ X, size_t ldx, int nrhs,
+                                                                      const O o)
+{
+    using M = Mfma<T>;
+    using acc = typename M::acc;
+    extern __shared__ double row_lds[];
+    __shared__ double inv_s[16];
+    __shared__ int act_s[16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const int lr = lane & 15, lk = lane >> 4;
+    const int row0 = blockIdx.x * 16;
+    const TA* ap = A + min(row0 + lr, n - 1);
+    const TX* xp = PACKED ? X + lr : X + (size_t)min(lr, nrhs - 1) * ldx;
+    StepScale sc;
+    if (MODE == ROW_STEP) sc.load(o, wave, nw, nrhs);
+    acc rr0{0, 0, 0, 0}, rr1{0, 0, 0, 0}, ii{0, 0, 0, 0};
+    auto load = [&](TA (&a)[U], TX (&x)[U], int c) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int col = min(c + 4 * u + lk, n - 1);
+            x[u] = PACKED ? xp[(size_t)col * 16] : xp[col];
+            a[u] = ap[(size_t)col * lda];
+        }
+    };
+    auto compute = [&](const TA (&a)[U], const TX (&x)[U], int c) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool ok = c + 4 * u + lk < n;
+            const T ar = ok ? (T)a[u].x : T(0), ai = ok ? (T)a[u].y : T(0);
+            const T xr = ok ? (T)x[u].x : T(0), xi = ok ? (T)x[u].y : T(0);
+            rr0 = M::run(ar, xr, rr0);
+            rr1 = M::run(ai, xi, rr1);
+            ii = M::run(ar + ai, xr + xi, ii);
+        }
+    };
+    int c = wave * 4 * U;
+    if (c < n) {
+        TA a[U];
+        TX x[U];
+        load(a, x, c);
+        for (;;) {
+            const int cn = c + nw * 4 * U;
+            if (cn >= n) {
+                compute(a, x, c);
+                break;
+            }
+            TA an[U];
+            TX xn[U];
+            load(an, xn, cn);
+            compute(a, x, c);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                a[u] = an[u];
+                x[u] = xn[u];
+            }
+            c = cn;
+        }
+    }
+    T* red = reinterpret_cast<T*>(row_lds);  // [wave][2 j + part][lane]
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        red[(wave * 8 + 2 * j) * 64 + lane] = rr0[j] - rr1[j];
+        red[(wave * 8 + 2 * j + 1) * 64 + lane] = ii[j] - rr0[j] - rr1[j];
+    }
+    if (MODE == ROW_STEP) sc.finish(o, wave, nw, nrhs, inv_s, act_s);
+    __syncthreads();
+    const int t = threadIdx.x, rl = t & 15, r = t >> 4;  // thread: row rl, right-hand side r
+    const int row = row0 + rl;
+    if (t >= 256 || r >= nrhs || row >= n) return;
+    // the lane and element that hold row rl of right-hand side r
+    const bool f64 = sizeof(T) == 8;
+    const int j = f64 ? rl >> 2 : rl & 3, src = (f64 ? rl & 3 : rl >> 2) * 16 + r;
+    T sr = T(0), si = T(0);
+    for (int w = 0; w < nw; ++w) {
+        sr += red[(w * 8 + 2 * j) * 64 + src];
+        si += red[(w * 8 + 2 * j + 1) * 64 + src];
+    }
+    row_store<MODE>(o, row, r, (double)sr, (double)si, inv_s, act_s);
+}
+
+// Vector form, NR = 1 to 4 right-hand sides: lane l holds row l % 16 and column
+// l / 16 of each 16 x 4 tile.  All of X goes to LDS first (from global memory a
+// wave's read of one value of X costs as much of the L1's rate as its read of a
+// tile of A).  PACKED: X is XT[c * NR + r].
+template <int NR, class TA, class TX, class ACC, int U, bool PACKED, int MODE, class O>
+__global__ __launch_bounds__(64 * ROW_MAX_WAVES) void k_rowblock_vec(const TA* __restrict__ A, size_t lda, int n,
+                                                                     const TX* __restrict__ X, size_t ldx, const O o)
+{
+    using S = decltype(ACC{}.x);
+    extern __shared__ double row_lds[];
+    ACC* xs = reinterpret_cast<ACC*>(row_lds);  // [column][NR]
+    __shared__ S red[ROW_MAX_WAVES][2 * NR][16];
+    __shared__ double inv_s[4];
+    __shared__ int act_s[4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const int lr = lane & 15, lk = lane >> 4;
+    const int row0 = blockIdx.x * 16;
+    const TA* ap = A + min(row0 + lr, n - 1);
+    StepScale sc;
+    if (MODE == ROW_STEP) sc.load(o, wave, nw, NR);
+    auto load = [&](TA (&a)[U], int c) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) a[u] = ap[(size_t)min(c + 4 * u + lk, n - 1) * lda];
+    };
+    int c = wave * 4 * U;
+    TA a[U];
+    if (c < n) load(a, c);
+    for (int t = threadIdx.x; t < n * NR; t += blockDim.x) {
+        const int r = PACKED ? 0 : t / n;
+        const TX x = PACKED ? X[t] : X[(size_t)r * ldx + (t - r * n)];
+        ACC v;
+        v.x = (S)x.x;
+        v.y = (S)x.y;
+        xs[PACKED ? t : (t - r * n) * NR + r] = v;
+    }
+    __syncthreads();
+    S ar[NR], ai[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) ar[r] = ai[r] = S(0);
+    while (c < n) {
+        const int cn = c + nw * 4 * U;
+        TA an[U];
+        if (cn < n) load(an, cn);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int col = c + 4 * u + lk;
+            const bool ok = col < n;
+            const S axr = ok ? (S)a[u].x : S(0), axi = ok ? (S)a[u].y : S(0);
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                const ACC x = xs[min(col, n - 1) * NR + r];
+                const S xr = ok ? x.x : S(0), xi = ok ? x.y : S(0);
+                ar[r] = fma(axr, xr, ar[r]);
+                ar[r] = fma(-axi, xi, ar[r]);
+                ai[r] = fma(axr, xi, ai[r]);
+                ai[r] = fma(axi, xr, ai[r]);
+            }
+        }
+        if (cn >= n) break;
+#pragma unroll
+        for (int u = 0; u < U; ++u) a[u] = an[u];
+        c = cn;
+    }
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        ar[r] += __shfl_xor(ar[r], 16, 64);
+        ai[r] += __shfl_xor(ai[r], 16, 64);
+        ar[r] += __shfl_xor(ar[r], 32, 64);
+        ai[r] += __shfl_xor(ai[r], 32, 64);
+        if (lk == 0) {
+            red[wave][2 * r][lr] = ar[r];
+            red[wave][2 * r + 1][lr] = ai[r];
+        }
+    }
+    if (MODE == ROW_STEP) sc.finish(o, wave, nw, NR, inv_s, act_s);
+    __syncthreads();
+    const int t = threadIdx.x, rl = t & 15, r = t >> 4;
+    const int row = row0 + rl;
+    if (r >= NR || row >= n) return;
+    S sr = S(0), si = S(0);
+    for (int w = 0; w < nw; ++w) {
+        sr += red[w][2 * r][rl];
+        si += red[w][2 * r + 1][rl];
+    }
+    row_store<MODE>(o, row, r, (double)sr, (double)si, inv_s, act_s);
+}
+
+// X of a row-block vector product fits the LDS beside the wave sums.
+constexpr size_t ROW_X_BYTES = 128 * 1024;
+bool row_fits(int n, int nr, size_t value_bytes) { return nr > 4 || (size_t)n * nr * value_bytes <= ROW_X_BYTES; }
+
+// A row-block product of up to 16 right-hand sides.  16 waves per workgroup
+// where the rows alone leave the chip's CUs less than one workgroup each.
+template <class TA, class TX, class ACC, bool PACKED, int MODE, class O>
+void launch_rowblock(const TA* A, size_t lda, int n, const TX* X, size_t ldx, int nr, const O& o, hipStream_t s)
+{
+    using S = decltype(ACC{}.x);
+    const int blocks = (n + 15) / 16, nw = blocks <= 256 ? 16 : 8;
+    constexpr int U = sizeof(TA) == 16 || sizeof(S) == 8 ? 4 : 8;
+    const size_t xlds = (size_t)n * nr * sizeof(ACC);
+#define BEM_ROW_VEC(NR_)                                                                                              \
+    hipLaunchKernelGGL((k_rowblock_vec<NR_, TA, TX, ACC, U, PACKED, MODE, O>), dim3(blocks), dim3(64 * nw), xlds, s, A, \
+                       lda, n, X, ldx, o)
+    if (nr > 4)
+        hipLaunchKernelGGL((k_rowblock_mfma<TA, S, TX, U, PACKED, MODE, O>), dim3(blocks), dim3(64 * nw),
+                           (size_t)nw * 8 * 64 * sizeof(S), s, A, lda, n, X, ldx, nr, o);
+    else if (nr == 1)
+        BEM_ROW_VEC(1);
+    else if (nr == 2)
+        BEM_ROW_VEC(2);
+    else if (nr == 3)
+        BEM_ROW_VEC(3);
+    else
+        BEM_ROW_VEC(4);
+#undef BEM_ROW_VEC
+}
+
 // XT[c * xw + r] = X[r * ldx + c] (r < nr), 0 for nr <= r < xw (xw = 16, 32, 48, 64)
 template <class TX, class V2>
 __global__ void k_pack_xt(const TX* __restrict__ X, size_t ldx, int n, int nr, int xw, V2* __restrict__ XT)
@@ -442,6 +738,39 @@ MvShape mfma_default(int n, int ng, bool f64)
     }
     c.splits = std::max(1, std::min(c.splits, std::max(1, n / 64)));
     return c;
+}
+
+// Shapes of the row-block products (in a table row: vector class rt = 1, one
+// group of 16 g3 = 2; both values had no meaning of their own before).
+constexpr MvShape ROW_VEC{1, 0, 1, 0}, ROW_MFMA{1, 4, 1, 2};
+bool row_shape(int ng, const MvShape& c) { return ng == 0 ? c.rt == 1 : ng == 1 && c.g3 == 2; }
+
+// A system takes the row-block product by itself while its matrix fits the 256
+// MiB Infinity Cache (n <= 4096 in FP64, 5792 in FP32) and it has up to 16
+// right-hand sides.  Both ways timed through bem_matvec, us (split / row-block;
+// 10 is what the call costs the host), 1, 3 and 16 right-hand sides, FP64:
+//   n  512  12.6 / 10.2   12.5 / 10.2   15.0 / 10.8
+//   n 1554  18.3 / 10.1   27.2 / 14.2   28.4 / 20.7
+//   n 2674  29.6 / 19.1   37.5 / 23.1   38.2 / 30.6
+//   n 4096  69.5 / 40.0   64.1 / (X does not fit)  58.1 / 47.9
+//   n 5400  88.9 / 103    110 / -       114 / 141
+// FP32: n 2674  22.7 / 12.3, 43.3 / 15.8, 29.6 / 22.7; n 5400  53.5 / 41.2,
+// 75.6 / 63.9, 73.5 / 75.3; n 6800  70.3 / 69.1, 110 / -, 89 / 126.
+bool row_default(int types, int ng, int n)
+{
+    return ng <= 1 && (size_t)n * n * (types & 2 ? sizeof(double2) : sizeof(float2)) <= ((size_t)256 << 20);
+}
+
+// The built-in shapes of a class (vector: ng = 0): split over columns, and the
+// one it takes by itself.
+MvShape split_shape(int types, int ng, int n)
+{
+    return ng == 0 ? MvShape{0, 0, matvec_splits_valu(n), 0} : mfma_default(n, ng, types & 1);
+}
+MvShape default_shape(int types, int ng, int n)
+{
+    if (row_default(types, ng, n)) return ng == 0 ? ROW_VEC : ROW_MFMA;
+    return split_shape(types, ng, n);
 }
 
 bool shape_valid(int ng, const MvShape& c)
@@ -519,7 +848,7 @@ namespace {
 // tuned table, else the default; splits clamped to split_cap.
 MvShape shape_from(const ShapeSnapshot* snap, int types, int ng, int n)
 {
-    MvShape c = ng == 0 ? MvShape{0, 0, matvec_splits_valu(n), 0} : mfma_default(n, ng, types & 1);
+    MvShape c = default_shape(types, ng, n);
     bool have = false;
     if (ng > 0) {
         MvShape t{};
@@ -610,17 +939,29 @@ hipError_t matvec_any(const TA* A, size_t lda, int n, const TX* X, size_t ldx, i
 {
     using S = decltype(ACC{}.x);
     constexpr int types = (sizeof(TA) == 16 ? 2 : 0) + (sizeof(S) == 8 ? 1 : 0);
-    const int splits = pick_shape(shapes, types, 0, n).splits;
-    const int cps = (n + splits - 1) / splits;
     const int rowblocks = (n + 64 * MV_WAVES - 1) / (64 * MV_WAVES);
     const int kind = B ? KIND_RESIDUAL : KIND_MATVEC;
+    const bool in_place = blocks_overlap(X, ldx * sizeof(TX), Y, ldy * sizeof(TY), nrhs);
     for (int r0 = 0; r0 < nrhs; r0 += MFMA_MAX_RHS) {
         const int nr = std::min(MFMA_MAX_RHS, nrhs - r0);
         const TX* Xg = X + (size_t)r0 * ldx;
-        if (nr > 4) {
+        const double2* Bg = B ? B + (size_t)r0 * ldb : nullptr;
+        const int ng = nr > 4 ? (nr + 15) / 16 : 0;
+        const MvShape picked = pick_shape(shapes, types, ng, n);
+        const bool row = row_shape(ng, picked) && !in_place && row_fits(n, nr, sizeof(ACC));
+        const MvShape cfg = row || !row_shape(ng, picked) ? picked : split_shape(types, ng, n);
+        if (row) {
+            const RowOut<TY, double2> o{Y + (size_t)r0 * ldy, ldy, Bg, ldb, nullptr, 0, nullptr, 0, nullptr, nullptr};
+            hook_call(hook, kind, 0, s);
+            if (B)
+                launch_rowblock<TA, TX, ACC, false, ROW_RESIDUAL>(A, lda, n, Xg, ldx, nr, o, s);
+            else
+                launch_rowblock<TA, TX, ACC, false, ROW_PRODUCT>(A, lda, n, Xg, ldx, nr, o, s);
+            hook_call(hook, kind, 1, s);
+            continue;
+        }
+        if (ng > 0) {
             // pack X right-hand-side fastest into the tail of the partial buffer
-            const int ng = (nr + 15) / 16;
-            const MvShape cfg = pick_shape(shapes, types, ng, n);
             const int ms = cfg.splits;
             const int mcps = ((n + ms - 1) / ms + 31) / 32 * 32;
             ACC* xt = part + (size_t)ms * nr * n;
@@ -632,9 +973,11 @@ hipError_t matvec_any(const TA* A, size_t lda, int n, const TX* X, size_t ldx, i
                                             n, xt, nr, part, mcps);
             hook_call(hook, kind, 1, s);
             hipLaunchKernelGGL((k_matvec_reduce<ACC, TY>), dim3((n + BS - 1) / BS, nr), dim3(BS), 0, s, part, ms, n,
-                               nr, Y + (size_t)r0 * ldy, ldy, B ? B + (size_t)r0 * ldb : nullptr, ldb);
+                               nr, Y + (size_t)r0 * ldy, ldy, Bg, ldb);
             continue;
         }
+        const int splits = cfg.splits;
+        const int cps = (n + splits - 1) / splits;
         dim3 grid(rowblocks, splits);
         hook_call(hook, kind, 0, s);
         if (nr == 1)
@@ -645,7 +988,7 @@ hipError_t matvec_any(const TA* A, size_t lda, int n, const TX* X, size_t ldx, i
             hipLaunchKernelGGL((k_matvec<4, TA, TX, ACC>), grid, dim3(BS), 0, s, A, lda, n, Xg, ldx, nr, part, cps);
         hook_call(hook, kind, 1, s);
         hipLaunchKernelGGL((k_matvec_reduce<ACC, TY>), dim3((n + BS - 1) / BS, nr), dim3(BS), 0, s, part, splits, n,
-                           nr, Y + (size_t)r0 * ldy, ldy, B ? B + (size_t)r0 * ldb : nullptr, ldb);
+                           nr, Y + (size_t)r0 * ldy, ldy, Bg, ldb);
     }
     return hipGetLastError();
 }
@@ -697,14 +1040,34 @@ __global__ void k_step_reduce(const ACC* __restrict__ part, int splits, int n, i
     *y = make_double2((double)sr * inv, (double)si * inv);
 }
 
-// Products of the Krylov steps with 5-64 right-hand sides, packed by the
-// caller at part + xt_offset: the matrix-core kernel and the split reduction
-// (with sn: inputs not yet normalised, see k_step_reduce).
+// Products of the Krylov steps whose inputs the caller has packed at part +
+// xt_offset: the row-block product, or (5-64 right-hand sides) the matrix-core
+// kernel and the split reduction (with sn: inputs not yet normalised, see
+// k_step_reduce).
 template <class TA, class ACC>
 hipError_t product_packed(const ProductPlan& pl, const TA* A, size_t lda, int n, int nr, ACC* part, double2* Y,
                           size_t ldy, const StepNorm* sn, hipStream_t s, const KernelHook* hook)
 {
     using S = decltype(ACC{}.x);
+    if (pl.row) {
+        const ACC* xt = part + pl.xt_offset;
+        hook_call(hook, KIND_MATVEC, 0, s);
+        if (!sn)
+            launch_rowblock<TA, ACC, ACC, true, ROW_PRODUCT>(
+                A, lda, n, xt, 0, nr, RowOut<double2, double2>{Y, ldy, nullptr, 0, nullptr, 0, nullptr, 0, nullptr, nullptr}, s);
+        else if (sn->v32)
+            launch_rowblock<TA, ACC, ACC, true, ROW_STEP>(
+                A, lda, n, xt, 0, nr,
+                RowOut<double2, float2>{Y, ldy, nullptr, 0, sn->norm_part, sn->nu, static_cast<float2*>(sn->V), sn->ldv,
+                                        sn->hnorm, sn->active}, s);
+        else
+            launch_rowblock<TA, ACC, ACC, true, ROW_STEP>(
+                A, lda, n, xt, 0, nr,
+                RowOut<double2, double2>{Y, ldy, nullptr, 0, sn->norm_part, sn->nu, static_cast<double2*>(sn->V),
+                                         sn->ldv, sn->hnorm, sn->active}, s);
+        hook_call(hook, KIND_MATVEC, 1, s);
+        return hipGetLastError();
+    }
     const int rows_per_block = 16 * pl.shape.rt * MV_WAVES;
     const int mcps = ((n + pl.splits - 1) / pl.splits + 31) / 32 * 32;
     hook_call(hook, KIND_MATVEC, 0, s);
@@ -731,9 +1094,12 @@ ProductPlan product_plan(const MvShapes* shapes, int types, int n, int nr)
     ProductPlan pl{};
     pl.ng = nr > 4 ? (nr + 15) / 16 : 0;
     pl.shape = pick_shape(shapes, types, pl.ng, n);
+    pl.row = row_shape(pl.ng, pl.shape) && row_fits(n, nr, types & 1 ? sizeof(double2) : sizeof(float2));
+    if (!pl.row && row_shape(pl.ng, pl.shape)) pl.shape = split_shape(types, pl.ng, n);
+    pl.packed = pl.row || pl.ng > 0;
     pl.splits = pl.shape.splits;
-    pl.xt_offset = pl.ng > 0 ? (size_t)pl.splits * nr * n : 0;
-    pl.xw = 16 * pl.ng;
+    pl.xt_offset = pl.packed && !pl.row ? (size_t)pl.splits * nr * n : 0;
+    pl.xw = pl.ng > 0 ? 16 * pl.ng : pl.row ? nr : 0;
     return pl;
 }
 
@@ -778,13 +1144,22 @@ size_t matvec_part_elems(int n, int nrhs)
     return e * (size_t)n;
 }
 
-size_t matvec_part_elems_shaped(const MvShapes& sh, int types, int n, int nrhs)
+bool blocks_overlap(const void* X, size_t xcol, const void* Y, size_t ycol, int nrhs)
+{
+    const char *x = static_cast<const char*>(X), *y = static_cast<const char*>(Y);
+    return x < y + ycol * nrhs && y < x + xcol * nrhs;
+}
+
+size_t matvec_part_elems_shaped(const MvShapes& sh, int types, int n, int nrhs, bool in_place)
 {
     size_t e = 0;
     for (int r0 = 0; r0 < nrhs; r0 += MFMA_MAX_RHS) {
         const int nr = std::min(MFMA_MAX_RHS, nrhs - r0);
         const int ng = nr > 4 ? (nr + 15) / 16 : 0;
-        const size_t c = (size_t)sh.s[types][ng].splits * nr + (ng ? 16 * ng : 0);
+        const bool row = row_shape(ng, sh.s[types][ng]);
+        if (row && !in_place && row_fits(n, nr, types & 1 ? sizeof(double2) : sizeof(float2)))
+            continue;  // neither partial sums nor a packed copy
+        const size_t c = (size_t)(row ? split_shape(types, ng, n) : sh.s[types][ng]).splits * nr + (ng ? 16 * ng : 0);
         e = std::max(e, c);
     }
     return e * (size_t)n;
@@ -868,12 +1243,14 @@ std::vector<MvShape> candidate_shapes(int types, int ng, int n)
     const int cap = split_cap(n, ng);
     std::vector<int> splits;
     for (int s = cap; s >= 1; s /= 2) splits.push_back(s);
+    const MvShape d = default_shape(types, ng, n);
+    out.push_back(d);  // the default first
+    if (ng <= 1 && !row_shape(ng, d)) out.push_back(ng == 0 ? ROW_VEC : ROW_MFMA);
     if (ng == 0) {
-        for (int s : splits) out.push_back(MvShape{0, 0, s, 0});
+        for (int s : splits)
+            if (row_shape(0, d) || s != d.splits) out.push_back(MvShape{0, 0, s, 0});
         return out;
     }
-    const MvShape d = mfma_default(n, ng, types & 1);
-    out.push_back(d);  // the default first
     const int rts[] = {1, 2, 4}, us[] = {2, 4, 8};
     for (int rt : rts)
         for (int u : us)
