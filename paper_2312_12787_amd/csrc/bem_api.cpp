@@ -225,7 +225,7 @@ WorkLayout make_work(int n, int nr, int m)
     W.anblk = bemk::arnoldi_blocks(n);
     W.dot_part = take((size_t)nr * W.anblk * (m + 1) * sizeof(double2));
     W.dot_part2 = take((size_t)nr * W.anblk * (m + 1) * sizeof(double2));
-    W.upd_part = take((size_t)nr * W.anblk * sizeof(double));
+    W.upd_part = take((size_t)bemk::update_blocks(n, nr) * nr * sizeof(double));
     W.thr = take((size_t)nr * sizeof(double));
     W.iters = take((size_t)nr * sizeof(int));
     W.y = take((size_t)nr * (m + 1) * sizeof(double2));
@@ -933,7 +933,7 @@ bem_status apply_basis(const Solver& c, int j, double2* Y, size_t ldy)
         bemk::StepNorm sn{};
         if (j >= 1) {
             sn.norm_part = c.at<double>(c.W.upd_part);
-            sn.nu = bemk::update_blocks(c.n);
+            sn.nu = bemk::update_blocks(c.n, c.nr);
             sn.V = c.v32() ? static_cast<void*>(c.V32(j)) : static_cast<void*>(c.V(j));
             sn.ldv = c.W.ldv;
             sn.v32 = c.v32();

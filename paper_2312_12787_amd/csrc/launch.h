@@ -124,14 +124,14 @@ ProductPlan product_plan(const MvShapes* shapes, int types, int n, int nr);
 // of step j - 1.
 struct StepNorm {
     const double* norm_part;  // [nr][nu] partial sums of |w|^2 of the update blocks
-    int nu;                   // update_blocks(n)
+    int nu;                   // update_blocks(n, nr)
     void* V;                  // v_j, column-major (ldv): complex64 if v32, else complex128
     size_t ldv;
     bool v32;
     double* hnorm;
     int* active;
 };
-int update_blocks(int n);
+int update_blocks(int n, int nr);
 hipError_t launch_product_packed_f64(const ProductPlan& pl, const double2* A, size_t lda, int n, int nr,
                                      double2* part, double2* Y, size_t ldy, const StepNorm* sn, hipStream_t s,
                                      const KernelHook* hook);
@@ -152,7 +152,8 @@ hipError_t launch_residual_f32A(const float2* A, size_t lda, int n, const double
 hipError_t launch_col_norms(const double2* X, size_t ldx, int n, int nr, double* partial, double* out,
                             hipStream_t s);
 // Row chunks of the projection kernel and blocks of the update kernel: the
-// partial-sum buffers hold arnoldi_blocks(n) entries per right-hand side.
+// partial-sum buffers hold arnoldi_blocks(n) and update_blocks(n, nr) entries
+// per right-hand side.
 int arnoldi_blocks(int n);
 // One Arnoldi step j (0..m) of the batched GMRES cycle (linalg.hip): delayed
 // re-orthogonalisation, two passes over the basis; W = A V_j for j < m.

@@ -310,6 +310,39 @@ __device__ __forceinline__ double2 cmul2(double2 a, double2 b)
     return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 
+// S = sum over row chunks of the projection partials P, T of Q (if any), in
+// chunk order; a block of NT threads.
+template <int NT>
+__device__ __forceinline__ void sum_partials(int r, int ns, int jc, const double2* __restrict__ partP,
+                                             const double2* __restrict__ partQ, double2* S, double2* T)
+{
+    for (int i = threadIdx.x; i < jc; i += NT) {
+        const double2* p = partP + (size_t)r * ns * jc + i;
+        double pr = 0.0, pi = 0.0;
+        if (partQ) {
+            const double2* q = partQ + (size_t)r * ns * jc + i;
+            double qr = 0.0, qi = 0.0;
+#pragma unroll 4
+            for (int b = 0; b < ns; ++b) {
+                const double2 x = p[(size_t)b * jc], y = q[(size_t)b * jc];
+                pr += x.x;
+                pi += x.y;
+                qr += y.x;
+                qi += y.y;
+            }
+            T[i] = make_double2(qr, qi);
+        } else {
+#pragma unroll 4
+            for (int b = 0; b < ns; ++b) {
+                const double2 x = p[(size_t)b * jc];
+                pr += x.x;
+                pi += x.y;
+            }
+        }
+        S[i] = make_double2(pr, pi);
+    }
+}
+
 // The small work of step j for one right-hand side (one block): sum the
 // projection partials into S = [s, alpha] and T = [t, tau], complete column
 // j-1 (Givens, residual, decision) and form column j.  Hraw holds the
@@ -337,9 +370,19 @@ __device__ __forceinline__ void block_sum4x3(double& a, double& b, double& c, do
     c = ((red[8] + red[9]) + red[10]) + red[11];
 }
 
-// LDS of the step and update blocks (double2 units): five arrays of m + 1
-// entries, the wave partials zp[4][64], then reduction slots and a flag.
-__host__ __device__ constexpr size_t arn_lds_elems(int m) { return 5 * ((size_t)m + 1) + 4 * 64 + 16; }
+// LDS of the step and update blocks (double2 units).  Step: five arrays of m + 1
+// entries, the wave partials, then reduction slots and a flag.  The partials
+// are zp[3][ARN_ZROWS] where they are formed beside the rotations, zp[4][64]
+// where the arrays of a very long restart leave no more room.  Update: two
+// such arrays, 16 reduction slots and, where its waves share the basis, two
+// sums of each wave and row.
+constexpr int ARN_ZROWS = 128, ARN_ZMAX = 1900;
+__host__ __device__ constexpr size_t arn_zp_elems(int m) { return m <= ARN_ZMAX ? 3 * ARN_ZROWS : 4 * 64; }
+__host__ __device__ constexpr size_t arn_lds_elems(int m)
+{
+    const size_t step = 5 * ((size_t)m + 1) + arn_zp_elems(m) + 16, update = 2 * ((size_t)m + 1) + 16 + 2 * 4 * 64;
+    return step > update ? step : update;
+}
 static_assert(arn_lds_elems(BEM_MAX_RESTART) * sizeof(double2) <= 160 * 1024,
               "a step block of the longest restart fits the 160 KiB of LDS a gfx950 workgroup can hold");
 
@@ -360,15 +403,16 @@ __device__ __forceinline__ void dc_step(int r, int nr, int j, int m, int ns, con
 {
     // S, T and the column being completed stay in LDS for the whole step; the
     // inputs of earlier steps (column j - 1 as produced, the rotations, the
-    // rotated right-hand side) are loaded first, alongside the partial sums
+    // rotated right-hand side, the counters) are loaded first, alongside the
+    // partial sums
     const size_t L = (size_t)m + 1;
     double2* col = lds;
     double2* lc = lds + L;
     double2* ls = lds + 2 * L;
     double2* Sl = lds + 3 * L;
     double2* Tl = lds + 4 * L;
-    double2(*zp)[64] = reinterpret_cast<double2(*)[64]>(lds + 5 * L);
-    double* red = reinterpret_cast<double*>(lds + 5 * L + 4 * 64);
+    double2* zp = lds + 5 * L;
+    double* red = reinterpret_cast<double*>(lds + 5 * L + arn_zp_elems(m));
     int* still_p = reinterpret_cast<int*>(red + 16);
     int& still_s = *still_p;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -377,35 +421,25 @@ __device__ __forceinline__ void dc_step(int r, int nr, int j, int m, int ns, con
         if (flags_out && tid == 0) flags_out[r] = 0;
         return;
     }
-    const int jc = j + 1;
+    const int jc = j + 1, c0 = j - 1;
     const bool hasw = partQ != nullptr;
     double2* Hc = Hraw + (size_t)r * (m + 1) * m + (size_t)(j >= 1 ? j - 1 : 0) * (m + 1);
+    const double beta = j >= 1 ? hnorm[r] : 1.0;
+    double2 gj = make_double2(0.0, 0.0);
+    double threshold = 0.0;
+    int it = 0;
     if (j >= 1) {
         for (int i = tid; i < j; i += DC_STEP_BS) col[i] = Hc[i];
-        for (int i = tid; i < j - 1; i += DC_STEP_BS) {
+        for (int i = tid; i < c0; i += DC_STEP_BS) {
             lc[i] = cs[(size_t)r * m + i];
             ls[i] = sn[(size_t)r * m + i];
         }
+        gj = gvec[(size_t)r * (m + 1) + c0];
+        threshold = thr[r];
+        it = iters[r] + 1;
     }
-    for (int i = tid; i < jc; i += DC_STEP_BS) {
-        double pr = 0.0, pi = 0.0, qr = 0.0, qi = 0.0;
-#pragma unroll 8
-        for (int b = 0; b < ns; ++b) {
-            const size_t o = ((size_t)r * ns + b) * jc + i;
-            const double2 p = partP[o];
-            pr += p.x;
-            pi += p.y;
-            if (hasw) {
-                const double2 t = partQ[o];
-                qr += t.x;
-                qi += t.y;
-            }
-        }
-        Sl[i] = make_double2(pr, pi);
-        if (hasw) Tl[i] = make_double2(qr, qi);
-    }
+    sum_partials<DC_STEP_BS>(r, ns, jc, partP, partQ, Sl, Tl);
     __syncthreads();
-    const double beta = j >= 1 ? hnorm[r] : 1.0;
     const bool brk = !(beta > 0.0);  // previous step ended the Krylov space
     double ss = 0.0, str = 0.0, sti = 0.0;
     for (int i = tid; i < j; i += DC_STEP_BS) {
@@ -420,6 +454,15 @@ __device__ __forceinline__ void dc_step(int r, int nr, int j, int m, int ns, con
     block_sum4x3(ss, str, sti, red);
     const double alpha = Sl[j].x;
     const double gamma = brk ? 0.0 : sqrt(fmax(alpha - ss, 0.0));
+    // column j needs z_i = sum_l H[i, l] s_l over the Hessenberg band l >= i - 1
+    // (below it the array is not written)
+    const double2* Hr = Hraw + (size_t)r * (m + 1) * m;
+    auto band = [&](int i, int l) {
+        return i <= l + 1 ? Hr[(size_t)l * (m + 1) + i] : make_double2(0.0, 0.0);
+    };
+    // Beside the rotations, which are one thread's chain, the other waves form
+    // z of the first ARN_ZROWS rows: wave w takes the columns l = w - 1 (mod 3)
+    const bool beside = hasw && j >= 1 && gamma > 0.0 && m <= ARN_ZMAX;
     int still = 1;
     if (j >= 1) {
         // complete column j - 1
@@ -440,52 +483,76 @@ __device__ __forceinline__ void dc_step(int r, int nr, int j, int m, int ns, con
         }
         __syncthreads();
         if (tid == 0) {
-            const int c0 = j - 1;
             // the previous rotations in order; the running entry stays in
-            // registers, so only the loads (independent of the chain) touch LDS
+            // registers, so only the loads (independent of the chain) touch
+            // LDS.  The cosines are real.
             double2 hi = col[0];
 #pragma unroll 4
             for (int i = 0; i < c0; ++i) {
                 const double2 hn = col[i + 1];
-                const double2 ci = lc[i], si = ls[i];
-                col[i] = make_double2(ci.x * hi.x - ci.y * hi.y + si.x * hn.x - si.y * hn.y,
-                                      ci.x * hi.y + ci.y * hi.x + si.x * hn.y + si.y * hn.x);
-                hi = make_double2(-(si.x * hi.x + si.y * hi.y) + (ci.x * hn.x + ci.y * hn.y),
-                                  -(si.x * hi.y - si.y * hi.x) + (ci.x * hn.y - ci.y * hn.x));
+                const double ci = lc[i].x;
+                const double2 si = ls[i];
+                col[i] = make_double2(fma(ci, hi.x, fma(si.x, hn.x, -si.y * hn.y)),
+                                      fma(ci, hi.y, fma(si.x, hn.y, si.y * hn.x)));
+                hi = make_double2(fma(-si.x, hi.x, fma(-si.y, hi.y, ci * hn.x)),
+                                  fma(-si.x, hi.y, fma(si.y, hi.x, ci * hn.y)));
             }
-            col[c0] = hi;
-            const double2 a = col[c0], b = col[c0 + 1];
-            const double na = hypot(a.x, a.y), nb = hypot(b.x, b.y);
+            const double2 a = hi;
+            const double nb = col[j].x;  // beta gamma >= 0
+            const double na = hypot(a.x, a.y);
             const double rho = hypot(na, nb);
-            double2 cj, sj;
+            double cj;
+            double2 sj;
             if (rho == 0.0) {
-                cj = make_double2(1.0, 0.0);
+                cj = 1.0;
                 sj = make_double2(0.0, 0.0);
             } else if (na == 0.0) {
-                cj = make_double2(0.0, 0.0);
-                sj = make_double2(b.x / nb, -b.y / nb);
+                cj = 0.0;
+                sj = make_double2(1.0, 0.0);
             } else {
-                cj = make_double2(na / rho, 0.0);
-                const double ux = a.x / na, uy = a.y / na;
-                sj = make_double2((ux * b.x + uy * b.y) / rho, (uy * b.x - ux * b.y) / rho);
+                cj = na / rho;
+                const double f = nb / rho;
+                sj = make_double2(a.x / na * f, a.y / na * f);
             }
-            cs[(size_t)r * m + c0] = cj;
-            sn[(size_t)r * m + c0] = sj;
-            col[c0] = make_double2(cj.x * a.x + sj.x * b.x - sj.y * b.y, cj.x * a.y + sj.x * b.y + sj.y * b.x);
-            col[c0 + 1] = make_double2(0.0, 0.0);
-            double2* gv = gvec + (size_t)r * (m + 1);
-            const double2 gj = gv[c0];
+            // the rotated right-hand side: |gn| = |s| |gj|
             const double2 gn = make_double2(-(sj.x * gj.x + sj.y * gj.y), -(sj.x * gj.y - sj.y * gj.x));
-            gv[c0 + 1] = gn;
-            gv[c0] = make_double2(cj.x * gj.x, cj.x * gj.y);
             const double res = hypot(gn.x, gn.y);
-            const int it = iters[r] + 1;
+            // stop on convergence, a spent budget, the end of the Krylov space or a non-finite value
+            still = (res > threshold) && it < maxit && (gamma > 0.0) && !brk;
+            still_s = still;
+            if (!still) active[r] = stop_mark;
+            cs[(size_t)r * m + c0] = make_double2(cj, 0.0);
+            sn[(size_t)r * m + c0] = sj;
+            col[c0] = make_double2(fma(cj, a.x, sj.x * nb), fma(cj, a.y, sj.y * nb));
+            col[j] = make_double2(0.0, 0.0);
+            double2* gv = gvec + (size_t)r * (m + 1);
+            gv[j] = gn;
+            gv[c0] = make_double2(cj * gj.x, cj * gj.y);
             iters[r] = it;
             kdim[r] = j;
-            // stop on convergence, a spent budget, the end of the Krylov space or a non-finite value
-            still = (res > thr[r]) && it < maxit && (gamma > 0.0) && !brk;
-            if (!still) active[r] = stop_mark;
-            still_s = still;
+        } else if (beside && wv > 0) {
+            double2 z0 = make_double2(0.0, 0.0), z1 = z0;
+            const int i1 = 64 + lane;
+            auto add = [](double2& z, double2 h, double2 a) {
+                z.x += h.x * a.x - h.y * a.y;
+                z.y += h.x * a.y + h.y * a.x;
+            };
+            int l = wv - 1;
+            if (jc <= 64) {
+#pragma unroll 8
+                for (; l < j; l += 3) add(z0, band(lane, l), Sl[l]);
+            } else {
+#pragma unroll 8
+                for (; l < 63; l += 3) add(z0, band(lane, l), Sl[l]);
+#pragma unroll 4
+                for (; l < j; l += 3) {
+                    const double2 a = Sl[l];
+                    add(z0, band(lane, l), a);
+                    add(z1, band(i1, l), a);
+                }
+            }
+            zp[(wv - 1) * ARN_ZROWS + lane] = z0;
+            zp[(wv - 1) * ARN_ZROWS + i1] = z1;
         }
         __syncthreads();
         still = still_s;
@@ -502,12 +569,23 @@ __device__ __forceinline__ void dc_step(int r, int nr, int j, int m, int ns, con
     const double2 tau = Tl[j];
     const double ig = 1.0 / gamma;
     const double2 c = make_double2((tau.x - str) * ig, (tau.y - sti) * ig);
-    const double2* Hr = Hraw + (size_t)r * (m + 1) * m;
     double2* Hj = Hraw + (size_t)r * (m + 1) * m + (size_t)j * (m + 1);
-    // z_i = sum_l H[i, l] s_l over the Hessenberg band l >= i - 1, rows in
-    // chunks of 64; wave w takes the columns l = w (mod 4), the four partial
-    // sums are added in wave order
-    for (int i0 = 0; i0 < jc; i0 += 64) {
+    auto put = [&](int i, double zx, double zy) {
+        const double2 base = i < j ? Tl[i] : c;
+        Hj[i] = make_double2((base.x - zx) * ig, (base.y - zy) * ig);
+    };
+    int i0 = 0;
+    if (beside) {
+        if (tid < min(jc, ARN_ZROWS)) {
+            const double2 a = zp[tid], b = zp[ARN_ZROWS + tid], d = zp[2 * ARN_ZROWS + tid];
+            put(tid, (a.x + b.x) + d.x, (a.y + b.y) + d.y);
+        }
+        i0 = ARN_ZROWS;
+        if (i0 < jc) __syncthreads();  // zp is used again
+    }
+    // the other rows in chunks of 64; wave w takes the columns l = w (mod 4),
+    // the four partial sums are added in wave order
+    for (; i0 < jc; i0 += 64) {
         const int i = i0 + lane;
         double zr = 0.0, zi = 0.0;
         if (i < jc) {
@@ -521,14 +599,11 @@ __device__ __forceinline__ void dc_step(int r, int nr, int j, int m, int ns, con
                 zi += h.x * a.y + h.y * a.x;
             }
         }
-        zp[wv][lane] = make_double2(zr, zi);
+        zp[wv * 64 + lane] = make_double2(zr, zi);
         __syncthreads();
-        if (wv == 0 && i < jc) {
-            const double zx = ((zp[0][lane].x + zp[1][lane].x) + zp[2][lane].x) + zp[3][lane].x;
-            const double zy = ((zp[0][lane].y + zp[1][lane].y) + zp[2][lane].y) + zp[3][lane].y;
-            const double2 base = i < j ? Tl[i] : c;
-            Hj[i] = make_double2((base.x - zx) * ig, (base.y - zy) * ig);
-        }
+        if (wv == 0 && i < jc)
+            put(i, ((zp[lane].x + zp[64 + lane].x) + zp[128 + lane].x) + zp[192 + lane].x,
+                ((zp[lane].y + zp[64 + lane].y) + zp[128 + lane].y) + zp[192 + lane].y);
         __syncthreads();
     }
 }
@@ -538,9 +613,13 @@ __device__ __forceinline__ void dc_step(int r, int nr, int j, int m, int ns, con
 // |w|^2 of each block.  Every block forms S, T, gamma and c itself from the
 // projection partials, with the step block's sums in the step block's order,
 // so the step's Hessenberg work runs beside the update instead of before it.
+//
+// shared: a block takes 64 rows and its four waves every fourth basis vector,
+// four loads in flight each, their sums added through LDS in wave order;
+// otherwise 256 rows, one per thread, which walks the whole basis.
 template <class TV>
-__device__ __forceinline__ void dc_update(int r, int bx, int nu, TV* __restrict__ V, size_t ldv, int nr, int j, int m,
-                                          int ns, const double2* __restrict__ partP,
+__device__ __forceinline__ void dc_update(int r, int bx, int nu, bool shared, TV* __restrict__ V, size_t ldv, int nr,
+                                          int j, int m, int ns, const double2* __restrict__ partP,
                                           const double2* __restrict__ partQ, const double* __restrict__ hnorm,
                                           double2* __restrict__ W, size_t ldw, int n, double* __restrict__ norm_out,
                                           const int* __restrict__ active, TV* __restrict__ xt, int xw,
@@ -551,25 +630,11 @@ __device__ __forceinline__ void dc_update(int r, int bx, int nu, TV* __restrict_
     double2* sl = lds;
     double2* tl = lds + L;
     double* red = reinterpret_cast<double*>(lds + 2 * L);
-    const int jc = j + 1, tid = threadIdx.x;
-    for (int i = tid; i < jc; i += BS) {
-        double pr = 0.0, pi = 0.0, qr = 0.0, qi = 0.0;
-#pragma unroll 8
-        for (int b = 0; b < ns; ++b) {
-            const size_t o = ((size_t)r * ns + b) * jc + i;
-            const double2 p = partP[o];
-            pr += p.x;
-            pi += p.y;
-            const double2 t = partQ[o];
-            qr += t.x;
-            qi += t.y;
-        }
-        sl[i] = make_double2(pr, pi);
-        tl[i] = make_double2(qr, qi);
-    }
+    const int jc = j + 1, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    sum_partials<BS>(r, ns, jc, partP, partQ, sl, tl);
     const double beta = j >= 1 ? hnorm[r] : 1.0;
     // this thread's candidate rows, loaded while the coefficients are formed
-    const int q = bx * BS + threadIdx.x;
+    const int q = shared ? bx * 64 + lane : bx * BS + tid;
     TV* vj = V + ((size_t)j * nr + r) * ldv;
     double2 v = make_double2(0.0, 0.0), w = make_double2(0.0, 0.0);
     if (q < n) {
@@ -592,15 +657,16 @@ __device__ __forceinline__ void dc_update(int r, int bx, int nu, TV* __restrict_
     const double2 tau = tl[j];
     const double2 c = make_double2((tau.x - str) * ig, (tau.y - sti) * ig);
     double nn[1] = {0.0};
-    if (q < n) {
-        for (int i = 0; i < j; ++i) {
-            const double2 b = ld2(V + ((size_t)i * nr + r) * ldv + q);
-            const double2 a = sl[i], t = tl[i];
-            v.x -= a.x * b.x - a.y * b.y;
-            v.y -= a.x * b.y + a.y * b.x;
-            w.x -= t.x * b.x - t.y * b.y;
-            w.y -= t.x * b.y + t.y * b.x;
-        }
+    const TV* vb = V + (size_t)r * ldv + min(q, n - 1);
+    const size_t vs = (size_t)nr * ldv;
+    auto add = [&](double2& x, double2& y, int i, double2 b) {
+        const double2 a = sl[i], t = tl[i];
+        x.x -= a.x * b.x - a.y * b.y;
+        x.y -= a.x * b.y + a.y * b.x;
+        y.x -= t.x * b.x - t.y * b.y;
+        y.y -= t.x * b.y + t.y * b.x;
+    };
+    auto finish = [&]() {
         v = make_double2(v.x * ig, v.y * ig);
         const double2 vc = cmul2(v, c);
         w = make_double2((w.x - vc.x) * ig, (w.y - vc.y) * ig);
@@ -608,9 +674,43 @@ __device__ __forceinline__ void dc_update(int r, int bx, int nu, TV* __restrict_
         W[(size_t)r * ldw + q] = w;
         if (xt) st2(xt + (size_t)q * xw + r, w);  // the next product's input (its reduction divides by |w|)
         nn[0] = fma(w.x, w.x, w.y * w.y);
+    };
+    if (shared) {
+        constexpr int U = 4;
+        double2(*part)[4][64] = reinterpret_cast<double2(*)[4][64]>(lds + 2 * L + 16);
+        double2 x = make_double2(0.0, 0.0), y = x;
+        int i = wave;
+        for (; i + 4 * (U - 1) < j; i += 4 * U) {
+            double2 b[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) b[u] = ld2(vb + (size_t)(i + 4 * u) * vs);
+#pragma unroll
+            for (int u = 0; u < U; ++u) add(x, y, i + 4 * u, b[u]);
+        }
+        for (; i < j; i += 4) add(x, y, i, ld2(vb + (size_t)i * vs));
+        part[0][wave][lane] = x;
+        part[1][wave][lane] = y;
+        __syncthreads();
+        if (wave != 0) return;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double2 p = part[0][k][lane], t = part[1][k][lane];
+            v.x += p.x;
+            v.y += p.y;
+            w.x += t.x;
+            w.y += t.y;
+        }
+        if (q < n) finish();
+        const double sum = wave_sum(nn[0]);
+        if (lane == 0) norm_out[r * nu + bx] = sum;
+        return;
+    }
+    if (q < n) {
+        for (int i = 0; i < j; ++i) add(v, w, i, ld2(vb + (size_t)i * vs));
+        finish();
     }
     block_sum<1>(nn, red + 12);
-    if (threadIdx.x == 0) norm_out[r * nu + bx] = nn[0];
+    if (tid == 0) norm_out[r * nu + bx] = nn[0];
 }
 
 // beta = |w| from the update partials (every block sums them in the same
@@ -821,6 +921,7 @@ struct ArnProb {
     void* xt;
     int nr, n, maxit, xw;
     int ns, rcp, nu;  // projection row chunks, padded (right-hand side, chunk) pairs, update blocks
+    bool shared;      // update blocks whose waves share the basis
     int b0[4];        // first block of this problem in the projection, step, update and next launches
 };
 // NP: capacity of the set.  A lone problem launches with NP = 1, whose
@@ -869,7 +970,7 @@ __global__ __launch_bounds__(BS) void k_dc_update(const ArnSet<NP> S, int j, int
         return;
     }
     const int u = b - P.nr;
-    dc_update<TV>(u / P.nu, u % P.nu, P.nu, static_cast<TV*>(P.V), P.ldv, P.nr, j, m, P.ns, P.partP, P.partQ,
+    dc_update<TV>(u / P.nu, u % P.nu, P.nu, P.shared, static_cast<TV*>(P.V), P.ldv, P.nr, j, m, P.ns, P.partP, P.partQ,
                   P.hnorm, P.W, P.ldw, P.n, P.norm_part, P.active, static_cast<TV*>(P.xt), P.xw, arn_lds);
 }
 
@@ -878,7 +979,8 @@ __global__ __launch_bounds__(BS) void k_dc_next(const ArnSet<NP> S, int jc)
 {
     const ArnProb& P = S.p[set_problem(S, 3, blockIdx.x)];
     const int b = (int)blockIdx.x - P.b0[3];
-    dc_next<TV>(b / P.nu, b % P.nu, P.W, P.ldw, P.n, P.norm_part, P.nu,
+    const int nb = (P.n + BS - 1) / BS;
+    dc_next<TV>(b / nb, b % nb, P.W, P.ldw, P.n, P.norm_part, P.nu,
                 static_cast<TV*>(P.V) + (size_t)jc * P.nr * P.ldv, P.ldv, P.hnorm, P.active, P.nr,
                 static_cast<TV*>(P.xt), P.xw);
 }
@@ -928,7 +1030,11 @@ DotCfg dot_cfg()
     return c;
 }
 
-int update_blocks(int n) { return (n + BS - 1) / BS; }
+// Update blocks whose waves share the basis: where blocks of 256 rows would
+// leave the chip's 1024 SIMDs fewer than two waves each.
+bool update_shared(int n, int nr) { return (long long)((n + BS - 1) / BS) * nr < 512; }
+
+int update_blocks(int n, int nr) { return update_shared(n, nr) ? (n + 63) / 64 : (n + BS - 1) / BS; }
 
 int arnoldi_blocks(int n) { return std::max((n + BS - 1) / BS, (n + dot_cfg().rows - 1) / dot_cfg().rows); }
 
@@ -1002,13 +1108,14 @@ hipError_t launch_arnoldi_t(const ArnoldiArgs* a, int np, int j, hipStream_t s)
         P.xw = A.xw;
         P.ns = (A.n + dc.rows - 1) / dc.rows;  // row chunks of the projection kernel
         P.rcp = (A.nr * P.ns + 7) / 8 * 8;
-        P.nu = update_blocks(A.n);              // blocks of the update kernel
+        P.shared = update_shared(A.n, A.nr);
+        P.nu = update_blocks(A.n, A.nr);        // blocks of the update kernel
         // projection, (unused), step + update, normalisation blocks; the
         // normalisation of a problem with packed product inputs runs only at
         // the last step (before the projection)
         const bool packed = A.xt != nullptr;
         const int counts[4] = {P.rcp * ((jc + dc.batch - 1) / dc.batch), 0, A.nr + (j == m ? 0 : P.nu * A.nr),
-                               (j == m) == packed ? P.nu * A.nr : 0};
+                               (j == m) == packed ? (A.n + BS - 1) / BS * A.nr : 0};
         for (int q = 0; q < 4; ++q) {
             P.b0[q] = nb[q];
             nb[q] += counts[q];
