@@ -920,7 +920,7 @@ struct ArnProb {
     int *iters, *kdim, *active, *flags_out;
     void* xt;
     int nr, n, maxit, xw;
-    int ns, rcp, nu;  // projection row chunks, padded (right-hand side, chunk) pairs, update blocks
+    int rpt, ns, rcp, nu;  // projection rows per thread, row chunks, padded (right-hand side, chunk) pairs, update blocks
     bool shared;      // update blocks whose waves share the basis
     int b0[4];        // first block of this problem in the projection, step, update and next launches
 };
@@ -947,11 +947,11 @@ __device__ __forceinline__ int set_problem(const ArnSet<NP>& S, int k, int b)
 }
 
 template <int BATCH, bool HASW, class TV, int NP>
-__global__ __launch_bounds__(BS) void k_dc_dots(const ArnSet<NP> S, int jc, int rpt)
+__global__ __launch_bounds__(BS) void k_dc_dots(const ArnSet<NP> S, int jc)
 {
     const ArnProb& P = S.p[set_problem(S, 0, blockIdx.x)];
     dc_dots<BATCH, HASW, TV>((int)blockIdx.x - P.b0[0], static_cast<const TV*>(P.V), P.ldv, P.nr, jc, P.W, P.ldw, P.n,
-                             rpt, P.ns, P.rcp, P.partP, HASW ? P.partQ : nullptr, P.active);
+                             P.rpt, P.ns, P.rcp, P.partP, HASW ? P.partQ : nullptr, P.active);
 }
 
 // Step blocks first (one per right-hand side: the Hessenberg column, the
@@ -1009,6 +1009,12 @@ hipError_t launch_col_norms(const double2* X, size_t ldx, int n, int nr, double*
     return hipGetLastError();
 }
 
+// Update blocks whose waves share the basis: where blocks of 256 rows would
+// leave the chip's 1024 SIMDs fewer than two waves each.
+bool update_shared(int n, int nr) { return (long long)((n + BS - 1) / BS) * nr < 512; }
+
+int update_blocks(int n, int nr) { return update_shared(n, nr) ? (n + 63) / 64 : (n + BS - 1) / BS; }
+
 // Shape of the projection kernel: rows per block (a multiple of BS) and basis
 // vectors per block (4, 8 or 16); BEM_DOT_CFG="rows,batch" overrides it
 // (tuning).  Measured on gfx950: 2048 rows of 4 vectors against 512 rows
@@ -1019,9 +1025,12 @@ struct DotCfg {
     int rows, batch;
 };
 
-DotCfg dot_cfg()
+// Systems whose update blocks share the basis (few rows in all) take 1024 rows:
+// more blocks, shorter chains; the mixed request (n = 2674, 11 right-hand sides)
+// 12.08 -> 11.6 ms (512 rows 11.8), kite4096 keeps 2048 (31.76 against 31.80 ms).
+DotCfg dot_cfg(int n, int nr)
 {
-    DotCfg c{2048, 4};
+    DotCfg c{update_shared(n, nr) ? 1024 : 2048, 4};
     if (const char* e = getenv("BEM_DOT_CFG")) {
         int a = 0, b = 0;
         if (sscanf(e, "%d,%d", &a, &b) == 2 && a >= BS && a <= 16384 && a % BS == 0 && (b == 4 || b == 8 || b == 16))
@@ -1030,26 +1039,19 @@ DotCfg dot_cfg()
     return c;
 }
 
-// Update blocks whose waves share the basis: where blocks of 256 rows would
-// leave the chip's 1024 SIMDs fewer than two waves each.
-bool update_shared(int n, int nr) { return (long long)((n + BS - 1) / BS) * nr < 512; }
-
-int update_blocks(int n, int nr) { return update_shared(n, nr) ? (n + 63) / 64 : (n + BS - 1) / BS; }
-
-int arnoldi_blocks(int n) { return std::max((n + BS - 1) / BS, (n + dot_cfg().rows - 1) / dot_cfg().rows); }
+int arnoldi_blocks(int n) { return (n + BS - 1) / BS; }  // a chunk has at least BS rows
 
 namespace {
 
 template <bool HASW, class TV, int NP>
 void launch_dc_dots(const DotCfg& c, const ArnSet<NP>& S, int nblocks, int jc, hipStream_t s)
 {
-    const int rpt = c.rows / BS;
     if (c.batch == 4)
-        hipLaunchKernelGGL((k_dc_dots<4, HASW, TV, NP>), dim3(nblocks), dim3(BS), 0, s, S, jc, rpt);
+        hipLaunchKernelGGL((k_dc_dots<4, HASW, TV, NP>), dim3(nblocks), dim3(BS), 0, s, S, jc);
     else if (c.batch == 16)
-        hipLaunchKernelGGL((k_dc_dots<16, HASW, TV, NP>), dim3(nblocks), dim3(BS), 0, s, S, jc, rpt);
+        hipLaunchKernelGGL((k_dc_dots<16, HASW, TV, NP>), dim3(nblocks), dim3(BS), 0, s, S, jc);
     else
-        hipLaunchKernelGGL((k_dc_dots<8, HASW, TV, NP>), dim3(nblocks), dim3(BS), 0, s, S, jc, rpt);
+        hipLaunchKernelGGL((k_dc_dots<8, HASW, TV, NP>), dim3(nblocks), dim3(BS), 0, s, S, jc);
 }
 
 template <class TV, int NP>
@@ -1074,7 +1076,7 @@ hipError_t launch_arnoldi_kernels(const DotCfg& dc, const ArnSet<NP>& S, const i
 template <class TV>
 hipError_t launch_arnoldi_t(const ArnoldiArgs* a, int np, int j, hipStream_t s)
 {
-    const DotCfg dc = dot_cfg();
+    DotCfg dc{};  // the batch is the same for all problems
     const int m = a[0].m;
     const int jc = j + 1;
     ArnSet<MAX_FUSED> S{};
@@ -1106,6 +1108,8 @@ hipError_t launch_arnoldi_t(const ArnoldiArgs* a, int np, int j, hipStream_t s)
         P.n = A.n;
         P.maxit = A.maxit;
         P.xw = A.xw;
+        dc = dot_cfg(A.n, A.nr);
+        P.rpt = dc.rows / BS;
         P.ns = (A.n + dc.rows - 1) / dc.rows;  // row chunks of the projection kernel
         P.rcp = (A.nr * P.ns + 7) / 8 * 8;
         P.shared = update_shared(A.n, A.nr);
