@@ -735,20 +735,52 @@ __global__ void k_pack_xt(const TX* __restrict__ X, size_t ldx, int n, int nr, i
     XT[(size_t)c * xw + r] = v;
 }
 
+// Column splits of the product over one group of 16 right-hand sides, with rows
+// split into blocks of 128.  `room` blocks run at once: 256, one per CU, with
+// FP64 sums (its registers leave one wave per SIMD), 512 with FP32 sums.  More
+// blocks than that go in another turn, which costs as much as a full one, and
+// each split writes and re-reads its partial sums: the fewest splits that fill
+// the turns they take to 4/5.
+int group_splits(int n, int room)
+{
+    const int rowblocks = (n + 127) / 128, most = std::max(1, std::min(64, n / 64));
+    int best = 1;
+    double fill = 0;
+    for (int s = 1; s <= most && fill < 0.8; ++s) {
+        const int blocks = rowblocks * s, turns = (blocks + room - 1) / room;
+        const double f = (double)blocks / ((double)turns * room);
+        if (f > fill) {
+            fill = f;
+            best = s;
+        }
+    }
+    return best;
+}
+
 // Launch shape of the matrix-core product: row tiles per wave, column steps
-// in flight, column splits (0: enough for about 1024 blocks), 3-product form,
-// for one group of 16 right-hand sides and for 2-4 groups per pass.
+// in flight, column splits, 3-product form, for one group of 16 right-hand
+// sides and for 2-4 groups per pass.
+//
+// One group (bem_matvec, 16 right-hand sides, us; 8 column steps in flight and
+// 8 splits at every size / 8 steps with FP64 sums, 4 with FP32, and
+// group_splits): FP64 n 4400 88.6 / 65.3, 5400 115 / 88.2, 8192 189 / 172,
+// 10000 308 / 263, 12000 393 / 385, 16384 703 / 655; FP32 n 6800 90.2 / 86.7,
+// 8192 106 / 104, 10000 188 / 160, 12000 232 / 220, 16384 402 / 391.
+//
+// 2-4 groups: measured at n = 32768 with 32 and 64 right-hand sides; FP64 sums
+// over 3-4 groups take one row tile, which runs two waves per SIMD (the mixed
+// path's 64-RHS refinement residual 7.73 -> 6.29 ms); splits for about 1024
+// blocks.
 MvShape mfma_default(int n, int ng, bool f64)
 {
-    // defaults measured on gfx950 (n = 32768; 16, 32 and 64 right-hand sides;
-    // FP64 sums over 3-4 groups take one row tile, which runs two waves per
-    // SIMD: the mixed path's 64-RHS refinement residual 7.73 -> 6.29 ms)
-    MvShape c = ng == 1 ? MvShape{2, 8, 8, 1} : (f64 && ng == 2 ? MvShape{1, 4, 8, 1} : MvShape{f64 ? 1 : 2, 4, 0, 1});
-    if (c.splits == 0) {
+    MvShape c{f64 ? 1 : 2, 4, 0, 1};
+    if (ng == 1) {
+        c = f64 ? MvShape{2, 8, group_splits(n, 256), 1} : MvShape{2, 4, group_splits(n, 512), 1};
+    } else if (f64 && ng == 2) {
+        c.splits = 8;
+    } else {
         const int rowblocks = (n + 16 * c.rt * MV_WAVES - 1) / (16 * c.rt * MV_WAVES);
-        int s = (1024 + rowblocks - 1) / rowblocks;
-        s = std::min(s, std::max(1, n / 256));
-        c.splits = std::max(1, std::min(s, 64));
+        c.splits = std::min({(1024 + rowblocks - 1) / rowblocks, std::max(1, n / 256), 64});
     }
     c.splits = std::max(1, std::min(c.splits, std::max(1, n / 64)));
     return c;
@@ -826,7 +858,7 @@ int split_cap(int n, int ng)
 {
     if (ng == 0) return matvec_splits_valu(n);
     const int want = (131072 + n - 1) / std::max(1, n);  // about 2048 blocks at one row tile per wave
-    const int cap = std::max(1, std::min({want, 64, std::max(1, n / 64)}));
+    const int cap = std::max(1, std::min({std::max(want, 8), 64, std::max(1, n / 64)}));
     return std::max(cap, std::max(mfma_default(n, ng, true).splits, mfma_default(n, ng, false).splits));
 }
 

@@ -1,0 +1,35 @@
+"""Products of 5-16 right-hand sides above the row-block sizes: column splits by
+the number of row blocks (128 rows each) and of blocks that run at once.
+
+Sizes just above the row-block limits (FP64 n 4096, FP32 5792), a full turn of
+64 row blocks and the one beyond it, two turns; ragged last row block and last
+split.  Against the FP64 product of the same matrix; bound per entry: 4 sqrt(n)
+u (|A| |X|), u = 2^-53 or 2^-24 (a sum of n products rounds like a random walk;
+the complex product adds a few roundings).
+"""
+import pytest
+
+import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N", [2049, 2753, 2901, 4096, 4097, 5999])
+def test_products_split_by_row_blocks(N):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2312_12787_amd as P
+    P.tune_reset()
+    g = P.Problem(W.disk(N, 2.0, 3.0 + 0.1j))
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    for prec, dt, u in ((P.F64, torch.complex128, 2.0 ** -53), (P.F32, torch.complex64, 2.0 ** -24)):
+        A = g.assemble(prec)[:, :g.n]
+        wide = A.to(torch.complex128)
+        size = A.abs().double()
+        for nrhs in (5, 16):
+            X = torch.view_as_complex(torch.randn(nrhs, g.n, 2, generator=gen, device="cuda", dtype=torch.float64)).to(dt)
+            err = (g.matvec(X).to(torch.complex128) - X.to(torch.complex128) @ wide).abs()
+            bound = 4 * g.n ** 0.5 * u * (X.abs().double() @ size)
+            worst = float((err / bound).max())
+            assert worst < 1, (N, nrhs, dt, worst)
