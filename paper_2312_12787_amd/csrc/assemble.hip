@@ -360,7 +360,7 @@ __device__ __forceinline__ BlockConst block_const(const DomConst& Dm, int sg)
 }
 
 // Waves per SIMD that the far and near kernels leave room for.
-constexpr int FAR_WAVES = 3, NEAR_WAVES = 2;
+constexpr int FAR_WAVES = 3, NEAR_WAVES = 2, ALL_WAVES = 3;
 
 // Entries of the u and w columns from the sums (tt = t_i.t_j, tn = t_i.n_j;
 // in the plane n_i.n_j = tt and n_i.t_j = -tn).
@@ -421,7 +421,7 @@ template <class T2>
 struct AsmArgs {
     const char* g;
     GeomLayout L;
-    int N, n_if, q, side;
+    int N, n_if, q;
     T2* A;
     float2* A32;  // FP32 copy of an FP64 matrix, or null
     size_t lda;
@@ -442,28 +442,27 @@ struct AsmArgs {
 // assembly, against point-by-point sums: kite of 4096 elements, one lossy
 // wavenumber, 2019 -> 645 us; 8192 elements in FP32 3280 -> 1106 us, the
 // entries' error against 32-digit values 2 to 5 times smaller; 777 elements at
-// k h = 0.8 288 -> 68 us; three sectors, 1900 elements, 1005 -> 185 us.
+// k h = 0.8 288 -> 68 us (50 in the single launch below); three sectors,
+// 1900 elements, 1005 -> 185 us (154).
 // Entries in FP64 are as close to 32-digit values as before (the phase k r,
 // once averaged over q points, is formed from a compensated distance).
 // ---------------------------------------------------------------------------
 template <bool CPLX, bool BM, class T2>
-__global__ __launch_bounds__(ROW_TILE, FAR_WAVES) void k_assemble_far(const AsmArgs<T2> P, const int* __restrict__ tiles,
-                                                                      int per)
+__device__ __forceinline__ void far_part(const AsmArgs<T2>& P, int side, int tile, int li, int col_part, int per)
 {
     constexpr bool LOW = sizeof(T2) == sizeof(float2);
     constexpr int BASE = LOW ? 4 : 8;
-    const Tile rt = tab<Tile>(P.g, P.L.rtiles)[tiles[blockIdx.x]];
+    const Tile rt = tab<Tile>(P.g, P.L.rtiles)[tile];
     const int parts = COL_CHUNK / per;
-    const Tile cc = tab<Tile>(P.g, P.L.cchunks)[blockIdx.y / parts];
-    const int j0 = (int)(blockIdx.y % parts) * per;
+    const Tile cc = tab<Tile>(P.g, P.L.cchunks)[col_part / parts];
+    const int j0 = col_part % parts * per;
     const int j1 = min(j0 + per, cc.count);
-    const int li = threadIdx.x;
     if (li >= rt.count || j0 >= j1) return;
     const IfacePlan F = tab<IfacePlan>(P.g, P.L.iface)[rt.iface];
-    const int d = P.side ? F.dr : F.dl;
+    const int d = side ? F.dr : F.dl;
     const int sg = tab<int>(P.g, P.L.sigma)[d * P.n_if + cc.iface];
     const int i = rt.start + li;
-    const size_t row = (size_t)((P.side ? F.row_r : F.row_l) + (i - F.off));
+    const size_t row = (size_t)((side ? F.row_r : F.row_l) + (i - F.off));
     if (sg == 0) {  // this domain does not touch the interface
         for (int jj = j0; jj < j1; ++jj) store_entry(P.A, P.lda, P.A32, row, cc.start + jj, P.N, {0.0, 0.0}, {0.0, 0.0});
         return;
@@ -504,6 +503,12 @@ __global__ __launch_bounds__(ROW_TILE, FAR_WAVES) void k_assemble_far(const AsmA
         store_entry(P.A, P.lda, P.A32, row, j, P.N, au, aw);
     }
 }
+template <bool CPLX, bool BM, class T2>
+__global__ __launch_bounds__(ROW_TILE, FAR_WAVES) void k_assemble_far(const AsmArgs<T2> P, int side,
+                                                                      const int* __restrict__ tiles, int per)
+{
+    far_part<CPLX, BM>(P, side, tiles[blockIdx.x], threadIdx.x, blockIdx.y, per);
+}
 
 // ---------------------------------------------------------------------------
 // Near launch: the elements the far launch leaves, over the host's list of
@@ -520,29 +525,34 @@ __global__ __launch_bounds__(ROW_TILE, FAR_WAVES) void k_assemble_far(const AsmA
 // evaluated point by point by all lanes, 30 us with one close pair per lane,
 // 15 us with one point per lane; kite of 4096 elements 296 -> 121 us.
 // ---------------------------------------------------------------------------
+struct NearLds {
+    unsigned char todo[64 * NEAR_PART];
+    double part[8][64];
+};
+static_assert(64 * NEAR_PART <= 256, "a list entry is one byte");
+
 template <bool CPLX, bool BM, class T2>
-__global__ __launch_bounds__(64, NEAR_WAVES) void k_assemble_near(const AsmArgs<T2> P, const int* __restrict__ items,
-                                                                  int per)
+__device__ __forceinline__ void near_part(const AsmArgs<T2>& P, int side, const int* __restrict__ items, int item, int per,
+                                          NearLds& lds)
 {
     constexpr bool LOW = sizeof(T2) == sizeof(float2);
     constexpr int NV = BM ? 8 : 4;  // partial sums of a point: S, D and, Burton-Miller rows, D*, E
-    __shared__ unsigned char todo[64 * NEAR_PART];
-    __shared__ double part[NV][64];
-    static_assert(64 * NEAR_PART <= 256, "a list entry is one byte");
+    unsigned char* todo = lds.todo;
+    double(*part)[64] = lds.part;
     const int parts = NEAR_PART / per;
-    const int* it = items + 3 * (blockIdx.x / parts);
+    const int* it = items + 3 * (item / parts);
     const Tile rt = tab<Tile>(P.g, P.L.rtiles)[it[0] >> 2];
     const Tile cc = tab<Tile>(P.g, P.L.cchunks)[it[1]];
-    const int j0 = it[2] * NEAR_PART + (int)(blockIdx.x % parts) * per, cnt = min(per, cc.count - j0);
+    const int j0 = it[2] * NEAR_PART + item % parts * per, cnt = min(per, cc.count - j0);
     const int lane = threadIdx.x, l0 = (it[0] & 3) * 64;
     const IfacePlan F = tab<IfacePlan>(P.g, P.L.iface)[rt.iface];
-    const int d = P.side ? F.dr : F.dl;
+    const int d = side ? F.dr : F.dl;
     const int sg = tab<int>(P.g, P.L.sigma)[d * P.n_if + cc.iface];
     const int jside = tab<IfacePlan>(P.g, P.L.iface)[cc.iface].dr == d ? 1 : 0;
     const WaveConst W = scalar_copy(tab<WaveConst>(P.g, P.L.wave) + d);
     const BlockConst B = block_const<BM>(tab<DomConst>(P.g, P.L.dom)[d], sg);
     const ElemRec* el = tab<ElemRec>(P.g, P.L.elem);
-    const int row0 = (P.side ? F.row_r : F.row_l) - F.off;
+    const int row0 = (side ? F.row_r : F.row_l) - F.off;
     const bool valid = l0 + lane < rt.count;
     const int i = rt.start + (valid ? l0 + lane : 0);
     int ntodo = 0;  // uniform
@@ -660,6 +670,71 @@ __global__ __launch_bounds__(64, NEAR_WAVES) void k_assemble_near(const AsmArgs<
         __syncthreads();
     }
 }
+template <bool CPLX, bool BM, class T2>
+__global__ __launch_bounds__(64, NEAR_WAVES) void k_assemble_near(const AsmArgs<T2> P, int side,
+                                                                  const int* __restrict__ items, int per)
+{
+    __shared__ NearLds lds;
+    near_part<CPLX, BM>(P, side, items, blockIdx.x, per, lds);
+}
+
+// ---------------------------------------------------------------------------
+// Small systems: every variant's near and far work in one launch, the near
+// work (the longer chains) first.  One wave per workgroup; a range of blocks
+// belongs to one variant and kind.  CPLX: some wavenumber is complex.  Where
+// one variant's work does not fill the chip, launches that follow each other
+// cost more than its arithmetic, and so do the events that fork a second stream
+// and join it.  bem_assemble, kite of N elements, real / lossy interior, FP64,
+// us (a launch per variant and kind on two streams -> one launch): N 256  52.4
+// -> 15.1 / 54.8 -> 15.8, 777  58.6 -> 41.9 / 63.4 -> 50.1, 1337  97.0 -> 80.8 /
+// 111 -> 97.9, 2600  244 -> 233 / 285 -> 277, 3300  385 -> 380 / 460 -> 448,
+// 4096  543 -> 566 / 647 -> 671; FP32 2600  181 -> 181 / 217 -> 217, 4096  349 ->
+// 373 / 429 -> 456: the near code's registers leave three waves per SIMD to
+// the far code, too, which costs most where the chip is full.
+// ---------------------------------------------------------------------------
+struct AsmRange {
+    int end;                // first block after the range
+    short kind, per;        // near 1, Burton-Miller rows 2, complex wavenumber 4, side 8; elements per wave
+    int tiles;              // far: row tiles of the variant
+    const int* list;        // near: items; far: row tiles
+};
+struct AsmRanges {
+    AsmRange r[2 * ASM_VARIANTS];
+};
+template <bool CPLX, class T2>
+__global__ __launch_bounds__(64, ALL_WAVES) void k_assemble_all(const AsmArgs<T2> P, const AsmRanges R)
+{
+    __shared__ NearLds lds;
+    int b = blockIdx.x, k = 0, first = 0;
+    while (b >= R.r[k].end) first = R.r[k++].end;
+    const AsmRange r = R.r[k];
+    b -= first;
+    const int side = r.kind >> 3, per = r.per;
+    const bool bm = r.kind & 2, cplx = CPLX && (r.kind & 4);
+    if (r.kind & 1) {
+        if (bm && cplx)
+            near_part<CPLX, true>(P, side, r.list, b, per, lds);
+        else if (cplx)
+            near_part<CPLX, false>(P, side, r.list, b, per, lds);
+        else if (bm)
+            near_part<false, true>(P, side, r.list, b, per, lds);
+        else
+            near_part<false, false>(P, side, r.list, b, per, lds);
+        return;
+    }
+    // far: the waves of a row tile, then the tiles, then the column parts
+    const int li = (b % (ROW_TILE / 64)) * 64 + threadIdx.x;
+    b /= ROW_TILE / 64;
+    const int tile = r.list[b % r.tiles], col_part = b / r.tiles;
+    if (bm && cplx)
+        far_part<CPLX, true>(P, side, tile, li, col_part, per);
+    else if (cplx)
+        far_part<CPLX, false>(P, side, tile, li, col_part, per);
+    else if (bm)
+        far_part<false, true>(P, side, tile, li, col_part, per);
+    else
+        far_part<false, false>(P, side, tile, li, col_part, per);
+}
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -683,28 +758,51 @@ int elements_per_wave(int most, int least, long long waves, long long wanted)
     return per;
 }
 
-// One launch per variant (side of the interface, row type, complex wavenumber)
-// over the row tiles of that variant; lists[v] / counts[v] are device / host.
-// Variants write disjoint rows: they alternate over the two streams.
+// A variant is a side of the interface, a row type and whether the wavenumber is
+// complex; lists[v] / counts[v] are its row tiles, device / host.  Larger systems
+// take a far and a near launch per variant, whose registers suit each; variants
+// write disjoint rows, so they alternate over the two streams.
 template <class T2>
 hipError_t launch_variants(AsmArgs<T2> P, int n_cchunks, const int* const* lists, const int* counts,
                            const int* const* pairs, const int* pair_counts, hipStream_t s0, hipStream_t s1)
 {
     const int per = elements_per_wave(COL_CHUNK, 2, (long long)((P.N + 63) / 64) * n_cchunks, 4096);
+    if (assemble_one_launch(P.N)) {
+        AsmRanges R{};
+        int k = 0, end = 0;
+        bool any_cplx = false;
+        auto add = [&](int v, int near, int blocks, int each) {
+            if (blocks == 0) return;
+            end += blocks;
+            const int kind = near | (v >> 1 & 1) << 1 | (v & 1) << 2 | (v >> 2 & 1) << 3;
+            R.r[k++] = AsmRange{end, (short)kind, (short)each, counts[v], near ? pairs[v] : lists[v]};
+            any_cplx = any_cplx || (v & 1);
+        };
+        for (int v = 0; v < ASM_VARIANTS; ++v) {
+            const int nper = elements_per_wave(NEAR_PART, 1, pair_counts[v], 512);
+            add(v, 1, pair_counts[v] * (NEAR_PART / nper), nper);
+        }
+        for (int v = 0; v < ASM_VARIANTS; ++v)
+            add(v, 0, counts[v] * (ROW_TILE / 64) * n_cchunks * (COL_CHUNK / per), per);
+        if (any_cplx)
+            hipLaunchKernelGGL((k_assemble_all<true, T2>), dim3(end), dim3(64), 0, s0, P, R);
+        else
+            hipLaunchKernelGGL((k_assemble_all<false, T2>), dim3(end), dim3(64), 0, s0, P, R);
+        return hipGetLastError();
+    }
     int k = 0;
     for (int v = 0; v < ASM_VARIANTS; ++v) {
         if (counts[v] == 0) continue;
         const hipStream_t s = (k++ & 1) ? s1 : s0;
-        const int bm = v >> 1 & 1, cplx = v & 1;
-        P.side = v >> 2 & 1;
+        const int bm = v >> 1 & 1, cplx = v & 1, side = v >> 2 & 1;
         const dim3 grid(counts[v], n_cchunks * (COL_CHUNK / per));
         const int nper = elements_per_wave(NEAR_PART, 1, pair_counts[v], 4096);
 #define BEM_ASM_LAUNCH(C_, B_)                                                                             \
     if (cplx == C_ && bm == B_) {                                                                          \
         if (pair_counts[v] > 0)                                                                            \
             hipLaunchKernelGGL((k_assemble_near<C_, B_, T2>), dim3(pair_counts[v] * (NEAR_PART / nper)), dim3(64), 0, \
-                               s, P, pairs[v], nper);                                                      \
-        hipLaunchKernelGGL((k_assemble_far<C_, B_, T2>), grid, dim3(ROW_TILE), 0, s, P, lists[v], per);     \
+                               s, P, side, pairs[v], nper);                                                \
+        hipLaunchKernelGGL((k_assemble_far<C_, B_, T2>), grid, dim3(ROW_TILE), 0, s, P, side, lists[v], per); \
     }
         BEM_ASM_LAUNCH(false, false)
         BEM_ASM_LAUNCH(true, false)
@@ -717,12 +815,14 @@ hipError_t launch_variants(AsmArgs<T2> P, int n_cchunks, const int* const* lists
 
 }  // namespace
 
+bool assemble_one_launch(int N) { return 2 * (long long)N * N <= 1 << 24; }
+
 hipError_t launch_assemble_f64(const char* g, const GeomLayout& L, int N, int n_if, int n_cchunks, int q,
                                const int* const* lists, const int* counts, const int* const* pairs,
                                const int* pair_counts, double2* A, size_t lda, float2* A32, hipStream_t s,
                                hipStream_t s1)
 {
-    return launch_variants(AsmArgs<double2>{g, L, N, n_if, q, 0, A, A32, lda}, n_cchunks, lists, counts, pairs,
+    return launch_variants(AsmArgs<double2>{g, L, N, n_if, q, A, A32, lda}, n_cchunks, lists, counts, pairs,
                            pair_counts, s, s1);
 }
 
@@ -730,7 +830,7 @@ hipError_t launch_assemble_f32(const char* g, const GeomLayout& L, int N, int n_
                                const int* const* lists, const int* counts, const int* const* pairs,
                                const int* pair_counts, float2* A, size_t lda, hipStream_t s, hipStream_t s1)
 {
-    return launch_variants(AsmArgs<float2>{g, L, N, n_if, q, 0, A, nullptr, lda}, n_cchunks, lists, counts, pairs,
+    return launch_variants(AsmArgs<float2>{g, L, N, n_if, q, A, nullptr, lda}, n_cchunks, lists, counts, pairs,
                            pair_counts, s, s1);
 }
 

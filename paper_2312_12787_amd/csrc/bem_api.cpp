@@ -653,9 +653,10 @@ bem_status bem_assemble(bem_problem* p, int prec, void* A_dev, size_t lda, hipSt
     bemk::hook_call(p->hk(), bemk::KIND_ASSEMBLE, 0, stream);
     float2* A32 = prec == BEM_MIXED ? reinterpret_cast<float2*>(static_cast<char*>(A_dev) + mixed_offset(n, lda))
                                     : nullptr;
-    // The equation-block variants write disjoint rows, so every second one
-    // runs on the problem's side stream (forked from the caller's stream and
-    // joined back below): one variant's launches fill the other's tails.
+    // The equation-block variants write disjoint rows, so every second one of
+    // those launched by themselves runs on the problem's side stream (forked
+    // from the caller's stream and joined back below): one variant's launches
+    // fill the other's tails.
     int nvar = 0;
     for (int v = 0; v < bemk::ASM_VARIANTS; ++v) nvar += p->vcount[v] > 0;
     hipStream_t side = stream;
@@ -663,7 +664,7 @@ bem_status bem_assemble(bem_problem* p, int prec, void* A_dev, size_t lda, hipSt
         const char* e = getenv("BEM_ASM_ONE_STREAM");  // measurement switch: every variant on the caller's stream
         return e && e[0] == '1';
     }();
-    if (nvar >= 2 && !one_stream) {
+    if (nvar >= 2 && !one_stream && !bemk::assemble_one_launch(p->N)) {
         if (!p->asm_side) HIP_OK(hipStreamCreateWithFlags(&p->asm_side, hipStreamNonBlocking));
         for (hipEvent_t& e : p->asm_ev)
             if (!e) HIP_OK(hipEventCreateWithFlags(&e, hipEventDisableTiming));

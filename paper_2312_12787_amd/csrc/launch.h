@@ -35,7 +35,9 @@ constexpr int ASM_VARIANTS = 8;
 // lists[v] / counts[v]: row tiles of variant v (device list / host count);
 // pairs[v] / pair_counts[v]: its (row tile, column chunk, part of NEAR_PART
 // elements) triples that may hold near element pairs (device list / host count).
-// Variants go alternately to s and s1 (they write disjoint rows; s1 may be s).
+// Systems of assemble_one_launch(N) elements go to s in one launch; otherwise
+// variants go alternately to s and s1 (they write disjoint rows; s1 may be s).
+bool assemble_one_launch(int N);
 hipError_t launch_assemble_f64(const char* g, const GeomLayout& L, int N, int n_if, int n_cchunks, int q,
                                const int* const* lists, const int* counts, const int* const* pairs,
                                const int* pair_counts, double2* A, size_t lda, float2* A32, hipStream_t s,
