@@ -112,11 +112,12 @@ struct bem_problem {
     std::vector<bemk::DomIn> dom_in;
     bemk::GlobalIn glob{};
     GeomLayout L{};
-    // pinned host slots for the asynchronous read-back of the GMRES flags
+    // pinned host buffer for the read-back of norms, step counts and flags
     int* pinned = nullptr;      // host address
     int* pinned_dev = nullptr;  // the same memory as the kernels address it
     size_t pinned_ints = 0;
-    hipEvent_t flag_ev[bemk::FLAG_RING] = {};
+    unsigned steps = 0;  // Krylov steps launched, modulo 2^30: the tags of their flags
+    hipEvent_t flag_ev[bemk::SEGMENT_EVENTS] = {};
     bool lent = false;  // pinned / flag_ev belong to the caller (request server slot)
     // Arnoldi segments captured as HIP graphs (bem_solve_opts.graph_steps), by
     // segment index, and everything their launches bake in
@@ -977,18 +978,46 @@ bem_status residual(const Solver& c, const double2* B, size_t ldb, const double2
     return BEM_OK;
 }
 
-bem_status col_norms(const Solver& c, const double2* X, size_t ldx, double* dev_out, std::vector<double>& host)
+// The pinned read-back buffer (pinned_ints): norms of B, norms of the last
+// residual, step counts, flag slots; for the host, and as the kernels address it.
+struct ReadBack {
+    double *bnorm, *norm;
+    int *iters, *flags;
+};
+ReadBack read_back(int* base, size_t nr)
 {
-    HIP_OK(bemk::launch_col_norms(X, ldx, c.n, c.nr, c.at<double>(c.W.norm_part), dev_out, c.s));
-    host.resize(c.nr);
-    HIP_OK(hipMemcpyAsync(host.data(), dev_out, c.nr * sizeof(double), hipMemcpyDeviceToHost, c.s));
-    HIP_OK(hipStreamSynchronize(c.s));
+    double* d = reinterpret_cast<double*>(base);
+    return {d, d + nr, base + 4 * nr, base + (5 * nr + 1) / 2 * 2};
+}
+
+// The buffer with `ring` flag slots: a lent one, or the problem's own.
+bem_status ensure_pinned(const Solver& c, int ring)
+{
+    bem_problem* p = c.p;
+    const size_t ints = bemk::pinned_ints(ring, (size_t)c.nr);
+    if (p->pinned_ints < ints) {
+        if (p->lent) return fail(BEM_E_ARG, "lent flag buffer smaller than the flag ring times nrhs");
+        if (p->pinned) HIP_OK(hipHostFree(p->pinned));
+        p->pinned = nullptr;
+        p->pinned_dev = nullptr;
+        p->pinned_ints = 0;
+        HIP_OK(hipHostMalloc(reinterpret_cast<void**>(&p->pinned), ints * sizeof(int),
+                             hipHostMallocMapped | hipHostMallocCoherent));
+        p->pinned_ints = ints;
+    }
+    if (!p->pinned_dev) HIP_OK(hipHostGetDevicePointer(reinterpret_cast<void**>(&p->pinned_dev), p->pinned, 0));
     return BEM_OK;
 }
 
-bem_status upload_ints(const Solver& c, size_t off, const std::vector<int>& v)
+// Norms of the columns of X into dev_out and, after the stream's work, `host`;
+// with iters, also the step counts (device) into the read-back buffer.
+bem_status col_norms(const Solver& c, const double2* X, size_t ldx, double* dev_out, const int* iters,
+                     std::vector<double>& host)
 {
-    HIP_OK(hipMemcpyAsync(c.w + off, v.data(), v.size() * sizeof(int), hipMemcpyHostToDevice, c.s));
+    const ReadBack d = read_back(c.p->pinned_dev, (size_t)c.nr), h = read_back(c.p->pinned, (size_t)c.nr);
+    HIP_OK(bemk::launch_col_norms(X, ldx, c.n, c.nr, c.at<double>(c.W.norm_part), dev_out, d.norm, iters, d.iters, c.s));
+    HIP_OK(hipStreamSynchronize(c.s));
+    host.assign(h.norm, h.norm + c.nr);
     return BEM_OK;
 }
 
@@ -1043,7 +1072,7 @@ bem_status segment_graph(Solver& c, bemk::ArnoldiArgs arn, int sg, int S, int ri
         for (int j = sg * S; j <= j1 && st == BEM_OK && e == hipSuccess; ++j) {
             if (j < c.m) st = apply_basis(cc, j, c.at<double2>(c.W.W), c.W.ldv);
             if (st != BEM_OK) break;
-            arn.flags_out = p->pinned_dev + (size_t)(j % ring) * c.nr;
+            arn.flags_out = read_back(p->pinned_dev, (size_t)c.nr).flags + (size_t)(j % ring) * c.nr;
             e = bemk::launch_arnoldi(arn, j, p->cap);
         }
         hipGraph_t g = nullptr;
@@ -1060,6 +1089,8 @@ bem_status segment_graph(Solver& c, bemk::ArnoldiArgs arn, int sg, int S, int ri
     out = G.seg[sg];
     return BEM_OK;
 }
+
+constexpr unsigned STEP_MASK = (1u << 30) - 1;  // tags of the steps' flags
 
 // GMRES(m) from X = 0 on the columns with want[r] != 0 (Sec. 3.2).  Arnoldi
 // with delayed re-orthogonalisation (launch_arnoldi: steps 0..m, the last one
@@ -1099,55 +1130,20 @@ struct GmItem {
 };
 
 // Start of a GMRES run: X = 0 on the wanted columns, R = B, norms, stopping
-// thresholds, the flag ring (ring slots per column) and the step arguments.
-bem_status gmres_begin(GmItem& g, int ring, int nev)
+// thresholds and counters on the device, the step arguments.  Nothing waits for
+// the norms: the first cycle's start leaves columns with a zero or non-finite B
+// out, and the host learns of them at the cycle's end.
+bem_status gmres_begin(GmItem& g)
 {
     Solver& c = *g.c;
     const int n = c.n, nr = c.nr, m = c.m;
     const size_t ldv = c.W.ldv;
-    double2* R = c.at<double2>(c.W.R);
-    for (int r = 0; r < nr; ++r)
-        if (g.want[r]) HIP_OK(hipMemsetAsync(g.X + (size_t)r * g.ldx, 0, (size_t)n * sizeof(double2), c.s));
-    HIP_OK(hipMemcpy2DAsync(R, ldv * sizeof(double2), g.B, g.ldb * sizeof(double2), (size_t)n * sizeof(double2), nr,
-                            hipMemcpyDeviceToDevice, c.s));
-    if (bem_status st = col_norms(c, g.B, g.ldb, c.at<double>(c.W.bnorm), g.bnorm)) return st;
-    g.rnorm = g.bnorm;
-    HIP_OK(hipMemcpyAsync(c.at<double>(c.W.rnorm), g.rnorm.data(), nr * sizeof(double), hipMemcpyHostToDevice, c.s));
-    g.alive.assign(nr, 0);
-    for (int r = 0; r < nr; ++r) {
-        if (!g.want[r]) continue;
-        if (!std::isfinite(g.bnorm[r])) {
-            g.nonfinite = true;
-            continue;
-        }
-        if (g.bnorm[r] == 0.0) {
-            (*g.conv)[r] = 1;
-            (*g.rel)[r] = 0.0;
-            continue;
-        }
-        g.alive[r] = 1;
-    }
-    // device-side stopping thresholds and counters
-    std::vector<double> thr(nr);
-    for (int r = 0; r < nr; ++r) thr[r] = g.tol[(size_t)r] * g.bnorm[r];
-    HIP_OK(hipMemcpyAsync(c.at<double>(c.W.thr), thr.data(), nr * sizeof(double), hipMemcpyHostToDevice, c.s));
-    HIP_OK(hipMemcpyAsync(c.at<int>(c.W.iters), g.iters->data(), nr * sizeof(int), hipMemcpyHostToDevice, c.s));
     bem_problem* p = c.p;
-    if (p->pinned_ints < (size_t)ring * nr) {
-        if (p->lent) return fail(BEM_E_ARG, "lent flag buffer smaller than the flag ring times nrhs");
-        if (p->pinned) HIP_OK(hipHostFree(p->pinned));
-        p->pinned = nullptr;
-        p->pinned_dev = nullptr;
-        HIP_OK(hipHostMalloc(reinterpret_cast<void**>(&p->pinned), (size_t)ring * nr * sizeof(int),
-                             hipHostMallocMapped | hipHostMallocCoherent));
-        p->pinned_ints = (size_t)ring * nr;
-    }
-    if (!p->pinned_dev) HIP_OK(hipHostGetDevicePointer(reinterpret_cast<void**>(&p->pinned_dev), p->pinned, 0));
-    for (int k = 0; k < nev; ++k)
-        if (!p->flag_ev[k]) {
-            if (p->lent) return fail(BEM_E_ARG, "lent flag events fewer than the flag ring");
-            HIP_OK(hipEventCreateWithFlags(&p->flag_ev[k], hipEventDisableTiming));
-        }
+    HIP_OK(bemk::launch_begin(g.B, g.ldb, n, nr, c.at<double2>(c.W.R), ldv, g.X, g.ldx, g.want.data(), g.tol.data(),
+                              c.at<double>(c.W.norm_part), c.at<double>(c.W.bnorm), c.at<double>(c.W.rnorm),
+                              c.at<double>(c.W.thr), c.at<int>(c.W.iters), read_back(p->pinned_dev, (size_t)nr).bnorm,
+                              c.s));
+    g.alive = g.want;
     bemk::ArnoldiArgs& arn = g.arn;
     arn = bemk::ArnoldiArgs{};
     arn.V = c.V(0);
@@ -1187,22 +1183,21 @@ bem_status gmres_begin(GmItem& g, int ring, int nev)
     return BEM_OK;
 }
 
-// Start of a cycle: the active flags, v_0 = r / |r| (and its packed copy), g.
+// Start of a cycle: the active marks, v_0 = r / |r| (and its packed copy), g.
 bem_status gmres_cycle_start(GmItem& g)
 {
     Solver& c = *g.c;
     const size_t ldv = c.W.ldv;
     double2* R = c.at<double2>(c.W.R);
-    if (bem_status st = upload_ints(c, c.W.active, g.alive)) return st;
-    HIP_OK(hipMemsetAsync(c.at<int>(c.W.kdim), 0, c.nr * sizeof(int), c.s));
+    const double *rnorm = c.at<double>(c.W.rnorm), *bnorm = c.at<double>(c.W.bnorm);
+    double2* gvec = c.at<double2>(c.W.gvec);
+    int *active = c.at<int>(c.W.active), *kdim = c.at<int>(c.W.kdim);
     if (c.v32())
-        HIP_OK(bemk::launch_start_cycle(R, ldv, c.n, c.nr, c.at<double>(c.W.rnorm), c.m, c.V32(0), ldv,
-                                        c.at<double2>(c.W.gvec), c.at<int>(c.W.active), static_cast<float2*>(g.xt),
-                                        g.pl.xw, c.s));
+        HIP_OK(bemk::launch_start_cycle(R, ldv, c.n, c.nr, rnorm, bnorm, c.m, c.V32(0), ldv, gvec, g.alive.data(), active,
+                                        kdim, static_cast<float2*>(g.xt), g.pl.xw, c.s));
     else
-        HIP_OK(bemk::launch_start_cycle(R, ldv, c.n, c.nr, c.at<double>(c.W.rnorm), c.m, c.V(0), ldv,
-                                        c.at<double2>(c.W.gvec), c.at<int>(c.W.active), static_cast<double2*>(g.xt),
-                                        g.pl.xw, c.s));
+        HIP_OK(bemk::launch_start_cycle(R, ldv, c.n, c.nr, rnorm, bnorm, c.m, c.V(0), ldv, gvec, g.alive.data(), active,
+                                        kdim, static_cast<double2*>(g.xt), g.pl.xw, c.s));
     return BEM_OK;
 }
 
@@ -1227,14 +1222,24 @@ bem_status gmres_cycle_end(GmItem& g)
     // the inner tolerance of an ill-conditioned problem, which then never
     // stops
     if (bem_status st = residual(c, g.B, g.ldb, g.X, g.ldx, R, ldv)) return st;
-    std::vector<int> dev_iters(nr);
-    HIP_OK(hipMemcpyAsync(dev_iters.data(), c.at<int>(c.W.iters), nr * sizeof(int), hipMemcpyDeviceToHost, c.s));
-    if (bem_status st = col_norms(c, R, ldv, c.at<double>(c.W.rnorm), g.rnorm)) return st;
+    if (bem_status st = col_norms(c, R, ldv, c.at<double>(c.W.rnorm), c.at<int>(c.W.iters), g.rnorm)) return st;
+    const ReadBack h = read_back(c.p->pinned, (size_t)nr);
+    g.bnorm.assign(h.bnorm, h.bnorm + nr);
     std::vector<int>& iters = *g.iters;
-    for (int r = 0; r < nr; ++r)
-        if (g.alive[r]) iters[r] = dev_iters[r];
     for (int r = 0; r < nr; ++r) {
         if (!g.alive[r]) continue;
+        if (!std::isfinite(g.bnorm[r])) {
+            g.nonfinite = true;
+            g.alive[r] = 0;
+            continue;
+        }
+        if (g.bnorm[r] == 0.0) {
+            (*g.conv)[r] = 1;
+            (*g.rel)[r] = 0.0;
+            g.alive[r] = 0;
+            continue;
+        }
+        iters[r] = h.iters[r];
         double& rel = (*g.rel)[r];
         rel = g.rnorm[r] / g.bnorm[r];
         if (!std::isfinite(rel)) {
@@ -1252,17 +1257,51 @@ bem_status gmres_cycle_end(GmItem& g)
     return BEM_OK;
 }
 
+// What the flags of step `tag` in slot `slot` say: -1 not written yet, 0 every
+// column stopped, 1 some column runs.
+int flags_of(const Solver& c, int slot, unsigned tag)
+{
+    const volatile int* f = read_back(c.p->pinned, (size_t)c.nr).flags + (size_t)slot * c.nr;
+    int any = 0;
+    for (int r = 0; r < c.nr; ++r) {
+        const int v = f[r];
+        if ((unsigned)v >> 1 != tag) return -1;
+        any |= v & 1;
+    }
+    return any;
+}
+
+// flags_of, once the step has run.  The stream is asked now and then, so that a
+// failed launch ends the wait.
+bem_status wait_flags(const Solver& c, int slot, unsigned tag, int& any)
+{
+    for (unsigned spin = 1;; ++spin) {
+        if ((any = flags_of(c, slot, tag)) >= 0) return BEM_OK;
+        if (spin % 4096 == 0) {
+            const hipError_t e = hipStreamQuery(c.s);
+            if (e == hipErrorNotReady) continue;
+            HIP_OK(e);
+            if ((any = flags_of(c, slot, tag)) >= 0) return BEM_OK;
+            return fail(BEM_E_DEVICE, "a Krylov step ended without its flags");
+        }
+        __builtin_ia32_pause();
+    }
+}
+
 bem_status gmres_batch(const std::vector<GmItem*>& items)
 {
     Solver& c0 = *items[0]->c;
     const int m = c0.m;
     // The GPU decides per right-hand side when to stop (the step blocks, which also
-    // writes the decision into a ring of pinned host slots); the host reads
-    // the flags `lag` steps behind, so the queue never drains.  A
-    // small matrix gets a longer lag (its steps are shorter than the host's
-    // launch work); steps enqueued after every column stopped do nothing but
-    // an unused product.  A batch takes the lag of its largest matrix and the
-    // events of its first problem.
+    // write the decision, tagged with the number of the step, into a ring of
+    // pinned host slots).  After launching a step the host looks for the
+    // newest step whose flags have come, and waits only for the one `lag`
+    // steps back, so the queue never drains.  A small matrix gets a longer lag
+    // (its steps are shorter than the host's launch work); steps enqueued after
+    // every column stopped do nothing but an unused product.  A batch takes the
+    // lag of its largest matrix.
+    // (An event per step costs the GPU a gap, and flags read only `lag` steps
+    // late up to four steps too many: figures at launch_begin.)
     // With captured segments of S steps (one problem) the host reads the
     // flags of a segment's last step one segment late: S + 1 slots keep that
     // slot clear of the segment running meanwhile; two events mark segment
@@ -1271,12 +1310,21 @@ bem_status gmres_batch(const std::vector<GmItem*>& items)
     const int S = graphs ? c0.graph : 0;
     int nmax = 0;
     for (GmItem* g : items) nmax = std::max(nmax, g->c->n);
-    const int lag = graphs ? 1 : flag_lag(nmax, c0.p->prec);
+    const int lag = flag_lag(nmax, c0.p->prec);
     const int ring = graphs ? S + 1 : lag + 1;
-    const int nev = graphs ? 2 : ring;
-    for (GmItem* g : items)
-        if (bem_status st = gmres_begin(*g, ring, g == items[0] ? nev : 0)) return st;
     hipEvent_t* ev = c0.p->flag_ev;
+    for (int k = 0; graphs && k < bemk::SEGMENT_EVENTS; ++k)
+        if (!ev[k]) {
+            if (c0.p->lent) return fail(BEM_E_ARG, "lent events fewer than the segments need");
+            HIP_OK(hipEventCreateWithFlags(&ev[k], hipEventDisableTiming));
+        }
+    for (GmItem* g : items) {
+        Solver& c = *g->c;
+        if (bem_status st = ensure_pinned(c, ring)) return st;
+        // flags of an earlier solve, of this problem or another one that was lent the buffer
+        std::fill_n(read_back(c.p->pinned, (size_t)c.nr).flags, (size_t)ring * c.nr, -1);
+        if (bem_status st = gmres_begin(*g)) return st;
+    }
     hipStream_t s = c0.s;
     std::vector<bemk::ArnoldiArgs> set;
     for (;;) {
@@ -1299,7 +1347,7 @@ bem_status gmres_batch(const std::vector<GmItem*>& items)
                 if (sg >= 1) {
                     HIP_OK(hipEventSynchronize(ev[(sg - 1) & 1]));
                     const int jl = sg * S - 1;  // last step of the previous segment
-                    const int* prev = c.p->pinned + (size_t)(jl % ring) * c.nr;
+                    const int* prev = read_back(c.p->pinned, (size_t)c.nr).flags + (size_t)(jl % ring) * c.nr;
                     bool any = false;
                     for (int r = 0; r < c.nr; ++r) any = any || prev[r];
                     if (!any) break;
@@ -1313,27 +1361,32 @@ bem_status gmres_batch(const std::vector<GmItem*>& items)
                 Solver& c = *g->c;
                 if (j < m)
                     if (bem_status st = apply_basis(c, j, c.at<double2>(c.W.W), c.W.ldv)) return st;
-                g->arn.flags_out = c.p->pinned_dev + (size_t)(j % ring) * c.nr;
+                g->arn.flags_out = read_back(c.p->pinned_dev, (size_t)c.nr).flags + (size_t)(j % ring) * c.nr;
+                g->arn.tag = (int)(c.p->steps & STEP_MASK);
                 set.push_back(g->arn);
             }
             for (size_t k = 0; k < set.size(); k += bemk::MAX_FUSED)
                 HIP_OK(bemk::launch_arnoldi_set(set.data() + k, (int)std::min(set.size() - k, (size_t)bemk::MAX_FUSED), j,
                                                 s));
-            HIP_OK(hipEventRecord(ev[j % ring], s));
-            if (j >= lag) {
-                HIP_OK(hipEventSynchronize(ev[(j - lag) % ring]));
-                bool any_run = false;
-                for (GmItem* g : cyc) {
-                    if (!g->run) continue;
-                    const int* prev = g->c->p->pinned + (size_t)((j - lag) % ring) * g->c->nr;
-                    bool any = false;
-                    for (int r = 0; r < g->c->nr; ++r) any = any || prev[r];
-                    // every column stopped at step j - lag: the later steps were no-ops for it
-                    if (!any) g->run = false;
-                    any_run = any_run || g->run;
+            bool any_run = false;
+            for (GmItem* g : cyc) {
+                if (!g->run) continue;
+                Solver& c = *g->c;
+                const unsigned now = c.p->steps++;  // the tag of step j
+                int any = -1;
+                for (int back = 0; back <= std::min(j, lag) && any < 0; ++back) {
+                    const unsigned tag = (now - back) & STEP_MASK;
+                    const int slot = (j - back) % ring;
+                    if (back < lag)
+                        any = flags_of(c, slot, tag);
+                    else if (bem_status st = wait_flags(c, slot, tag, any))
+                        return st;
                 }
-                if (!any_run) break;
+                // every column stopped at some step: the later ones were no-ops for it
+                if (any == 0) g->run = false;
+                any_run = any_run || g->run;
             }
+            if (!any_run) break;
         }
         for (GmItem* g : cyc)
             if (bem_status st = gmres_cycle_end(*g)) return st;
@@ -1454,11 +1507,16 @@ bem_status bem_solve_batch(int np, bem_problem* const* ps, const int* nrhs_v, co
         for (SolveItem& t : it) {
             Solver& c = t.c;
             const size_t ldv = c.W.ldv;
-            for (int r = 0; r < c.nr; ++r)
-                HIP_OK(hipMemsetAsync(t.X + (size_t)r * t.ldx, 0, (size_t)c.n * sizeof(double2), stream));
-            if (bem_status st = col_norms(c, t.B, t.ldb, c.at<double>(c.W.bnorm), t.bnorm)) return st;
-            HIP_OK(hipMemcpy2DAsync(c.at<double2>(c.W.Ro), ldv * sizeof(double2), t.B, t.ldb * sizeof(double2),
-                                    (size_t)c.n * sizeof(double2), c.nr, hipMemcpyDeviceToDevice, stream));
+            if (bem_status st = ensure_pinned(c, bemk::FLAG_RING)) return st;
+            HIP_OK(bemk::launch_begin(t.B, t.ldb, c.n, c.nr, c.at<double2>(c.W.Ro), ldv, t.X, t.ldx, t.want.data(), nullptr,
+                                      c.at<double>(c.W.norm_part), c.at<double>(c.W.bnorm), c.at<double>(c.W.rnorm),
+                                      nullptr, nullptr, read_back(c.p->pinned_dev, (size_t)c.nr).bnorm, stream));
+        }
+        for (SolveItem& t : it) {
+            Solver& c = t.c;
+            HIP_OK(hipStreamSynchronize(stream));
+            const ReadBack h = read_back(c.p->pinned, (size_t)c.nr);
+            t.bnorm.assign(h.bnorm, h.bnorm + c.nr);
             t.rnorm = t.bnorm;
             t.active.assign(c.nr, 1);
         }
@@ -1512,11 +1570,9 @@ bem_status bem_solve_batch(int np, bem_problem* const* ps, const int* nrhs_v, co
                     t.iters[r] += t.it2[r];
                     if (t.active[r]) ++t.cycles[r];
                 }
-                if (bem_status st = upload_ints(c, c.W.active, t.active)) return st;
-                HIP_OK(bemk::launch_add_f64(c.at<double2>(c.W.D), ldv, c.n, c.nr, t.X, t.ldx, c.at<int>(c.W.active),
-                                            stream));
+                HIP_OK(bemk::launch_add_f64(c.at<double2>(c.W.D), ldv, c.n, c.nr, t.X, t.ldx, t.active.data(), stream));
                 if (bem_status st = residual(c, t.B, t.ldb, t.X, t.ldx, c.at<double2>(c.W.Ro), ldv)) return st;
-                if (bem_status st = col_norms(c, c.at<double2>(c.W.Ro), ldv, c.at<double>(c.W.rnorm), t.rnorm))
+                if (bem_status st = col_norms(c, c.at<double2>(c.W.Ro), ldv, c.at<double>(c.W.rnorm), nullptr, t.rnorm))
                     return st;
             }
         }
@@ -1586,7 +1642,7 @@ size_t matrix_bytes_ld(int prec, size_t n, size_t lda)
                              : mixed_offset(n, lda) + lda * n * sizeof(float2);
 }
 
-// The request server keeps one pinned flag buffer and FLAG_RING events per slot and
+// The request server keeps one pinned read-back buffer and two events per slot and
 // lends them to each problem it runs, so that no request allocates or frees
 // pinned memory (hipHostFree may wait for the whole device).
 void lend_flag_buffers(bem_problem* p, int* pinned, size_t ints, const hipEvent_t* ev)
@@ -1594,7 +1650,7 @@ void lend_flag_buffers(bem_problem* p, int* pinned, size_t ints, const hipEvent_
     p->pinned = pinned;
     p->pinned_dev = nullptr;
     p->pinned_ints = ints;
-    for (int k = 0; k < FLAG_RING; ++k) p->flag_ev[k] = ev[k];
+    for (int k = 0; k < SEGMENT_EVENTS; ++k) p->flag_ev[k] = ev[k];
     p->lent = true;
 }
 

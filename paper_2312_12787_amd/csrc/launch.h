@@ -14,11 +14,17 @@ namespace bemk {
 // Optional callback around the main kernel of a launcher (phase 0 before the
 // launch, 1 after), used by the library's HIP-event timing.
 enum { KIND_ASSEMBLE = 0, KIND_MATVEC = 1, KIND_RESIDUAL = 2, N_KINDS = 3 };
-// GMRES stopping-flag read-back: ring of pinned slots and events (host lag + 1)
+// GMRES stopping-flag read-back: ring of pinned slots (host lag + 1); the
+// captured path marks the ends of its segments with two events.
 constexpr int FLAG_RING = 5;
+constexpr int SEGMENT_EVENTS = 2;
 // Graph-captured Arnoldi: at most this many Krylov steps per captured segment
 // (the flag ring of that path has GRAPH_MAX_STEPS + 1 slots)
 constexpr int GRAPH_MAX_STEPS = 16;
+// Pinned read-back buffer of a solve, in ints (even): per right-hand side the
+// norm of B and of a residual (doubles) and the steps done, then `ring` slots of
+// stopping flags.
+constexpr size_t pinned_ints(int ring, size_t nr) { return (5 * nr + 1) / 2 * 2 + ((size_t)ring * nr + 1) / 2 * 2; }
 struct KernelHook {
     void (*fn)(void* ctx, int kind, int phase, hipStream_t s);
     void* ctx;
@@ -151,8 +157,19 @@ hipError_t launch_residual_f32A(const float2* A, size_t lda, int n, const double
                                 hipStream_t s, const KernelHook* hook = nullptr, const MvShapes* shapes = nullptr);
 
 // GMRES building blocks (basis V[(i * nr + r) * ldv + q], FP64).
+// Norms of nr columns into out and the pinned host_norm; with iters, the
+// step counts into the pinned host_iters.
 hipError_t launch_col_norms(const double2* X, size_t ldx, int n, int nr, double* partial, double* out,
-                            hipStream_t s);
+                            double* host_norm, const int* iters, int* host_iters, hipStream_t s);
+// Columns are chosen by a 64-bit mask in the kernel's arguments: a launch per
+// MASK_COLS columns.
+constexpr int MASK_COLS = 64;
+// Start of a run: R = B on all columns, X = 0 on the wanted ones, |B| into bnorm,
+// rnorm and the pinned host_bnorm, thr = tol |B|, iters = 0 (tol, thr and iters
+// may be null together).
+hipError_t launch_begin(const double2* B, size_t ldb, int n, int nr, double2* R, size_t ldr, double2* X, size_t ldx,
+                        const int* want, const double* tol, double* partial, double* bnorm, double* rnorm, double* thr,
+                        int* iters, double* host_bnorm, hipStream_t s);
 // Row chunks of the projection kernel and blocks of the update kernel: the
 // partial-sum buffers hold arnoldi_blocks(n) and update_blocks(n, nr) entries
 // per right-hand side.
@@ -172,7 +189,8 @@ struct ArnoldiArgs {
     const double* thr;             // absolute stopping thresholds
     int maxit;
     int *iters, *kdim, *active;    // counters and flags (device)
-    int* flags_out;                // copy of the stopping flags in pinned host memory (device address)
+    int* flags_out;                // the stopping flags in pinned host memory (device address): 2 tag + still running
+    int tag;                       // number of the step, by which the host tells its flags from older ones
     bool v32;                      // basis stored as complex64 at V (same element offsets), else complex128
     // where the next product reads its packed right-hand sides (xw columns;
     // nullptr: the vector product reads V itself)
@@ -189,14 +207,15 @@ hipError_t launch_arnoldi_set(const ArnoldiArgs* a, int np, int j, hipStream_t s
 // Host side (bem_api.cpp): bytes of a matrix buffer of order n and leading
 // dimension lda in precision prec (a bem_prec value).
 size_t matrix_bytes_ld(int prec, size_t n, size_t lda);
-// v_0 = R / |R| per active right-hand side (and its packed copy at xt, xw
-// columns, for the first product; xt may be nullptr), g = |R| e_0.
-hipError_t launch_start_cycle(const double2* R, size_t ldr, int n, int nr, const double* rnorm, int m,
-                              double2* V, size_t ldv, double2* gvec, const int* active, double2* xt, int xw,
-                              hipStream_t s);
-hipError_t launch_start_cycle(const double2* R, size_t ldr, int n, int nr, const double* rnorm, int m,
-                              float2* V, size_t ldv, double2* gvec, const int* active, float2* xt, int xw,
-                              hipStream_t s);
+// v_0 = R / |R| per running right-hand side (and its packed copy at xt, xw
+// columns, for the first product; xt may be nullptr), g = |R| e_0, kdim = 0 and
+// the active marks: columns with run[r] != 0 (host) and 0 < bnorm[r] < inf.
+hipError_t launch_start_cycle(const double2* R, size_t ldr, int n, int nr, const double* rnorm, const double* bnorm,
+                              int m, double2* V, size_t ldv, double2* gvec, const int* run, int* active, int* kdim,
+                              double2* xt, int xw, hipStream_t s);
+hipError_t launch_start_cycle(const double2* R, size_t ldr, int n, int nr, const double* rnorm, const double* bnorm,
+                              int m, float2* V, size_t ldv, double2* gvec, const int* run, int* active, int* kdim,
+                              float2* xt, int xw, hipStream_t s);
 hipError_t launch_backsolve(int nr, int m, const double2* H, const double2* gvec, const int* kdim, double2* y,
                             hipStream_t s);
 // y: [nr][m + 1] (the back-solve's output)
@@ -206,7 +225,8 @@ hipError_t launch_xupdate(const float2* V, size_t ldv, int nr, int n, int m, con
                           double2* X, size_t ldx, hipStream_t s);
 hipError_t launch_axpby_res(const double2* B, size_t ldb, const double2* AX, size_t ldax, int n, int nr,
                             double2* R, size_t ldr, hipStream_t s);
-hipError_t launch_add_f64(const double2* D, size_t ldd, int n, int nr, double2* X, size_t ldx, const int* active,
+// X += D on the columns with add[r] != 0 (host)
+hipError_t launch_add_f64(const double2* D, size_t ldd, int n, int nr, double2* X, size_t ldx, const int* add,
                           hipStream_t s);
 
 // Field at points (nearfield.hip): right-hand sides in groups of NF_RB, their

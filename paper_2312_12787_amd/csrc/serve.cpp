@@ -33,10 +33,10 @@ namespace {
 
 constexpr int MAX_SLOTS = 16;
 constexpr int MAX_REQ_RHS = 256;
-// flag slots per right-hand side: the kernel-by-kernel ring or the captured
-// path's GRAPH_MAX_STEPS + 1, whichever is longer
-constexpr size_t FLAG_INTS =
-    (size_t)(bemk::FLAG_RING > bemk::GRAPH_MAX_STEPS + 1 ? bemk::FLAG_RING : bemk::GRAPH_MAX_STEPS + 1) * MAX_REQ_RHS;
+// read-back buffer of a request: as many flag slots as the kernel-by-kernel
+// ring or the captured path's GRAPH_MAX_STEPS + 1, whichever is longer
+constexpr size_t FLAG_INTS = bemk::pinned_ints(
+    bemk::FLAG_RING > bemk::GRAPH_MAX_STEPS + 1 ? bemk::FLAG_RING : bemk::GRAPH_MAX_STEPS + 1, MAX_REQ_RHS);
 
 size_t al(size_t b) { return (b + 255) & ~size_t(255); }
 
@@ -111,7 +111,7 @@ struct Request {
 struct Slot {
     hipStream_t stream = nullptr;
     int* pinned = nullptr;
-    hipEvent_t ev[bemk::FLAG_RING] = {};
+    hipEvent_t ev[bemk::SEGMENT_EVENTS] = {};
     std::thread th;
 };
 
