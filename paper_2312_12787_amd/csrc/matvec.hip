@@ -125,7 +125,7 @@ __global__ __launch_bounds__(BS) void k_matvec(const TA* __restrict__ A, size_t 
     }
 }
 
-// Y[:, r] = sum over splits (in order) of the partial products; optionally
+// Y[:, r] = sum over splits (in order, in FP64) of the partial products; optionally
 // R = B - Y (residual form) when B != nullptr.
 template <class ACC, class TY>
 __global__ void k_matvec_reduce(const ACC* __restrict__ part, int splits, int n, int nrhs, TY* __restrict__ Y,
@@ -134,8 +134,7 @@ __global__ void k_matvec_reduce(const ACC* __restrict__ part, int splits, int n,
     const int row = blockIdx.x * blockDim.x + threadIdx.x;
     const int r = blockIdx.y;
     if (row >= n || r >= nrhs) return;
-    using S = decltype(ACC{}.x);
-    S sr = S(0), si = S(0);
+    double sr = 0.0, si = 0.0;
     for (int s = 0; s < splits; ++s) {
         const ACC v = part[((size_t)s * nrhs + r) * n + row];
         sr += v.x;
@@ -144,8 +143,8 @@ __global__ void k_matvec_reduce(const ACC* __restrict__ part, int splits, int n,
     TY out;
     if (B) {
         const double2 b = B[(size_t)r * ldb + row];
-        out.x = (decltype(out.x))(b.x - (double)sr);
-        out.y = (decltype(out.y))(b.y - (double)si);
+        out.x = (decltype(out.x))(b.x - sr);
+        out.y = (decltype(out.y))(b.y - si);
     } else {
         out.x = (decltype(out.x))sr;
         out.y = (decltype(out.y))si;
@@ -198,14 +197,13 @@ struct Mfma<float> {
 // The wide shapes, which are matrix-core bound, carry an occupancy target:
 // left alone the compiler puts their accumulators in AGPRs beside the load
 // slots and runs one or two waves per SIMD; with the target they fit in the
-// VGPRs without spilling (FP32 sums with 64 right-hand sides: three waves,
-// 3.49 -> 3.45 ms per kite16384 product; FP64 sums over two to four groups,
-// where RT * NG <= 4 keeps them spill-free: two waves, the kite16384 FP64
-// path 73.7 -> 84.4 solves/s).  The single-group shapes keep the compiler's
+// VGPRs (FP32 sums over three or four groups, with their totals: two waves;
+// FP64 sums over two to four groups, where RT * NG <= 4 keeps them spill-free:
+// two waves, the kite16384 FP64 path 73.7 -> 84.4 solves/s).  The single-group shapes keep the compiler's
 // own allocation (the HBM-bound 16-RHS product pipelines its loads instead).
 constexpr int mfma_min_waves(int tbytes, int rt, int ng)
 {
-    return (tbytes == 4 && ng >= 4) ? 3 : (tbytes == 8 && ng >= 2 && rt * ng <= 4) ? 2 : 1;
+    return (tbytes == 4 && ng >= 3) ? 2 : (tbytes == 8 && ng >= 2 && rt * ng <= 4) ? 2 : 1;
 }
 
 template <class TA, class T, int RT, int U, bool G3, int NG>
@@ -235,6 +233,32 @@ __global__ __launch_bounds__(BS, mfma_min_waves(sizeof(T), RT, NG)) void k_matve
     for (int g = 0; g < NG; ++g)
 #pragma unroll
         for (int t = 0; t < RT; ++t) rr0[g][t] = rr1[g][t] = ii0[g][t] = ii1[g][t] = acc{0, 0, 0, 0};
+    // The FP32 sums of two and more groups run over 256 columns at most and are
+    // then added to totals, so that their rounding does not grow with the
+    // columns of a split (n = 16384, 64 right-hand sides, largest error against
+    // FP64 sums 1.1e-6 with 8 splits, 2.2e-6 with the faster 2, 4.4e-7 folded).
+    // The other shapes have no registers to spare for totals (FP64, one group:
+    // 172 -> 188 us at n = 8192); their splits are not fewer than mfma_default
+    // says.
+    constexpr int FOLD = sizeof(T) == 4 && NG >= 2 ? 256 : 0;
+    acc sum[4][FOLD ? NG : 1][FOLD ? RT : 1];
+    if (FOLD)
+#pragma unroll
+        for (int g = 0; g < NG; ++g)
+#pragma unroll
+            for (int t = 0; t < RT; ++t) sum[0][g][t] = sum[1][g][t] = sum[2][g][t] = sum[3][g][t] = acc{0, 0, 0, 0};
+    auto fold = [&]() {
+#pragma unroll
+        for (int g = 0; g < NG; ++g)
+#pragma unroll
+            for (int t = 0; t < RT; ++t) {
+                sum[0][g][t] += rr0[g][t];
+                sum[1][g][t] += rr1[g][t];
+                sum[2][g][t] += ii0[g][t];
+                if (!G3) sum[3][g][t] += ii1[g][t];
+                rr0[g][t] = rr1[g][t] = ii0[g][t] = ii1[g][t] = acc{0, 0, 0, 0};
+            }
+    };
     // one 16 x 4 tile of A (per row tile) against 4 x 16 NG of X
     auto step = [&](const T (&ar)[RT], const T (&ai)[RT], const T (&xr)[NG], const T (&xi)[NG]) {
 #pragma unroll
@@ -329,6 +353,8 @@ __global__ __launch_bounds__(BS, mfma_min_waves(sizeof(T), RT, NG)) void k_matve
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 c = cn;
+                if constexpr (FOLD != 0)
+                    if ((c - c0) % FOLD == 0) fold();
                 if (!more) break;
             }
         }
@@ -355,6 +381,8 @@ __global__ __launch_bounds__(BS, mfma_min_waves(sizeof(T), RT, NG)) void k_matve
                 for (int g = 0; g < NG; ++g) x[u][g] = xn[u][g];
             }
             c = cn;
+            if constexpr (FOLD != 0)
+                if ((c - c0) % FOLD == 0) fold();
         }
     }
     for (; c < c1; c += 4) {
@@ -382,6 +410,18 @@ __global__ __launch_bounds__(BS, mfma_min_waves(sizeof(T), RT, NG)) void k_matve
             }
         }
         step(ar, ai, xr, xi);
+    }
+    if constexpr (FOLD != 0) {
+        fold();
+#pragma unroll
+        for (int g = 0; g < NG; ++g)
+#pragma unroll
+            for (int t = 0; t < RT; ++t) {
+                rr0[g][t] = sum[0][g][t];
+                rr1[g][t] = sum[1][g][t];
+                ii0[g][t] = sum[2][g][t];
+                ii1[g][t] = sum[3][g][t];
+            }
     }
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
@@ -553,12 +593,15 @@ __global__ __launch_bounds__(64 * ROW_MAX_WAVES) void k_rowblock_mfma(const TA* 
             ii = M::run(ar + ai, xr + xi, ii);
         }
     };
+    // FP32 sums over 256 columns at most, then into totals, as k_matvec_mfma's
+    constexpr int FOLD = sizeof(T) == 4 ? 256 / (4 * U) : 0;
+    acc s0{0, 0, 0, 0}, s1{0, 0, 0, 0}, s2{0, 0, 0, 0};
     int c = wave * 4 * U;
     if (c < n) {
         TA a[U];
         TX x[U];
         load(a, x, c);
-        for (;;) {
+        for (int trip = 1;; ++trip) {
             const int cn = c + nw * 4 * U;
             if (cn >= n) {
                 compute(a, x, c);
@@ -568,6 +611,13 @@ __global__ __launch_bounds__(64 * ROW_MAX_WAVES) void k_rowblock_mfma(const TA* 
             TX xn[U];
             load(an, xn, cn);
             compute(a, x, c);
+            if constexpr (FOLD != 0)
+                if (trip % FOLD == 0) {
+                    s0 += rr0;
+                    s1 += rr1;
+                    s2 += ii;
+                    rr0 = rr1 = ii = acc{0, 0, 0, 0};
+                }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 a[u] = an[u];
@@ -575,6 +625,11 @@ __global__ __launch_bounds__(64 * ROW_MAX_WAVES) void k_rowblock_mfma(const TA* 
             }
             c = cn;
         }
+    }
+    if (FOLD != 0) {
+        rr0 += s0;
+        rr1 += s1;
+        ii += s2;
     }
     T* red = reinterpret_cast<T*>(row_lds);  // [wave][2 j + part][lane]
 #pragma unroll
@@ -590,12 +645,12 @@ __global__ __launch_bounds__(64 * ROW_MAX_WAVES) void k_rowblock_mfma(const TA* 
     // the lane and element that hold row rl of right-hand side r
     const bool f64 = sizeof(T) == 8;
     const int j = f64 ? rl >> 2 : rl & 3, src = (f64 ? rl & 3 : rl >> 2) * 16 + r;
-    T sr = T(0), si = T(0);
+    double sr = 0.0, si = 0.0;
     for (int w = 0; w < nw; ++w) {
         sr += red[(w * 8 + 2 * j) * 64 + src];
         si += red[(w * 8 + 2 * j + 1) * 64 + src];
     }
-    row_store<MODE>(o, row, r, (double)sr, (double)si, inv_s, act_s);
+    row_store<MODE>(o, row, r, sr, si, inv_s, act_s);
 }
 
 // Vector form, NR = 1 to 4 right-hand sides: lane l holds row l % 16 and column
@@ -678,12 +733,12 @@ __global__ __launch_bounds__(64 * ROW_MAX_WAVES) void k_rowblock_vec(const TA* _
     const int t = threadIdx.x, rl = t & 15, r = t >> 4;
     const int row = row0 + rl;
     if (r >= NR || row >= n) return;
-    S sr = S(0), si = S(0);
+    double sr = 0.0, si = 0.0;
     for (int w = 0; w < nw; ++w) {
         sr += red[w][2 * r][rl];
         si += red[w][2 * r + 1][rl];
     }
-    row_store<MODE>(o, row, r, (double)sr, (double)si, inv_s, act_s);
+    row_store<MODE>(o, row, r, sr, si, inv_s, act_s);
 }
 
 // X of a row-block vector product fits the LDS beside the wave sums.
@@ -735,20 +790,19 @@ __global__ void k_pack_xt(const TX* __restrict__ X, size_t ldx, int n, int nr, i
     XT[(size_t)c * xw + r] = v;
 }
 
-// Column splits of the product over one group of 16 right-hand sides, with rows
-// split into blocks of 128.  `room` blocks run at once: 256, one per CU, with
-// FP64 sums (its registers leave one wave per SIMD), 512 with FP32 sums.  More
-// blocks than that go in another turn, which costs as much as a full one, and
-// each split writes and re-reads its partial sums: the fewest splits that fill
-// the turns they take to 4/5.
-int group_splits(int n, int room)
+// Column splits of the FP64 product over one group of 16 right-hand sides, with
+// rows split into blocks of 128.  256 blocks run at once, one per CU (the
+// registers leave one wave per SIMD).  More go in another turn, which costs as
+// much as a full one, and each split writes and re-reads its partial sums: the
+// fewest splits that fill the turns they take to 4/5.
+int group_splits(int n)
 {
     const int rowblocks = (n + 127) / 128, most = std::max(1, std::min(64, n / 64));
     int best = 1;
     double fill = 0;
     for (int s = 1; s <= most && fill < 0.8; ++s) {
-        const int blocks = rowblocks * s, turns = (blocks + room - 1) / room;
-        const double f = (double)blocks / ((double)turns * room);
+        const int blocks = rowblocks * s, turns = (blocks + 255) / 256;
+        const double f = (double)blocks / (256.0 * turns);
         if (f > fill) {
             fill = f;
             best = s;
@@ -757,33 +811,69 @@ int group_splits(int n, int room)
     return best;
 }
 
+// Column splits of the product over 2-4 groups, which is bound by the matrix
+// cores: a CU's blocks share them, so the fullest CU sets the time, ceil(blocks
+// / 256) blocks of n / splits columns; a block costs about 40 columns more to
+// start and to end.  A lone wave per SIMD with FP64 sums over one row tile
+// leaves gaps (5 %; two row tiles, or FP32 sums, have twice the products in a
+// step and none).
+//
+// FP64 sums, which run through a whole split, take at least as many splits as
+// give about 1024 blocks, or 8 (two groups).
+int wide_splits(int n, int rt, bool f64, int least_splits, int most)
+{
+    const int rowblocks = (n + 16 * rt * MV_WAVES - 1) / (16 * rt * MV_WAVES);
+    const int first = std::min(least_splits, most);
+    int best = first;
+    double least = 0;
+    for (int s = first; s <= most; ++s) {
+        const int deep = (rowblocks * s + 255) / 256;
+        double cost = deep * (1.0 / s + 40.0 / n);
+        if (f64 && rt == 1 && deep == 1) cost *= 1.05;
+        if (s == first || cost < least) {
+            least = cost;
+            best = s;
+        }
+    }
+    return best;
+}
+
+// The most column splits a product may take: its partial-sum buffer is sized for them.
+int split_limit(int n, int ng)
+{
+    const int want = (131072 + n - 1) / std::max(1, n);  // about 2048 blocks at one row tile per wave
+    return std::max(1, std::min({ng <= 2 ? std::max(want, 8) : want, 64, std::max(1, n / 64)}));
+}
+
 // Launch shape of the matrix-core product: row tiles per wave, column steps
 // in flight, column splits, 3-product form, for one group of 16 right-hand
 // sides and for 2-4 groups per pass.
 //
-// One group (bem_matvec, 16 right-hand sides, us; 8 column steps in flight and
-// 8 splits at every size / 8 steps with FP64 sums, 4 with FP32, and
-// group_splits): FP64 n 4400 88.6 / 65.3, 5400 115 / 88.2, 8192 189 / 172,
-// 10000 308 / 263, 12000 393 / 385, 16384 703 / 655; FP32 n 6800 90.2 / 86.7,
-// 8192 106 / 104, 10000 188 / 160, 12000 232 / 220, 16384 402 / 391.
+// One group (bem_matvec, 16 right-hand sides, us).  FP64, 8 splits at every
+// size / group_splits: n 4400 88.6 / 65.3, 5400 115 / 88.2, 8192 189 / 172, 10000
+// 308 / 263, 12000 393 / 385, 16384 703 / 655.  FP32 keeps 8 splits (fewer are
+// up to 15 % faster, but long FP32 sums lose accuracy), 8 / 4 column steps in
+// flight: n 6800 90.2 / 86.7, 8192 106 / 104, 12000 232 / 218, 16384 412 / 405.
 //
-// 2-4 groups: measured at n = 32768 with 32 and 64 right-hand sides; FP64 sums
-// over 3-4 groups take one row tile, which runs two waves per SIMD (the mixed
-// path's 64-RHS refinement residual 7.73 -> 6.29 ms); splits for about 1024
-// blocks.
+// 2-4 groups (32, 48 and 64 right-hand sides, us; splits for about 1024 blocks,
+// FP32 and two groups of FP64 always 2 and 1 row tiles / as here): FP32 n 1554
+// 28.8, 36.3, 45.2 / 20.0, 23.9, 27.1; 2674  33.5, 42.9, 50.5 / 31.6, 37.5, 44.9;
+// 4096  52.1, 64.8, 81.5 / 47.0, 61.6, 74.0; 10000  237, 325, 438 / 220, 294, 374;
+// 16384  533, 715, 957 / 525, 701, 892; FP64 n 1554  27.2, 37.1, 44.3 / 24.9, 30.5,
+// 35.0; 2674  54.2, 62.6, 77.4 / 42.0, 51.8, 64.8; 6000  156, 209, 272 / 145, 194,
+// 249; 10000  416, 550, 712 / 375, 506, 649; 16384  1026, 1285, 1618 / 924, 1278,
+// 1625.  Two row tiles read X half as often, but fill the chip with longer
+// splits: below n = 3072 one is faster (FP32, 64 right-hand sides, best
+// splits of each, 1 / 2 tiles: n 2674 44.9 / 47.4, 4096 79.4 / 74.0; FP64, 32:
+// 42.0 / 42.7, 74.6 / 72.7).  FP64 sums over 3-4 groups take one, whose registers
+// leave two waves per SIMD (n = 8192, 64 right-hand sides: 425 / 503).
 MvShape mfma_default(int n, int ng, bool f64)
 {
-    MvShape c{f64 ? 1 : 2, 4, 0, 1};
-    if (ng == 1) {
-        c = f64 ? MvShape{2, 8, group_splits(n, 256), 1} : MvShape{2, 4, group_splits(n, 512), 1};
-    } else if (f64 && ng == 2) {
-        c.splits = 8;
-    } else {
-        const int rowblocks = (n + 16 * c.rt * MV_WAVES - 1) / (16 * c.rt * MV_WAVES);
-        c.splits = std::min({(1024 + rowblocks - 1) / rowblocks, std::max(1, n / 256), 64});
-    }
-    c.splits = std::max(1, std::min(c.splits, std::max(1, n / 64)));
-    return c;
+    const int most = split_limit(n, ng);
+    if (ng == 1) return f64 ? MvShape{2, 8, std::min(group_splits(n), most), 1} : MvShape{2, 4, std::min(8, most), 1};
+    const int rt = n < 3072 || (f64 && ng >= 3) ? 1 : 2;
+    const int tiles = (n + 63) / 64, least = !f64 ? 1 : ng == 2 ? 8 : std::max(1, std::min((1023 + tiles) / tiles, n / 256));
+    return {rt, 4, wide_splits(n, rt, f64, least, most), 1};
 }
 
 // Shapes of the row-block products (in a table row: vector class rt = 1, one
@@ -854,13 +944,7 @@ int size_class(int n)
     return lg;
 }
 
-int split_cap(int n, int ng)
-{
-    if (ng == 0) return matvec_splits_valu(n);
-    const int want = (131072 + n - 1) / std::max(1, n);  // about 2048 blocks at one row tile per wave
-    const int cap = std::max(1, std::min({std::max(want, 8), 64, std::max(1, n / 64)}));
-    return std::max(cap, std::max(mfma_default(n, ng, true).splits, mfma_default(n, ng, false).splits));
-}
+int split_cap(int n, int ng) { return ng == 0 ? matvec_splits_valu(n) : split_limit(n, ng); }
 
 // Environment overrides of the launch shape (manual tuning): BEM_MV_CFG for
 // one group of 16 right-hand sides, BEM_MV_CFG_WIDE for 2-4 groups,
@@ -1058,8 +1142,7 @@ __global__ void k_step_reduce(const ACC* __restrict__ part, int splits, int n, i
     const int row = blockIdx.x * blockDim.x + threadIdx.x;
     const int act = active[r];
     // this thread's loads first (they do not depend on |w|), then |w|
-    using S = decltype(ACC{}.x);
-    S sr = S(0), si = S(0);
+    double sr = 0.0, si = 0.0;
     double2 w = make_double2(0.0, 0.0);
     double2* y = Y + (size_t)r * ldy + row;
     if (row < n) {
@@ -1083,7 +1166,7 @@ __global__ void k_step_reduce(const ACC* __restrict__ part, int splits, int n, i
     if (row >= n) return;
     const double inv = inv_s;
     if (act == 1) st_basis(V + (size_t)r * ldv + row, make_double2(w.x * inv, w.y * inv));
-    *y = make_double2((double)sr * inv, (double)si * inv);
+    *y = make_double2(sr * inv, si * inv);
 }
 
 // Products of the Krylov steps whose inputs the caller has packed at part +

@@ -1,9 +1,10 @@
-"""Products of 5-16 right-hand sides above the row-block sizes: column splits by
-the number of row blocks (128 rows each) and of blocks that run at once.
+"""Products through the matrix cores with split columns: splits by the number of
+row blocks (128 or 64 rows each) and of blocks that run at once.
 
-Sizes just above the row-block limits (FP64 n 4096, FP32 5792), a full turn of
-64 row blocks and the one beyond it, two turns; ragged last row block and last
-split.  Against the FP64 product of the same matrix; bound per entry: 4 sqrt(n)
+Sizes just above the row-block limits of 16 right-hand sides (FP64 n 4096, FP32
+5792), a full turn of 64 row blocks and the one beyond it, two turns; with more
+right-hand sides also both sides of n = 3072, below which a wave takes one row
+tile, and tiny systems; ragged last row block and last split.  Against the FP64 product of the same matrix; bound per entry: 4 sqrt(n)
 u (|A| |X|), u = 2^-53 or 2^-24 (a sum of n products rounds like a random walk;
 the complex product adds a few roundings).
 """
@@ -15,7 +16,7 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("N", [2049, 2753, 2901, 4096, 4097, 5999])
+@pytest.mark.parametrize("N", [20, 77, 1535, 1536, 2049, 2753, 2901, 4096, 4097, 5999])
 def test_products_split_by_row_blocks(N):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
@@ -27,7 +28,7 @@ def test_products_split_by_row_blocks(N):
         A = g.assemble(prec)[:, :g.n]
         wide = A.to(torch.complex128)
         size = A.abs().double()
-        for nrhs in (5, 16):
+        for nrhs in (5, 16, 17, 33, 64):
             X = torch.view_as_complex(torch.randn(nrhs, g.n, 2, generator=gen, device="cuda", dtype=torch.float64)).to(dt)
             err = (g.matvec(X).to(torch.complex128) - X.to(torch.complex128) @ wide).abs()
             bound = 4 * g.n ** 0.5 * u * (X.abs().double() @ size)
