@@ -147,14 +147,14 @@ bem_status bem_sizes(const bem_problem *p, int prec, int nrhs, int restart, size
 /* Step (boundary -> element tables), Sec. 4 and Sec. 7: upload the nodes and
  * the plan into geom_dev and compute on the device the element table
  * (end nodes, midpoint, tangent, left normal, length), the Gauss-Legendre
- * rule, the Gauss points of every element, the per-domain constants (eps,
- * Burton-Miller coefficients, Hankel-function tables) and the analytic
- * self terms.  geom_dev must stay alive (and unmodified) until the problem is
+ * rule, the expansion of every element's Gauss sums about its midpoint, the
+ * per-domain constants (eps, Burton-Miller coefficients, wavenumber terms)
+ * and the analytic self terms.  geom_dev must stay alive (and unmodified) until the problem is
  * destroyed or bem_geometry is called again.                                 */
 bem_status bem_geometry(bem_problem *p, void *geom_dev, size_t geom_bytes, hipStream_t stream);
 
 /* Recompute every derived device table of bem_geometry (element table, Gauss
- * rule and points, per-domain constants, self terms) from the inputs already
+ * rule, expansions, per-domain constants, self terms) from the inputs already
  * uploaded into geom_dev, with no host-to-device copy and no synchronisation.
  * Invalidates the recorded matrix (bem_assemble must run again).            */
 bem_status bem_geometry_update(bem_problem *p, hipStream_t stream);
@@ -198,8 +198,8 @@ bem_status bem_matvec(const bem_problem *p, int nrhs, const void *X_dev, size_t 
  * allocates nothing and never records timing events (bem_profile_enable does
  * not apply).  BEM_E_ARG when the product's partial sums would exceed the
  * array (FP64: about splits x nrhs x n x 16 bytes, e.g. n = 8192 with 16
- * right-hand sides in the built-in shape takes 18.9 MB); every other error as
- * bem_matvec.  All calls on one GPU share the array: calls that overlap in
+ * right-hand sides in the built-in shape takes 10.5 MB; products in one launch
+ * by row blocks need none); every other error as bem_matvec.  All calls on one GPU share the array: calls that overlap in
  * time on that GPU (other streams, other threads) race and give wrong
  * results; calls ordered on one stream are safe.  Nothing in the array needs
  * clearing between calls (every call writes what it reads).                 */

@@ -17,6 +17,7 @@
 #include <string>
 #include <vector>
 
+#include "../../include/bem.h"
 #include "internal.h"
 #include "krylov_dev.h"
 #include "launch.h"
@@ -818,8 +819,7 @@ int group_splits(int n)
 // leaves gaps (5 %; two row tiles, or FP32 sums, have twice the products in a
 // step and none).
 //
-// FP64 sums, which run through a whole split, take at least as many splits as
-// give about 1024 blocks, or 8 (two groups).
+// FP64 sums, which run through a whole split, take `least_splits` or more.
 int wide_splits(int n, int rt, bool f64, int least_splits, int most)
 {
     const int rowblocks = (n + 16 * rt * MV_WAVES - 1) / (16 * rt * MV_WAVES);
@@ -859,10 +859,10 @@ int split_limit(int n, int ng)
 // FP32 and two groups of FP64 always 2 and 1 row tiles / as here): FP32 n 1554
 // 28.8, 36.3, 45.2 / 20.0, 23.9, 27.1; 2674  33.5, 42.9, 50.5 / 31.6, 37.5, 44.9;
 // 4096  52.1, 64.8, 81.5 / 47.0, 61.6, 74.0; 10000  237, 325, 438 / 220, 294, 374;
-// 16384  533, 715, 957 / 525, 701, 892; FP64 n 1554  27.2, 37.1, 44.3 / 24.9, 30.5,
-// 35.0; 2674  54.2, 62.6, 77.4 / 42.0, 51.8, 64.8; 6000  156, 209, 272 / 145, 194,
-// 249; 10000  416, 550, 712 / 375, 506, 649; 16384  1026, 1285, 1618 / 924, 1278,
-// 1625.  Two row tiles read X half as often, but fill the chip with longer
+// 16384  533, 715, 957 / 511, 686, 886; FP64 n 1554  27.2, 37.1, 44.3 / 24.9, 30.5,
+// 34.7; 2674  54.2, 62.6, 77.4 / 44.6, 55.0, 68; 6000  156, 209, 272 / 146, 203,
+// 261; 10000  416, 550, 712 / 374, 508, 651; 16384  1026, 1285, 1618 / 919, 1278,
+// 1612.  Two row tiles read X half as often, but fill the chip with longer
 // splits: below n = 3072 one is faster (FP32, 64 right-hand sides, best
 // splits of each, 1 / 2 tiles: n 2674 44.9 / 47.4, 4096 79.4 / 74.0; FP64, 32:
 // 42.0 / 42.7, 74.6 / 72.7).  FP64 sums over 3-4 groups take one, whose registers
@@ -872,8 +872,13 @@ MvShape mfma_default(int n, int ng, bool f64)
     const int most = split_limit(n, ng);
     if (ng == 1) return f64 ? MvShape{2, 8, std::min(group_splits(n), most), 1} : MvShape{2, 4, std::min(8, most), 1};
     const int rt = n < 3072 || (f64 && ng >= 3) ? 1 : 2;
-    const int tiles = (n + 63) / 64, least = !f64 ? 1 : ng == 2 ? 8 : std::max(1, std::min((1023 + tiles) / tiles, n / 256));
-    return {rt, 4, wide_splits(n, rt, f64, least, most), 1};
+    // splits for about 1024 blocks; 8 with two groups of FP64 sums.  FP64 sums
+    // take no fewer, and no shape takes more where its partial sums and packed
+    // right-hand sides would then outgrow bem_matvec_noalloc's array.
+    const int rows = f64 ? 64 : 128, blocks = (n + rows - 1) / rows;
+    const int usual = f64 && ng == 2 ? 8 : std::max(1, std::min((1023 + blocks) / blocks, n / 256));
+    const int fit = (int)(BEM_NOALLOC_SCRATCH_BYTES / ((f64 ? sizeof(double2) : sizeof(float2)) * 16 * ng * n)) - 1;
+    return {rt, 4, wide_splits(n, rt, f64, f64 ? usual : 1, std::min(most, std::max(usual, fit))), 1};
 }
 
 // Shapes of the row-block products (in a table row: vector class rt = 1, one

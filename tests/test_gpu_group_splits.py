@@ -34,3 +34,17 @@ def test_products_split_by_row_blocks(N):
             bound = 4 * g.n ** 0.5 * u * (X.abs().double() @ size)
             worst = float((err / bound).max())
             assert worst < 1, (N, nrhs, dt, worst)
+
+
+def test_wide_products_fit_the_scratch_they_fitted():
+    """64 right-hand sides at n = 2674, 11 splits: 31.3 of the 32 MiB that a
+    product without a workspace may take (12 splits would be refused)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2312_12787_amd as P
+    P.tune_reset()
+    g = P.Problem(W.disk(1337, 2.0, 3.0 + 0.1j))
+    g.assemble(P.F64)
+    X = torch.randn(64, g.n, 2, device="cuda", dtype=torch.float64, generator=torch.Generator(device="cuda").manual_seed(1))
+    X = torch.view_as_complex(X)
+    assert torch.equal(g.matvec_noalloc(X), g.matvec(X))
