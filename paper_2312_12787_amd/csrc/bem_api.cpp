@@ -436,9 +436,10 @@ bem_status bem_create(const bem_desc* desc, bem_problem** out)
         // launch runs over them alone, one wave per item.
         struct Box {
             double x0, x1, y0, y1, hh, hmin;  // midpoints, largest and smallest half length
+            double reach;                     // the expansion's, of the longest element
         };
         auto box = [&](int e0, int cnt) {
-            Box b{1e300, -1e300, 1e300, -1e300, 0.0, 1e300};
+            Box b{1e300, -1e300, 1e300, -1e300, 0.0, 1e300, 0.0};
             for (int e = e0; e < e0 + cnt; ++e) {
                 const int a = p->elnodes[2 * e], c = p->elnodes[2 * e + 1];
                 const double ax = p->xy[2 * a], ay = p->xy[2 * a + 1], cx = p->xy[2 * c], cy = p->xy[2 * c + 1];
@@ -451,6 +452,7 @@ bem_status bem_create(const bem_desc* desc, bem_problem** out)
                 b.hh = std::max(b.hh, hh);
                 b.hmin = std::min(b.hmin, hh);
             }
+            b.reach = b.hh / bemk::EXP_X20;
             return b;
         };
         constexpr int NP = bemk::COL_CHUNK / bemk::NEAR_PART;
@@ -459,12 +461,12 @@ bem_status bem_create(const bem_desc* desc, bem_problem** out)
         for (size_t t = 0; t < p->rtiles.size(); ++t)
             for (int w = 0; w < NW; ++w) {
                 const int s0 = 64 * w, cnt = std::min(64, p->rtiles[t].count - s0);
-                rb[t * NW + w] = cnt > 0 ? box(p->rtiles[t].start + s0, cnt) : Box{1e300, 1e300, 1e300, 1e300, 0.0, 1e300};
+                rb[t * NW + w] = cnt > 0 ? box(p->rtiles[t].start + s0, cnt) : Box{1e300, 1e300, 1e300, 1e300, 0.0, 1e300, 0.0};
             }
         for (size_t c = 0; c < p->cchunks.size(); ++c)
             for (int q = 0; q < NP; ++q) {
                 const int s0 = q * bemk::NEAR_PART, cnt = std::min(bemk::NEAR_PART, p->cchunks[c].count - s0);
-                cb[c * NP + q] = cnt > 0 ? box(p->cchunks[c].start + s0, cnt) : Box{1e300, 1e300, 1e300, 1e300, 0.0, 1e300};
+                cb[c * NP + q] = cnt > 0 ? box(p->cchunks[c].start + s0, cnt) : Box{1e300, 1e300, 1e300, 1e300, 0.0, 1e300, 0.0};
             }
         for (int v = 0; v < bemk::ASM_VARIANTS; ++v) {
             p->noff[v] = (int)p->npairs.size() / 3;
@@ -474,6 +476,7 @@ bem_status bem_create(const bem_desc* desc, bem_problem** out)
                 const int d = side ? P.dr : P.dl;
                 const double ak = std::abs(p->k[d]);
                 const double rs = std::max(bemk::XS_SERIES_F64, bemk::XS_SERIES_F32) / ak;
+                const double longest = bemk::EXP_KA_MAX / ((1.0 + 1e-6) * ak), shortest = bemk::EXP_KA_MIN * (1.0 + 1e-6) / ak;
                 for (int w = 0; w < NW && 64 * w < p->rtiles[t].count; ++w)
                     for (size_t c = 0; c < p->cchunks.size(); ++c) {
                         if (p->sigma[(size_t)d * p->n_if + p->cchunks[c].iface] == 0) continue;
@@ -482,9 +485,8 @@ bem_status bem_create(const bem_desc* desc, bem_problem** out)
                             const Box &a = rb[t * NW + w], &b = cb[c * NP + q];
                             const double dx = std::max(0.0, std::max(a.x0 - b.x1, b.x0 - a.x1));
                             const double dy = std::max(0.0, std::max(a.y0 - b.y1, b.y0 - a.y1));
-                            const double lim = std::max(rs, b.hh / bemk::EXP_X20) * (1.0 + 1e-6);
-                            if (dx * dx + dy * dy < lim * lim ||
-                                ak * b.hh * (1.0 + 1e-6) > bemk::EXP_KA_MAX || ak * b.hmin < bemk::EXP_KA_MIN * (1.0 + 1e-6)) {
+                            const double lim = std::max(rs, b.reach) * (1.0 + 1e-6);
+                            if (dx * dx + dy * dy < lim * lim || b.hh > longest || b.hmin < shortest) {
                                 p->npairs.push_back(t * NW + w);
                                 p->npairs.push_back((int)c);
                                 p->npairs.push_back(q);
