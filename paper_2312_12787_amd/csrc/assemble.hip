@@ -617,8 +617,9 @@ __device__ __forceinline__ void near_part(const AsmArgs<T2>& P, int side, const 
             }
             const double rx = Ei.cx - px, ry = Ei.cy - py;
             // a lane on the diagonal may sit on its own point: any distance
-            // will do there, its sums are not used
-            const double r2 = fmax(fma(rx, rx, ry * ry), 1e-300);
+            // will do there, its sums are not used.  Elsewhere a point that
+            // coincides has to leave a non-finite entry.
+            const double d2 = fma(rx, rx, ry * ry), r2 = &Ei == &Ej ? fmax(d2, 1e-300) : d2;
             double r, rinv;
             sqrt_rsqrt(r2, r, rinv);
             cd h0, h1;
