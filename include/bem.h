@@ -251,7 +251,8 @@ typedef struct {
  * Arnoldi, and an outer FP64 iterative refinement recomputes r = b - A x
  * with FP64 accumulation (FP32 matrix for BEM_F32, FP64 matrix for
  * BEM_MIXED) until tol.  X_dev is complex128 (ldx >= n) and is overwritten.  info is a host
- * array [nrhs].  Returns BEM_E_NOCONV if any column missed tol.            */
+ * array [nrhs].  More than 64 right-hand sides are solved in blocks of 64, one
+ * after the other.  Returns BEM_E_NOCONV if any column missed tol.          */
 bem_status bem_solve(bem_problem *p, int nrhs, const void *B_dev, size_t ldb, const bem_solve_opts *opts,
                      void *X_dev, size_t ldx, void *work_dev, size_t work_bytes, bem_solve_info *info,
                      hipStream_t stream);

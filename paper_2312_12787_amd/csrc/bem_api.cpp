@@ -1472,6 +1472,40 @@ bem_status bem_solve_batch(int np, bem_problem* const* ps, const int* nrhs_v, co
         t.want.assign(nrhs, 1);
         t.rel.assign(nrhs, 1.0);
     }
+    // A pass over the matrix serves MFMA_MAX_RHS right-hand sides (a column's
+    // Krylov space does not depend on its neighbours): more are solved in
+    // blocks of that many, one after the other.
+    if (*std::max_element(nrhs_v, nrhs_v + np) > bemk::MFMA_MAX_RHS) {
+        bem_status worst = BEM_OK;
+        for (int r0 = 0;; r0 += bemk::MFMA_MAX_RHS) {
+            std::vector<bem_problem*> bp;
+            std::vector<int> bn;
+            std::vector<const void*> bB;
+            std::vector<void*> bX, bw;
+            std::vector<size_t> bldb, bldx, bbytes;
+            std::vector<bem_solve_info*> binfo;
+            for (int k = 0; k < np; ++k) {
+                if (nrhs_v[k] <= r0) continue;
+                bp.push_back(ps[k]);
+                bn.push_back(std::min(bemk::MFMA_MAX_RHS, nrhs_v[k] - r0));
+                bB.push_back(static_cast<const double2*>(B_dev[k]) + (size_t)r0 * ldb_v[k]);
+                bX.push_back(static_cast<double2*>(X_dev[k]) + (size_t)r0 * ldx_v[k]);
+                bw.push_back(work_dev[k]);
+                bldb.push_back(ldb_v[k]);
+                bldx.push_back(ldx_v[k]);
+                bbytes.push_back(work_bytes[k]);
+                binfo.push_back(info[k] + r0);
+            }
+            if (bp.empty()) break;
+            const bem_status st = bem_solve_batch((int)bp.size(), bp.data(), bn.data(), bB.data(), bldb.data(), opts,
+                                                  bX.data(), bldx.data(), bw.data(), bbytes.data(), binfo.data(), stream);
+            if (st != BEM_OK && st != BEM_E_NOCONV && st != BEM_E_NONFINITE) return st;
+            if (st == BEM_E_NONFINITE || worst == BEM_OK) worst = st;
+        }
+        if (worst == BEM_E_NONFINITE) return fail(worst, "non-finite residual");
+        if (worst == BEM_E_NOCONV) return fail(worst, "GMRES reached max_iter before tol on some right-hand side");
+        return BEM_OK;
+    }
     auto item = [&](SolveItem& t, const double2* B, size_t ldb, double2* X, size_t ldx, const std::vector<double>& tol,
                     const std::vector<int>& want, std::vector<int>& iters, std::vector<int>& conv,
                     std::vector<double>& rel, std::vector<int>& cycles) {

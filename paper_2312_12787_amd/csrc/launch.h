@@ -65,6 +65,7 @@ hipError_t launch_rhs(const char* g, const GeomLayout& L, int N, const double* a
 // Y = A X; partial holds matvec_part_elems(n, nrhs) complex values (enough for
 // any launch shape), or matvec_part_elems_shaped(shapes, types, n, nrhs) for
 // the shapes given (types as in the shape classes below).
+constexpr int MFMA_MAX_RHS = 64;  // right-hand sides per pass over A
 size_t matvec_part_elems(int n, int nrhs);
 struct MvShapes;
 // (in_place: X and Y overlap, so no product may write Y while it reads X)

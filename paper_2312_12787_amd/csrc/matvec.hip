@@ -1020,7 +1020,6 @@ MvShape pick_shape(const MvShapes* shapes, int types, int ng, int n)
     return shape_from(nullptr, types, ng, n);
 }
 
-constexpr int MFMA_MAX_RHS = 64;  // right-hand sides per pass over A
 
 template <class TA, class T, class V2>
 void launch_mfma_variant(const MvShape& c, int ng, dim3 grid, hipStream_t s, const TA* A, size_t lda, int n,
