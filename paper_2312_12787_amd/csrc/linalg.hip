@@ -1317,6 +1317,8 @@ hipError_t launch_add_f64(const double2* D, size_t ldd, int n, int nr, double2* 
 
 namespace {
 
+constexpr int MAX_GRID_Y = 65535;  // rows of blocks in a launch
+
 template <bool BIG>
 hipError_t farfield_t(const char* g, const GeomLayout& L, int N, const double2* X, size_t ldx, int nrhs,
                       const double* dirs, int ndir, double2* F, size_t ldf, hipStream_t s)
@@ -1325,13 +1327,16 @@ hipError_t farfield_t(const char* g, const GeomLayout& L, int N, const double2* 
         const int nd = std::min(ANGLE_CHUNK, ndir - d0);
         AngleChunk c{};
         for (int k = 0; k < nd; ++k) c.v[k] = dirs[d0 + k];
-#define BEM_FF_LAUNCH(D_, R_)                                                                                            \
-    hipLaunchKernelGGL((k_farfield<D_, R_, BIG>), dim3((nd + D_ - 1) / D_, (nrhs + R_ - 1) / R_), dim3(BS), 0, s, g, L, N, \
-                       X, ldx, nrhs, c, nd, F + d0, ldf)
-        if (nrhs == 1)
-            BEM_FF_LAUNCH(2, 1);
-        else
-            BEM_FF_LAUNCH(3, 4);
+#define BEM_FF_LAUNCH(D_, R_)                                                                                           \
+    hipLaunchKernelGGL((k_farfield<D_, R_, BIG>), dim3((nd + D_ - 1) / D_, (nr + R_ - 1) / R_), dim3(BS), 0, s, g, L, N, \
+                       X + r0 * ldx, ldx, nr, c, nd, F + r0 * ldf + d0, ldf)
+        for (size_t r0 = 0; r0 < (size_t)nrhs; r0 += (size_t)MAX_GRID_Y * 4) {
+            const int nr = (int)std::min((size_t)MAX_GRID_Y * 4, (size_t)nrhs - r0);
+            if (nr == 1)
+                BEM_FF_LAUNCH(2, 1);
+            else
+                BEM_FF_LAUNCH(3, 4);
+        }
 #undef BEM_FF_LAUNCH
     }
     return hipGetLastError();
