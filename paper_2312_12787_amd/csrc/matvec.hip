@@ -227,8 +227,7 @@ __global__ __launch_bounds__(BS, mfma_min_waves(sizeof(T), RT, NG)) void k_matve
         rok[t] = row < n;
         ap[t] = A + (rok[t] ? row : 0);
     }
-    const int c0 = blockIdx.y * cps;
-    const int c1 = min(n, c0 + cps);
+    const int first = blockIdx.y * cps, end = min(n, first + cps);
     acc rr0[NG][RT], rr1[NG][RT], ii0[NG][RT], ii1[NG][RT];
 #pragma unroll
     for (int g = 0; g < NG; ++g)
@@ -238,9 +237,13 @@ __global__ __launch_bounds__(BS, mfma_min_waves(sizeof(T), RT, NG)) void k_matve
     // then added to totals, so that their rounding does not grow with the
     // columns of a split (n = 16384, 64 right-hand sides, largest error against
     // FP64 sums 1.1e-6 with 8 splits, 2.2e-6 with the faster 2, 4.4e-7 folded).
-    // The other shapes have no registers to spare for totals (FP64, one group:
-    // 172 -> 188 us at n = 8192); their splits are not fewer than mfma_default
-    // says.
+    // The other shapes have no registers to spare for totals.  The FP64 sums of
+    // one group, whose splits group_splits chooses by how they fill the chip, run
+    // over an eighth of the columns and are then added to totals in LDS (rms
+    // error, kite, 16 random right-hand sides, so / over whole splits: n = 8192
+    // 3.2e-14 / 4.6e-14, 16384 8.5e-14 / 1.7e-13).  The pipeline starts anew for
+    // each part: n = 8192 171 -> 174 us (totals in registers 188, as more partial
+    // sums in memory 189, both what eight splits take).
     constexpr int FOLD = sizeof(T) == 4 && NG >= 2 ? 256 : 0;
     acc sum[4][FOLD ? NG : 1][FOLD ? RT : 1];
     if (FOLD)
@@ -259,6 +262,20 @@ __global__ __launch_bounds__(BS, mfma_min_waves(sizeof(T), RT, NG)) void k_matve
                 if (!G3) sum[3][g][t] += ii1[g][t];
                 rr0[g][t] = rr1[g][t] = ii0[g][t] = ii1[g][t] = acc{0, 0, 0, 0};
             }
+    };
+    constexpr bool PARTS = sizeof(T) == 8 && NG == 1;
+    __shared__ V2 total[PARTS ? RT : 1][PARTS ? 4 : 1][PARTS ? BS : 1];  // a lane reads and writes its own
+    // the sum of result j of a row tile
+    auto value = [&](int g, int t, int j) {
+        V2 v;
+        if (G3) {
+            v.x = rr0[g][t][j] - rr1[g][t][j];
+            v.y = ii0[g][t][j] - rr0[g][t][j] - rr1[g][t][j];
+        } else {
+            v.x = rr0[g][t][j] + rr1[g][t][j];
+            v.y = ii0[g][t][j] + ii1[g][t][j];
+        }
+        return v;
     };
     // one 16 x 4 tile of A (per row tile) against 4 x 16 NG of X
     auto step = [&](const T (&ar)[RT], const T (&ai)[RT], const T (&xr)[NG], const T (&xi)[NG]) {
@@ -312,118 +329,140 @@ __global__ __launch_bounds__(BS, mfma_min_waves(sizeof(T), RT, NG)) void k_matve
             step(ar, ai, xr, xi);
         }
     };
-    int c = c0;
-    if constexpr (!PIPE) {
-        // rotating slots: slot u of the next 4U columns is loaded as soon as
-        // slot u of the current ones has gone into the matrix cores, so a
-        // wave keeps loads in flight without a second buffer; the scheduling
-        // barriers keep that order (the compiler otherwise moves the loads
-        // next to their uses and waits for all of them).  Measured on gfx950,
-        // kite of 16384 elements, 64 right-hand sides: FP32 product 3.82 ->
-        // 3.50 ms at the same register count (two waves per SIMD)
-        if (c + 4 * U <= c1) {
+    // (a multiple of every 4U)
+    const int cols = PARTS ? ((n + 7) / 8 + 31) / 32 * 32 : cps;
+    int c0 = first;
+    do {  // once at least: a split without columns leaves zeros
+        const int c1 = min(end, c0 + cols);
+        int c = c0;
+        if constexpr (!PIPE) {
+            // rotating slots: slot u of the next 4U columns is loaded as soon as
+            // slot u of the current ones has gone into the matrix cores, so a
+            // wave keeps loads in flight without a second buffer; the scheduling
+            // barriers keep that order (the compiler otherwise moves the loads
+            // next to their uses and waits for all of them).  Measured on gfx950,
+            // kite of 16384 elements, 64 right-hand sides: FP32 product 3.82 ->
+            // 3.50 ms at the same register count (two waves per SIMD)
+            if (c + 4 * U <= c1) {
+                TA a[U][RT];
+                V2 x[U][NG];
+                load(a, x, c);
+                for (;;) {
+                    const int cn = c + 4 * U;
+                    const bool more = cn + 4 * U <= c1;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        T ar[RT], ai[RT], xr[NG], xi[NG];
+#pragma unroll
+                        for (int t = 0; t < RT; ++t) {
+                            ar[t] = rok[t] ? (T)a[u][t].x : T(0);
+                            ai[t] = rok[t] ? (T)a[u][t].y : T(0);
+                        }
+#pragma unroll
+                        for (int g = 0; g < NG; ++g) {
+                            xr[g] = x[u][g].x;
+                            xi[g] = x[u][g].y;
+                        }
+                        step(ar, ai, xr, xi);
+                        __builtin_amdgcn_sched_barrier(0);
+                        // unconditional (the last pass reloads its own columns):
+                        // a load under a branch makes the compiler wait for every
+                        // load in flight before the next slot
+                        const int col = (more ? cn : c) + 4 * u + lk;
+#pragma unroll
+                        for (int g = 0; g < NG; ++g) x[u][g] = XT[(size_t)col * XW + 16 * g + lr];
+#pragma unroll
+                        for (int t = 0; t < RT; ++t) a[u][t] = ld_stream(ap[t] + (size_t)col * lda);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    c = cn;
+                    if constexpr (FOLD != 0)
+                        if ((c - c0) % FOLD == 0) fold();
+                    if (!more) break;
+                }
+            }
+        } else if (c + 4 * U <= c1) {
             TA a[U][RT];
             V2 x[U][NG];
             load(a, x, c);
             for (;;) {
                 const int cn = c + 4 * U;
-                const bool more = cn + 4 * U <= c1;
+                if (cn + 4 * U > c1) {
+                    compute(a, x);
+                    c = cn;
+                    break;
+                }
+                TA an[U][RT];
+                V2 xn[U][NG];
+                load(an, xn, cn);
+                compute(a, x);
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    T ar[RT], ai[RT], xr[NG], xi[NG];
 #pragma unroll
-                    for (int t = 0; t < RT; ++t) {
-                        ar[t] = rok[t] ? (T)a[u][t].x : T(0);
-                        ai[t] = rok[t] ? (T)a[u][t].y : T(0);
-                    }
+                    for (int t = 0; t < RT; ++t) a[u][t] = an[u][t];
 #pragma unroll
-                    for (int g = 0; g < NG; ++g) {
-                        xr[g] = x[u][g].x;
-                        xi[g] = x[u][g].y;
-                    }
-                    step(ar, ai, xr, xi);
-                    __builtin_amdgcn_sched_barrier(0);
-                    // unconditional (the last pass reloads its own columns):
-                    // a load under a branch makes the compiler wait for every
-                    // load in flight before the next slot
-                    const int col = (more ? cn : c) + 4 * u + lk;
-#pragma unroll
-                    for (int g = 0; g < NG; ++g) x[u][g] = XT[(size_t)col * XW + 16 * g + lr];
-#pragma unroll
-                    for (int t = 0; t < RT; ++t) a[u][t] = ld_stream(ap[t] + (size_t)col * lda);
-                    __builtin_amdgcn_sched_barrier(0);
+                    for (int g = 0; g < NG; ++g) x[u][g] = xn[u][g];
                 }
                 c = cn;
-                if constexpr (FOLD != 0)
-                    if ((c - c0) % FOLD == 0) fold();
-                if (!more) break;
             }
         }
-    } else if (c + 4 * U <= c1) {
-        TA a[U][RT];
-        V2 x[U][NG];
-        load(a, x, c);
-        for (;;) {
-            const int cn = c + 4 * U;
-            if (cn + 4 * U > c1) {
-                compute(a, x);
-                c = cn;
-                break;
+        for (; c < c1; c += 4) {
+            const int col = c + lk;
+            const bool ok = col < c1;
+            T ar[RT], ai[RT], xr[NG], xi[NG];
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                xr[g] = T(0);
+                xi[g] = T(0);
+                if (ok) {
+                    const V2 x = XT[(size_t)col * XW + 16 * g + lr];
+                    xr[g] = x.x;
+                    xi[g] = x.y;
+                }
             }
-            TA an[U][RT];
-            V2 xn[U][NG];
-            load(an, xn, cn);
-            compute(a, x);
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-#pragma unroll
-                for (int t = 0; t < RT; ++t) a[u][t] = an[u][t];
-#pragma unroll
-                for (int g = 0; g < NG; ++g) x[u][g] = xn[u][g];
-            }
-            c = cn;
-            if constexpr (FOLD != 0)
-                if ((c - c0) % FOLD == 0) fold();
-        }
-    }
-    for (; c < c1; c += 4) {
-        const int col = c + lk;
-        const bool ok = col < c1;
-        T ar[RT], ai[RT], xr[NG], xi[NG];
-#pragma unroll
-        for (int g = 0; g < NG; ++g) {
-            xr[g] = T(0);
-            xi[g] = T(0);
-            if (ok) {
-                const V2 x = XT[(size_t)col * XW + 16 * g + lr];
-                xr[g] = x.x;
-                xi[g] = x.y;
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < RT; ++t) {
-            ar[t] = T(0);
-            ai[t] = T(0);
-            if (ok && rok[t]) {
-                const TA a = ld_stream(ap[t] + (size_t)col * lda);
-                ar[t] = (T)a.x;
-                ai[t] = (T)a.y;
-            }
-        }
-        step(ar, ai, xr, xi);
-    }
-    if constexpr (FOLD != 0) {
-        fold();
-#pragma unroll
-        for (int g = 0; g < NG; ++g)
 #pragma unroll
             for (int t = 0; t < RT; ++t) {
-                rr0[g][t] = sum[0][g][t];
-                rr1[g][t] = sum[1][g][t];
-                ii0[g][t] = sum[2][g][t];
-                ii1[g][t] = sum[3][g][t];
+                ar[t] = T(0);
+                ai[t] = T(0);
+                if (ok && rok[t]) {
+                    const TA a = ld_stream(ap[t] + (size_t)col * lda);
+                    ar[t] = (T)a.x;
+                    ai[t] = (T)a.y;
+                }
             }
-    }
+            step(ar, ai, xr, xi);
+        }
+        if constexpr (FOLD != 0) {
+            fold();
+#pragma unroll
+            for (int g = 0; g < NG; ++g)
+#pragma unroll
+                for (int t = 0; t < RT; ++t) {
+                    rr0[g][t] = sum[0][g][t];
+                    rr1[g][t] = sum[1][g][t];
+                    ii0[g][t] = sum[2][g][t];
+                    ii1[g][t] = sum[3][g][t];
+                }
+        }
+        if (PARTS && end - first > cols) {
+#pragma unroll
+            for (int t = 0; t < RT; ++t) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    V2 v = value(0, t, j);
+                    if (c0 != first) {
+                        const V2 before = total[t][j][threadIdx.x];
+                        v.x += before.x;
+                        v.y += before.y;
+                    }
+                    total[t][j][threadIdx.x] = v;
+                }
+                rr0[0][t] = rr1[0][t] = ii0[0][t] = ii1[0][t] = acc{0, 0, 0, 0};
+            }
+        }
+        c0 += cols;
+    } while (PARTS && c0 < end);
+    const bool totals = PARTS && end - first > cols;
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
         const int r = 16 * g + lr;
@@ -433,17 +472,8 @@ __global__ __launch_bounds__(BS, mfma_min_waves(sizeof(T), RT, NG)) void k_matve
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int row = row0 + 16 * t + M::out_row(lk, j);
-                if (row < n) {
-                    V2 v;
-                    if (G3) {
-                        v.x = rr0[g][t][j] - rr1[g][t][j];
-                        v.y = ii0[g][t][j] - rr0[g][t][j] - rr1[g][t][j];
-                    } else {
-                        v.x = rr0[g][t][j] + rr1[g][t][j];
-                        v.y = ii0[g][t][j] + ii1[g][t][j];
-                    }
-                    part[((size_t)blockIdx.y * nrhs + r) * n + row] = v;
-                }
+                if (row < n)
+                    part[((size_t)blockIdx.y * nrhs + r) * n + row] = totals ? total[t][j][threadIdx.x] : value(g, t, j);
             }
     }
 }

@@ -3,9 +3,9 @@
 Its column splits follow the number of row blocks, down to two at n = 16384.
 Whatever they are, its sums may not run longer than those of eight splits: the
 rms error against extended precision, over 512 rows, is compared with that of
-eight splits (the same partial sums, so the two differ by the order in which
-eight numbers are added; bound 1 % for that, where twice and four times longer
-sums show 2.4 % and 7 %).
+eight splits (sums over an eighth of the columns in both, which differ by the
+order in which eight numbers are added; bound 1 % for that, where sums over half
+of the columns show twice the error).
 """
 import numpy as np
 import pytest
