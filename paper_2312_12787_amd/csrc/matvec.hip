@@ -777,12 +777,15 @@ constexpr size_t ROW_X_BYTES = 128 * 1024;
 bool row_fits(int n, int nr, size_t value_bytes) { return nr > 4 || (size_t)n * nr * value_bytes <= ROW_X_BYTES; }
 
 // A row-block product of up to 16 right-hand sides.  16 waves per workgroup
-// where the rows alone leave the chip's CUs less than one workgroup each.
+// where the rows alone leave the chip's CUs less than one workgroup each, and in
+// the vector form always: a lane sums 1/64 of the columns then, as much as the
+// 64 splits of the split form (FP32, 3 right-hand sides, n = 4800, 8 / 16 waves:
+// rms error 4.2e-6 / 3.0e-6, 59 / 51 us).
 template <class TA, class TX, class ACC, bool PACKED, int MODE, class O>
 void launch_rowblock(const TA* A, size_t lda, int n, const TX* X, size_t ldx, int nr, const O& o, hipStream_t s)
 {
     using S = decltype(ACC{}.x);
-    const int tiles = (n + 15) / 16, nw = tiles <= 256 ? 16 : 8;
+    const int tiles = (n + 15) / 16, nw = tiles <= 256 || nr <= 4 ? 16 : 8;
     const int blocks = (tiles + 7) / 8 * 8;  // see row_tile
     constexpr int U = sizeof(TA) == 16 || sizeof(S) == 8 ? 4 : 8;
     const size_t xlds = (size_t)n * nr * sizeof(ACC);
