@@ -149,7 +149,8 @@ __device__ __forceinline__ void setup_domain(char* g, const GeomLayout& L, int d
 // ---------------------------------------------------------------------------
 // Self term of the single-layer operator on a flat element at its midpoint
 // (Sec. 7, the weak singularity): S_ii = (i/(2k)) int_0^{kh/2} H0(t) dt, the
-// integral taken term by term from the ascending series of J0 and Y0.
+// integral taken term by term from the ascending series of J0 and Y0 (long
+// elements: int_h0_long).
 // One lane per (element, domain on either side of it).
 // ---------------------------------------------------------------------------
 __device__ cd int_h0(cd z)
@@ -178,6 +179,49 @@ __device__ cd int_h0(cd z)
     return {sj.re - iy.im, sj.im + iy.re};  // int J0 + i int Y0
 }
 
+// The same for |z| > 4, which only elements longer than 1.2 wavelengths reach and
+// where the series loses digits to cancellation (|z| = 6: 3e-15, 14: 3e-12).  Up
+// to |z| = 40 the rest of the ray in steps of at most 2 by the 16-point rule.
+// Beyond, from int_0^inf H0 = 1, 1 minus the integral of the asymptotic form
+//   H0(t) = sqrt(2/(pi t)) e^{i(t - pi/4)} sum_m c_m t^{-m},  c_m = c_{m-1} (2m - 1)^2 / (8 i m),
+// term by term: its antiderivative that vanishes at i inf has, in place of c_m, d_m with
+//   i d_m - (m - 1/2) d_{m-1} = c_m
+// (the terms fall to about e^{-|z|} before they grow).
+__device__ cd int_h0_long(cd z)
+{
+    const double b = hypot(z.re, z.im);
+    const cd e = cscale(z, 1.0 / b);
+    if (b <= 40.0) {
+        WaveConst W;
+        build_wave(e, W);
+        const int steps = (int)ceil(0.5 * (b - 4.0));
+        const double half = 0.5 * (b - 4.0) / steps;
+        cd sum = {0.0, 0.0};
+        for (int i = 0; i < 16 * steps; ++i) {
+            const double r = 4.0 + half * (2 * (i / 16) + 1 + GAUSS_X[15][i % 16]);
+            cd h0, h1;
+            hankel01<true, true>(W, r, r * r, 1.0 / r, sqrt(1.0 / r), h0, h1);
+            const double w = half * GAUSS_W[15][i % 16];
+            sum = {fma(w, h0.re, sum.re), fma(w, h0.im, sum.im)};
+        }
+        return cadd(int_h0(cscale(e, 4.0)), cmul(e, sum));
+    }
+    const cd iz = cdiv({1.0, 0.0}, z);
+    cd c = {1.0, 0.0}, d = {0.0, -1.0}, p = {1.0, 0.0}, sum = d;  // p = z^{-m}
+    for (int m = 1; m <= 40; ++m) {
+        const double f = (2.0 * m - 1.0) * (2.0 * m - 1.0) / (8.0 * m);
+        c = {f * c.im, -f * c.re};
+        const cd t = {fma(m - 0.5, d.re, c.re), fma(m - 0.5, d.im, c.im)};  // i d_m
+        d = {t.im, -t.re};
+        p = cmul(p, iz);
+        sum = cadd(sum, cmul(d, p));
+    }
+    double sn, cs;
+    sincos(z.re - 0.25 * PI, &sn, &cs);
+    const cd amp = cmul(csqrt_(cscale(iz, 2.0 / PI)), cscale({cs, sn}, exp(-z.im)));
+    return cadd({1.0, 0.0}, cmul(amp, sum));
+}
+
 __device__ __forceinline__ void setup_self(char* g, const GeomLayout& L, int N, int e, int side)
 {
     const double2* nodes = tab<double2>(g, L.nodes);
@@ -187,7 +231,8 @@ __device__ __forceinline__ void setup_self(char* g, const GeomLayout& L, int N, 
     const DomIn* in = tab<DomIn>(g, L.dom_in);
     const cd k = {in[d].k[0], in[d].k[1]};
     const double dx = nodes[ab.y].x - nodes[ab.x].x, dy = nodes[ab.y].y - nodes[ab.x].y;
-    const cd I = int_h0(cscale(k, 0.5 * sqrt(dx * dx + dy * dy)));
+    const cd z = cscale(k, 0.5 * sqrt(dx * dx + dy * dy));
+    const cd I = hypot(z.re, z.im) > 4.0 ? int_h0_long(z) : int_h0(z);
     const cd pre = cdiv({0.0, 0.5}, k);  // i / (2k)
     const cd s = cmul(pre, I);
     tabw<double2>(g, L.self)[(size_t)d * N + e] = make_double2(s.re, s.im);
