@@ -44,6 +44,8 @@ __device__ __forceinline__ double expansion_limit(double a, double ak, double x,
     return ka >= EXP_KA_MIN && ka <= kamax ? v * v : __longlong_as_double(0x7ff0000000000000ll);
 }
 
+__device__ __forceinline__ bool expanded(double close2) { return close2 < __longlong_as_double(0x7ff0000000000000ll); }
+
 // ---------------------------------------------------------------------------
 // Element table (Secs. 4, 7).
 // ---------------------------------------------------------------------------
@@ -70,7 +72,8 @@ __device__ __forceinline__ void setup_element(char* g, const GeomLayout& L, int 
     const DomIn* in = tab<DomIn>(g, L.dom_in);
     for (int side = 0; side < 2; ++side) {
         const int d = side ? P.dr : P.dl;
-        E.close2[side] = expansion_limit(0.5 * E.h, hypot(in[d].k[0], in[d].k[1]), EXP_X20, EXP_KA_MAX);
+        const double lim = expansion_limit(0.5 * E.h, hypot(in[d].k[0], in[d].k[1]), EXP_X20, EXP_KA_MAX);
+        E.close2[side] = expanded(lim) ? lim : 6.25 * E.h * E.h;
     }
     tabw<ElemRec>(g, L.elem)[e] = E;
 }
@@ -297,6 +300,8 @@ __device__ __forceinline__ void setup_expansion(char* g, const GeomLayout& L, in
         H->lim32_4 = lim(EXP32_X4, EXP32_KA4);
         H->lim32_6 = lim(EXP32_X6, EXP32_KA6);
         H->lim32_8 = lim(EXP32_X8, EXP32_KA8);
+        H->take64 = expanded(H->close2) ? H->near64 : sq(HANKEL_XS_F64 / ak + a);
+        H->take32 = expanded(H->close2) ? H->near32 : sq(HANKEL_XS_F32 / ak + a);
     }
     const int cw = L.exp_cplx ? 2 : 1;  // doubles per coefficient
     double* c = rec + EXP_HEAD + cw * exp_pos(m);
@@ -372,9 +377,9 @@ __global__ __launch_bounds__(SETUP_BS) void k_setup(char* g, GeomLayout L, int N
 //                           A[row, w_j] = -sigma eps S + c (eps delta/2 - sigma eps D*)
 //
 // All four sums come from ONE evaluation of H0 and H1, at the element's
-// midpoint (expansion_dev.h).  A few element lengths away, or for elements
-// longer than about 0.8 wavelengths, the Gauss points are evaluated one by
-// one.
+// midpoint (expansion_dev.h).  Closer than a few element lengths, or for
+// elements longer than about 0.8 wavelengths, the Gauss points are evaluated one
+// by one.
 // ---------------------------------------------------------------------------
 
 // Per-block combination constants of one equation block (see the entries above).
@@ -556,6 +561,83 @@ __global__ __launch_bounds__(ROW_TILE, FAR_WAVES) void k_assemble_far(const AsmA
 }
 
 // ---------------------------------------------------------------------------
+// Elements without expansion (|k| h/2 beyond EXP_KA_MAX or below EXP_KA_MIN),
+// for rows whose points are all at least XS/|k| from theirs: point by point, one
+// lane per row, over the far launch's grid; launched only where a domain has such
+// elements (a good conductor's |k| is large against any mesh of the host).  An
+// end point's value serves both elements that meet there.  Bound by FP64 VALU
+// issue, q + 1 Hankel evaluations per pair.  As "close" pairs of the near launch,
+// an LDS round per 3 to 6 of them, 4096 elements at |k| h/2 = 4 took 3.81 ms in
+// FP64 and in FP32, now 1.93 and 1.31.
+// ---------------------------------------------------------------------------
+template <bool CPLX, bool BM, class T2>
+__global__ __launch_bounds__(ROW_TILE, NEAR_WAVES) void k_assemble_points(const AsmArgs<T2> P, int side,
+                                                                          const int* __restrict__ tiles, int per)
+{
+    constexpr bool LOW = sizeof(T2) == sizeof(float2);
+    const Tile rt = tab<Tile>(P.g, P.L.rtiles)[tiles[blockIdx.x]];
+    const int parts = COL_CHUNK / per, li = threadIdx.x;
+    const Tile cc = tab<Tile>(P.g, P.L.cchunks)[blockIdx.y / parts];
+    const int j0 = blockIdx.y % parts * per, j1 = min(j0 + per, cc.count);
+    if (li >= rt.count || j0 >= j1) return;
+    const IfacePlan F = tab<IfacePlan>(P.g, P.L.iface)[rt.iface];
+    const int d = side ? F.dr : F.dl;
+    const int sg = tab<int>(P.g, P.L.sigma)[d * P.n_if + cc.iface];
+    if (sg == 0) return;
+    const int i = rt.start + li;
+    const size_t row = (size_t)((side ? F.row_r : F.row_l) + (i - F.off));
+    const int jside = tab<IfacePlan>(P.g, P.L.iface)[cc.iface].dr == d ? 1 : 0;
+    const WaveConst W = scalar_copy(tab<WaveConst>(P.g, P.L.wave) + d);
+    const BlockConst B = block_const<BM>(tab<DomConst>(P.g, P.L.dom)[d], sg);
+    const ElemRec* Ei = tab<ElemRec>(P.g, P.L.elem) + i;
+    const double xi = Ei->cx, yi = Ei->cy, tix = Ei->tx, tiy = Ei->ty;
+    ScalarPtr gl = (ScalarPtr)tab<double>(P.g, P.L.gl);
+    auto hankel = [&](double rx, double ry, cd& h0, cd& h1) {
+        double r, rinv;
+        sqrt_rsqrt(fma(rx, rx, ry * ry), r, rinv);
+        hankel_asym<CPLX, LOW>(W, r, 0.0, rinv, rsqrt_nr(r), h0, h1);
+        return rinv;
+    };
+    auto end_value = [&](double px, double py) {
+        const double rx = xi - px, ry = yi - py;
+        cd h0, h1;
+        const double rinv = hankel(rx, ry, h0, h1);
+        return cscale(h1, fma(rx, tix, ry * tiy) * rinv);
+    };
+    cd Ea = {0.0, 0.0};
+    int prev = -2;  // element whose second end point Ea belongs to
+    for (int jj = j0; jj < j1; ++jj) {
+        const int j = cc.start + jj;
+        ScalarPtr rec = (ScalarPtr)(tab<double>(P.g, P.L.expn) + ((size_t)jside * P.N + j) * P.L.exp_stride);
+        if (expanded(rec[EXP_H_CLOSE])) continue;
+        const ElemRec Ej = scalar_copy(tab<ElemRec>(P.g, P.L.elem) + j);
+        const double r2 = pair_r2(xi - Ej.cx, yi - Ej.cy);
+        if (__builtin_amdgcn_ballot_w64(r2 < rec[LOW ? EXP_H_TAKE32 : EXP_H_TAKE64]) != 0) continue;
+        cd S = {0.0, 0.0}, D = {0.0, 0.0}, Ds = {0.0, 0.0};
+        for (int g = 0; g < P.q; ++g) {
+            const double s = 0.5 * Ej.h * gl[g], w = 0.5 * Ej.h * gl[QMAX + g];
+            const double rx = xi - fma(s, Ej.tx, Ej.cx), ry = yi - fma(s, Ej.ty, Ej.cy);
+            cd h0, h1;
+            const double wr = w * hankel(rx, ry, h0, h1);
+            add_scaled(S, w, 1.0, h0);
+            add_scaled(D, wr, fma(rx, Ej.nx, ry * Ej.ny), h1);
+            if (BM) add_scaled(Ds, wr, fma(ry, tix, -rx * tiy), h1);
+        }
+        cd au = cmul(B.cD, D), aw = cmul(B.cS, S);
+        if (BM) {
+            if (prev != j - 1) Ea = end_value(Ej.ax, Ej.ay);
+            const cd Eb = end_value(Ej.bx, Ej.by);
+            au = cadd(au, cadd(cscale(cmul(B.cNS, S), fma(tix, Ej.tx, tiy * Ej.ty)),
+                               cmul(B.cNE, {Eb.re - Ea.re, Eb.im - Ea.im})));
+            aw = cadd(aw, cmul(B.cDs, Ds));
+            Ea = Eb;
+            prev = j;
+        }
+        store_entry(P.A, P.lda, P.A32, row, j, P.N, au, aw);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Near launch: the elements the far launch leaves, over the host's list of
 // (row tile and its 64-row wave, column chunk, part of NEAR_PART elements)
 // items that may hold one; one wave, one workgroup per `per` elements of an
@@ -612,7 +694,7 @@ __device__ __forceinline__ void near_part(const AsmArgs<T2>& P, int side, const 
             const double cx = Ej[E_CX], cy = Ej[E_CY], tx = Ej[E_TX], ty = Ej[E_TY];
             const double rx = xi - cx, ry = yi - cy;
             const double r2 = pair_r2(rx, ry);
-            if (__builtin_amdgcn_ballot_w64(valid && r2 < rec[LOW ? EXP_H_NEAR32 : EXP_H_NEAR64]) == 0) continue;
+            if (__builtin_amdgcn_ballot_w64(valid && r2 < rec[LOW ? EXP_H_TAKE32 : EXP_H_TAKE64]) == 0) continue;
             const bool close = valid && r2 < rec[EXP_H_CLOSE];
             const bool rest = valid && !close;
             if (__builtin_amdgcn_ballot_w64(rest) != 0) {
@@ -810,9 +892,23 @@ int elements_per_wave(int most, int least, long long waves, long long wanted)
 // write disjoint rows, so they alternate over the two streams.
 template <class T2>
 hipError_t launch_variants(AsmArgs<T2> P, int n_cchunks, const int* const* lists, const int* counts,
-                           const int* const* pairs, const int* pair_counts, hipStream_t s0, hipStream_t s1)
+                           const int* const* pairs, const int* pair_counts, const int* points, hipStream_t s0,
+                           hipStream_t s1)
 {
     const int per = elements_per_wave(COL_CHUNK, 2, (long long)((P.N + 63) / 64) * n_cchunks, 4096);
+    auto launch_points = [&](int v, hipStream_t s) {
+        const dim3 grid(counts[v], n_cchunks * (COL_CHUNK / per));
+        const int side = v >> 2 & 1;
+#define BEM_ASM_POINTS(C_, B_) \
+    hipLaunchKernelGGL((k_assemble_points<C_, B_, T2>), grid, dim3(ROW_TILE), 0, s, P, side, lists[v], per)
+        switch (v & 3) {
+            case 0: BEM_ASM_POINTS(false, false); break;
+            case 1: BEM_ASM_POINTS(true, false); break;
+            case 2: BEM_ASM_POINTS(false, true); break;
+            default: BEM_ASM_POINTS(true, true);
+        }
+#undef BEM_ASM_POINTS
+    };
     if (assemble_one_launch(P.N)) {
         AsmRanges R{};
         int k = 0, end = 0;
@@ -834,6 +930,8 @@ hipError_t launch_variants(AsmArgs<T2> P, int n_cchunks, const int* const* lists
             hipLaunchKernelGGL((k_assemble_all<true, T2>), dim3(end), dim3(64), 0, s0, P, R);
         else
             hipLaunchKernelGGL((k_assemble_all<false, T2>), dim3(end), dim3(64), 0, s0, P, R);
+        for (int v = 0; v < ASM_VARIANTS; ++v)
+            if (counts[v] > 0 && points[v]) launch_points(v, s0);
         return hipGetLastError();
     }
     int k = 0;
@@ -855,6 +953,7 @@ hipError_t launch_variants(AsmArgs<T2> P, int n_cchunks, const int* const* lists
         BEM_ASM_LAUNCH(false, true)
         BEM_ASM_LAUNCH(true, true)
 #undef BEM_ASM_LAUNCH
+        if (points[v]) launch_points(v, s);
     }
     return hipGetLastError();
 }
@@ -865,19 +964,20 @@ bool assemble_one_launch(int N) { return 2 * (long long)N * N <= 1 << 24; }
 
 hipError_t launch_assemble_f64(const char* g, const GeomLayout& L, int N, int n_if, int n_cchunks, int q,
                                const int* const* lists, const int* counts, const int* const* pairs,
-                               const int* pair_counts, double2* A, size_t lda, float2* A32, hipStream_t s,
-                               hipStream_t s1)
+                               const int* pair_counts, const int* points, double2* A, size_t lda, float2* A32,
+                               hipStream_t s, hipStream_t s1)
 {
     return launch_variants(AsmArgs<double2>{g, L, N, n_if, q, A, A32, lda}, n_cchunks, lists, counts, pairs,
-                           pair_counts, s, s1);
+                           pair_counts, points, s, s1);
 }
 
 hipError_t launch_assemble_f32(const char* g, const GeomLayout& L, int N, int n_if, int n_cchunks, int q,
                                const int* const* lists, const int* counts, const int* const* pairs,
-                               const int* pair_counts, float2* A, size_t lda, hipStream_t s, hipStream_t s1)
+                               const int* pair_counts, const int* points, float2* A, size_t lda, hipStream_t s,
+                               hipStream_t s1)
 {
     return launch_variants(AsmArgs<float2>{g, L, N, n_if, q, A, nullptr, lda}, n_cchunks, lists, counts, pairs,
-                           pair_counts, s, s1);
+                           pair_counts, points, s, s1);
 }
 
 }  // namespace bemk

@@ -106,6 +106,9 @@ struct bem_problem {
     int vcount[bemk::ASM_VARIANTS] = {0}, voff[bemk::ASM_VARIANTS] = {0};
     std::vector<int> npairs;  // (row tile * 4 + wave, column chunk, part) items that may hold near pairs, by variant
     int ncount[bemk::ASM_VARIANTS] = {0}, noff[bemk::ASM_VARIANTS] = {0};
+    // 1: some element of the variant's domains, of the domain has no expansion
+    int vpoints[bemk::ASM_VARIANTS] = {0};
+    std::vector<int> dom_points;
     std::vector<int> elif;          // interface of each element
     std::vector<int> elnodes;       // (a, b) node indices per element
     bemk::DomIn dummy{};
@@ -430,10 +433,11 @@ bem_status bem_create(const bem_desc* desc, bem_problem** out)
         // elements of the chunk -- whose bounding boxes (collocation points,
         // element midpoints) come within the near radius of the part in the
         // rows' domain (relative margin 1e-6): the series radius XS/|k_d| or
-        // the expansion's reach of the part's longest element, or any distance
-        // where an element is too long or too short for the expansion.  Only
-        // these can hold an element that the far launch leaves, so the near
-        // launch runs over them alone, one wave per item.
+        // the expansion's reach of the part's longest element, and half that
+        // element's length more than the series radius where one is too long or
+        // too short for the expansion.  Only these can hold an element that the
+        // far launch (and that of the elements without expansion) leaves, so the
+        // near launch runs over them alone, one wave per item.
         struct Box {
             double x0, x1, y0, y1, hh, hmin;  // midpoints, largest and smallest half length
             double reach;                     // the expansion's, of the longest element
@@ -468,6 +472,7 @@ bem_status bem_create(const bem_desc* desc, bem_problem** out)
                 const int s0 = q * bemk::NEAR_PART, cnt = std::min(bemk::NEAR_PART, p->cchunks[c].count - s0);
                 cb[c * NP + q] = cnt > 0 ? box(p->cchunks[c].start + s0, cnt) : Box{1e300, 1e300, 1e300, 1e300, 0.0, 1e300, 0.0};
             }
+        p->dom_points.assign((size_t)p->n_dom, 0);
         for (int v = 0; v < bemk::ASM_VARIANTS; ++v) {
             p->noff[v] = (int)p->npairs.size() / 3;
             const int side = v >> 2 & 1;
@@ -485,8 +490,11 @@ bem_status bem_create(const bem_desc* desc, bem_problem** out)
                             const Box &a = rb[t * NW + w], &b = cb[c * NP + q];
                             const double dx = std::max(0.0, std::max(a.x0 - b.x1, b.x0 - a.x1));
                             const double dy = std::max(0.0, std::max(a.y0 - b.y1, b.y0 - a.y1));
-                            const double lim = std::max(rs, b.reach) * (1.0 + 1e-6);
-                            if (dx * dx + dy * dy < lim * lim || b.hh > longest || b.hmin < shortest) {
+                            const bool points = b.hh > longest || b.hmin < shortest;
+                            p->vpoints[v] |= points;
+                            p->dom_points[d] |= points;
+                            const double lim = std::max(points ? rs + b.hh : rs, b.reach) * (1.0 + 1e-6);
+                            if (dx * dx + dy * dy < lim * lim) {
                                 p->npairs.push_back(t * NW + w);
                                 p->npairs.push_back((int)c);
                                 p->npairs.push_back(q);
@@ -677,10 +685,10 @@ bem_status bem_assemble(bem_problem* p, int prec, void* A_dev, size_t lda, hipSt
     }
     if (prec == BEM_F32)
         HIP_OK(bemk::launch_assemble_f32(p->geom, p->L, p->N, p->n_if, ncc, p->quad, lists, p->vcount, pairs,
-                                         p->ncount, static_cast<float2*>(A_dev), lda, stream, side));
+                                         p->ncount, p->vpoints, static_cast<float2*>(A_dev), lda, stream, side));
     else
         HIP_OK(bemk::launch_assemble_f64(p->geom, p->L, p->N, p->n_if, ncc, p->quad, lists, p->vcount, pairs,
-                                         p->ncount, static_cast<double2*>(A_dev), lda, A32, stream, side));
+                                         p->ncount, p->vpoints, static_cast<double2*>(A_dev), lda, A32, stream, side));
     if (side != stream) {
         HIP_OK(hipEventRecord(p->asm_ev[1], side));
         HIP_OK(hipStreamWaitEvent(stream, p->asm_ev[1], 0));
@@ -1662,7 +1670,7 @@ bem_status bem_nearfield(const bem_problem* p, int nrhs, const void* X_dev, size
     if (npts == 0) return BEM_OK;
     std::vector<int> cplx((size_t)p->n_dom);
     for (int d = 0; d < p->n_dom; ++d) cplx[(size_t)d] = p->k[(size_t)d].imag() != 0.0;
-    HIP_OK(bemk::launch_nearfield(p->geom, p->L, p->n_if, p->n_dom, p->N, p->quad, cplx.data(),
+    HIP_OK(bemk::launch_nearfield(p->geom, p->L, p->n_if, p->n_dom, p->N, p->quad, cplx.data(), p->dom_points.data(),
                                   static_cast<const double2*>(X_dev), ldx, nrhs, angles, xy_dev, dom_dev, npts,
                                   static_cast<double2*>(U_dev), ldu, stream));
     return BEM_OK;

@@ -28,7 +28,7 @@ struct ElemRec {
     double cx, cy;     // midpoint = collocation point
     double tx, ty;     // unit tangent (b - a) / h
     double nx, ny;     // unit normal (-ty, tx)
-    double close2[2];  // ExpHead::close2 in the domains dom_left and dom_right
+    double close2[2];  // ExpHead::close2 in the domains dom_left and dom_right; without expansion (5/2 h)^2
     double h;          // length |b - a|
     double ax, ay;     // first node
     double bx, by;     // second node
@@ -38,8 +38,9 @@ struct ElemRec {
 // Expansion record of one element in the domain on one side of it (the sums of
 // its Gauss rule from one Hankel evaluation at its midpoint, assemble.hip):
 // EXP_HEAD doubles of squared distance limits (infinite where the element is
-// too long against the wavelength), then the coefficients by order: order 0
-// has (S, Tt), an odd order (Gt, Gn), an even one (S, Tt, Tn).
+// too long against the wavelength, except for the last two), then the
+// coefficients by order: order 0 has (S, Tt), an odd order (Gt, Gn), an even one
+// (S, Tt, Tn).
 constexpr int EXP_HEAD = 12, EXP_LMAX = 20, EXP_NCOEF = 52, EXP_NTERMS = 14;
 __host__ __device__ constexpr int exp_pos(int m)
 {
@@ -52,9 +53,11 @@ struct ExpHead {
     double lim8, lim10, lim12, lim16;  // beyond it: order 8, 10, 12, 16 suffices
     double near32;                     // the same for the FP32 assembly (remainder 1e-9)
     double lim32_4, lim32_6, lim32_8;
-    double pad[2];
+    double take64, take32;             // below it: near launch; as near64, near32, but for an element
+                                       // without expansion (XS/|k| + h/2)^2
 };
-constexpr int EXP_H_CLOSE = 0, EXP_H_NEAR64 = 1, EXP_H_LIM = 2, EXP_H_NEAR32 = 6, EXP_H_LIM32 = 7;
+constexpr int EXP_H_CLOSE = 0, EXP_H_NEAR64 = 1, EXP_H_LIM = 2, EXP_H_NEAR32 = 6, EXP_H_LIM32 = 7,
+              EXP_H_TAKE64 = 10, EXP_H_TAKE32 = 11;
 static_assert(sizeof(ExpHead) == EXP_HEAD * sizeof(double), "head of an expansion record");
 // With x = (h/2)/r the remainder of order L is about x^L, and about
 // (kh/4)^L / (L+1)! where kr is large: the largest x and |k| h/2 at which the
@@ -64,9 +67,9 @@ constexpr double EXP_X8 = 0.0087, EXP_X10 = 0.0223, EXP_X12 = 0.0415, EXP_X16 = 
 constexpr double EXP_KA8 = 0.074, EXP_KA10 = 0.228, EXP_KA12 = 0.495, EXP_KA16 = 1.36, EXP_KA_MAX = 2.55;
 constexpr double EXP32_X4 = 0.0054, EXP32_X6 = 0.0306, EXP32_X8 = 0.0725, EXP32_X16 = 0.2;
 constexpr double EXP32_KA4 = 0.026, EXP32_KA6 = 0.206, EXP32_KA8 = 0.615;
-// Shorter elements take the Gauss rule: H_m and the coefficients would leave
-// the range of a double.
-constexpr double EXP_KA_MIN = 1e-8;
+// Shorter elements take the Gauss rule: H_20 at their close distance (7e264 at
+// this limit) and the coefficients (1e-299) would leave the range of a double.
+constexpr double EXP_KA_MIN = 1e-13;
 
 // Inputs of a domain as given by the caller (complex numbers as re, im).
 struct DomIn {

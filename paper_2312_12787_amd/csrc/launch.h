@@ -40,17 +40,19 @@ hipError_t launch_setup(char* g, const GeomLayout& L, int N, int n_dom, int q, h
 constexpr int ASM_VARIANTS = 8;
 // lists[v] / counts[v]: row tiles of variant v (device list / host count);
 // pairs[v] / pair_counts[v]: its (row tile, column chunk, part of NEAR_PART
-// elements) triples that may hold near element pairs (device list / host count).
+// elements) triples that may hold near element pairs (device list / host count);
+// points[v]: its domains have elements without expansion.
 // Systems of assemble_one_launch(N) elements go to s in one launch; otherwise
 // variants go alternately to s and s1 (they write disjoint rows; s1 may be s).
 bool assemble_one_launch(int N);
 hipError_t launch_assemble_f64(const char* g, const GeomLayout& L, int N, int n_if, int n_cchunks, int q,
                                const int* const* lists, const int* counts, const int* const* pairs,
-                               const int* pair_counts, double2* A, size_t lda, float2* A32, hipStream_t s,
-                               hipStream_t s1);
+                               const int* pair_counts, const int* points, double2* A, size_t lda, float2* A32,
+                               hipStream_t s, hipStream_t s1);
 hipError_t launch_assemble_f32(const char* g, const GeomLayout& L, int N, int n_if, int n_cchunks, int q,
                                const int* const* lists, const int* counts, const int* const* pairs,
-                               const int* pair_counts, float2* A, size_t lda, hipStream_t s, hipStream_t s1);
+                               const int* pair_counts, const int* points, float2* A, size_t lda, hipStream_t s,
+                               hipStream_t s1);
 
 // angles / dirs are HOST arrays: they travel to the kernels by value in
 // chunks of ANGLE_CHUNK (3 KiB of the 4 KiB of a launch's arguments; the usual
@@ -237,8 +239,8 @@ struct NearAngles {
     double v[NF_RB];
 };
 hipError_t launch_nearfield(const char* g, const GeomLayout& L, int n_if, int n_dom, int N, int q, const int* dom_cplx,
-                            const double2* X, size_t ldx, int nrhs, const double* angles, const double* xy,
-                            const int* dom, int npts, double2* U, size_t ldu, hipStream_t s);
+                            const int* dom_points, const double2* X, size_t ldx, int nrhs, const double* angles,
+                            const double* xy, const int* dom, int npts, double2* U, size_t ldu, hipStream_t s);
 // big: some |k0 c| of an element may reach 2^29
 hipError_t launch_farfield(const char* g, const GeomLayout& L, int N, bool big, const double2* X, size_t ldx, int nrhs,
                            const double* dirs, int ndir, double2* F, size_t ldf, hipStream_t s);

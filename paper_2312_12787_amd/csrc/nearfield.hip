@@ -16,7 +16,10 @@
 //
 // A point beyond an element's close distance takes its Gauss rule from one
 // Hankel evaluation at the midpoint (expansion_dev.h; that distance is about
-// four element lengths, so the rule applies there by the first line).
+// four element lengths, so the rule applies there by the first line); one
+// without expansion (|k| h/2 outside EXP_KA_MIN .. EXP_KA_MAX) point by point
+// beyond 5/2 lengths from the midpoint (1024 elements at |k| h/2 = 4, 101 x 101
+// points: 0.84 ms; 5.14 ms as close pairs).
 //
 // Layout: points xy[2 p], xy[2 p + 1], domain dom[p]; X column-major [u; w]
 // per right-hand side (ldx); U column-major, point fastest (ldu).
@@ -206,9 +209,32 @@ __device__ __forceinline__ const double* exp_record(const char* g, const GeomLay
     return tab<double>(g, L.expn) + ((size_t)(P.dr == d ? 1 : 0) * N + j) * L.exp_stride;
 }
 
-template <bool CPLX, int RB>
+// The sums S and Gn of an element without expansion, point by point; (rx, ry)
+// from its midpoint.
+template <bool CPLX>
+__device__ __forceinline__ PairSums rule_sums(const WaveConst& W, const ElemRec& E, const double* __restrict__ gl, int nq,
+                                              double rx, double ry)
+{
+    PairSums Q;
+    Q.S = Q.Gn = {0.0, 0.0};
+    const double half = 0.5 * E.h;
+    for (int i = 0; i < nq; ++i) {
+        const double s = half * gl[i], w = half * gl[QMAX + i];
+        const double px = fma(-s, E.tx, rx), py = fma(-s, E.ty, ry), r2 = fma(px, px, py * py);
+        double r, rinv;
+        sqrt_rsqrt(r2, r, rinv);
+        cd h0, h1;
+        hankel01<CPLX, true>(W, r, r2, rinv, rsqrt_nr(r), h0, h1);
+        add_scaled(Q.S, w, 1.0, h0);
+        add_scaled(Q.Gn, w * rinv, fma(px, E.nx, py * E.ny), h1);
+    }
+    return Q;
+}
+
+// POINTS: the domain has elements without expansion.
+template <bool CPLX, int RB, bool POINTS>
 __global__ __launch_bounds__(64 * NF_WAVES, RB > 4 ? 2 : 3) void k_nearfield(const char* __restrict__ g, GeomLayout L, int n_if,
-                                                                 int N, int d, const double2* __restrict__ X,
+                                                                 int N, int nq, int d, const double2* __restrict__ X,
                                                                  size_t ldx, int nr, NearAngles ang, int add_incident,
                                                                  const double* __restrict__ xy,
                                                                  const int* __restrict__ dom, int npts,
@@ -249,14 +275,19 @@ __global__ __launch_bounds__(64 * NF_WAVES, RB > 4 ? 2 : 3) void k_nearfield(con
             const int Lo = !closer(rec[EXP_H_LIM]) ? 8 : !closer(rec[EXP_H_LIM + 1]) ? 10 : !closer(rec[EXP_H_LIM + 2]) ? 12
                            : !closer(rec[EXP_H_LIM + 3]) ? 16 : 20;
             if (on) {
-                double r, rinv;
-                sqrt_rsqrt(r2, r, rinv);
-                const double rlo = sqrt_error(rx, ry, diff_error(x, cx, rx), diff_error(y, cy, ry), r, rinv);
-                cd h0, h1;
-                hankel01<CPLX, true>(W, r, r2, rinv, rsqrt_nr(r), h0, h1, rlo);
-                const PairSums Q = expand<CPLX, false, 8>(rec + EXP_HEAD, cw, Lo, h0, h1, fma(rx, tx, ry * ty) * rinv,
-                                                          fma(ry, tx, -rx * ty) * rinv,
-                                                          {W.tkr * rinv, CPLX ? W.tki * rinv : 0.0});
+                PairSums Q;
+                if (!POINTS || rec[EXP_H_CLOSE] < __longlong_as_double(0x7ff0000000000000ll)) {
+                    double r, rinv;
+                    sqrt_rsqrt(r2, r, rinv);
+                    const double rlo = sqrt_error(rx, ry, diff_error(x, cx, rx), diff_error(y, cy, ry), r, rinv);
+                    cd h0, h1;
+                    hankel01<CPLX, true>(W, r, r2, rinv, rsqrt_nr(r), h0, h1, rlo);
+                    Q = expand<CPLX, false, 8>(rec + EXP_HEAD, cw, Lo, h0, h1, fma(rx, tx, ry * ty) * rinv,
+                                               fma(ry, tx, -rx * ty) * rinv,
+                                               {W.tkr * rinv, CPLX ? W.tki * rinv : 0.0});
+                } else {
+                    Q = rule_sums<CPLX>(W, el[j], tab<double>(g, L.gl), nq, rx, ry);
+                }
                 const cd eS = cmul(cS, Q.S), sD = cmul(cD, Q.Gn);
 #pragma unroll
                 for (int q = 0; q < RB; ++q) {
@@ -451,8 +482,8 @@ __global__ __launch_bounds__(NF_BS, 2) void k_nearfield_close(const char* __rest
 }  // namespace
 
 hipError_t launch_nearfield(const char* g, const GeomLayout& L, int n_if, int n_dom, int N, int q, const int* dom_cplx,
-                            const double2* X, size_t ldx, int nrhs, const double* angles, const double* xy,
-                            const int* dom, int npts, double2* U, size_t ldu, hipStream_t s)
+                            const int* dom_points, const double2* X, size_t ldx, int nrhs, const double* angles,
+                            const double* xy, const int* dom, int npts, double2* U, size_t ldu, hipStream_t s)
 {
     bool cplx = false;
     for (int d = 0; d < n_dom; ++d) cplx = cplx || dom_cplx[d];
@@ -464,21 +495,25 @@ hipError_t launch_nearfield(const char* g, const GeomLayout& L, int n_if, int n_
         double2* Ur = U + (size_t)r0 * ldu;
         const int inc = angles ? 1 : 0;
         for (int d = 0; d < n_dom; ++d) {
-#define BEM_NF_LAUNCH(C_, R_)                                                                                       \
-    hipLaunchKernelGGL((k_nearfield<C_, R_>), dim3((npts + NF_PTS - 1) / NF_PTS), dim3(64 * NF_WAVES), 0, s, g, L, n_if, \
-                       N, d, Xr, ldx, nr, ang, inc, xy, dom, npts, Ur, ldu)
-            if (dom_cplx[d]) {
+#define BEM_NF_LAUNCH(C_, R_, P_)                                                                                       \
+    hipLaunchKernelGGL((k_nearfield<C_, R_, P_>), dim3((npts + NF_PTS - 1) / NF_PTS), dim3(64 * NF_WAVES), 0, s, g, L, n_if, \
+                       N, q, d, Xr, ldx, nr, ang, inc, xy, dom, npts, Ur, ldu)
+            if (dom_cplx[d] && dom_points[d])
+                BEM_NF_LAUNCH(true, NF_RB, true);
+            else if (dom_points[d])
+                BEM_NF_LAUNCH(false, NF_RB, true);
+            else if (dom_cplx[d]) {
                 if (nr == 1)
-                    BEM_NF_LAUNCH(true, 1);
+                    BEM_NF_LAUNCH(true, 1, false);
                 else
-                    BEM_NF_LAUNCH(true, NF_RB);
+                    BEM_NF_LAUNCH(true, NF_RB, false);
             } else {
                 if (nr == 1)
-                    BEM_NF_LAUNCH(false, 1);
+                    BEM_NF_LAUNCH(false, 1, false);
                 else if (nr <= 4)
-                    BEM_NF_LAUNCH(false, 4);
+                    BEM_NF_LAUNCH(false, 4, false);
                 else
-                    BEM_NF_LAUNCH(false, NF_RB);
+                    BEM_NF_LAUNCH(false, NF_RB, false);
             }
 #undef BEM_NF_LAUNCH
         }
