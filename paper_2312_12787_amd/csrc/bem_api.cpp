@@ -461,17 +461,21 @@ bem_status bem_create(const bem_desc* desc, bem_problem** out)
         };
         constexpr int NP = bemk::COL_CHUNK / bemk::NEAR_PART;
         constexpr int NW = bemk::ROW_TILE / 64;
-        std::vector<Box> rb(p->rtiles.size() * NW), cb(p->cchunks.size() * NP);
+        // (wb: a box of each whole chunk, which leaves most chunks out at once)
+        std::vector<Box> rb(p->rtiles.size() * NW), cb(p->cchunks.size() * NP), wb(p->cchunks.size());
         for (size_t t = 0; t < p->rtiles.size(); ++t)
-            for (int w = 0; w < NW; ++w) {
-                const int s0 = 64 * w, cnt = std::min(64, p->rtiles[t].count - s0);
-                rb[t * NW + w] = cnt > 0 ? box(p->rtiles[t].start + s0, cnt) : Box{1e300, 1e300, 1e300, 1e300, 0.0, 1e300, 0.0};
+            for (int w = 0; w < NW && 64 * w < p->rtiles[t].count; ++w)
+                rb[t * NW + w] = box(p->rtiles[t].start + 64 * w, std::min(64, p->rtiles[t].count - 64 * w));
+        for (size_t c = 0; c < p->cchunks.size(); ++c) {
+            Box& u = wb[c] = Box{1e300, -1e300, 1e300, -1e300, 0.0, 1e300, 0.0};
+            for (int q = 0; q < NP && q * bemk::NEAR_PART < p->cchunks[c].count; ++q) {
+                const int s0 = q * bemk::NEAR_PART;
+                const Box& b = cb[c * NP + q] =
+                    box(p->cchunks[c].start + s0, std::min(bemk::NEAR_PART, p->cchunks[c].count - s0));
+                u = Box{std::min(u.x0, b.x0), std::max(u.x1, b.x1), std::min(u.y0, b.y0), std::max(u.y1, b.y1),
+                        std::max(u.hh, b.hh), std::min(u.hmin, b.hmin), std::max(u.reach, b.reach)};
             }
-        for (size_t c = 0; c < p->cchunks.size(); ++c)
-            for (int q = 0; q < NP; ++q) {
-                const int s0 = q * bemk::NEAR_PART, cnt = std::min(bemk::NEAR_PART, p->cchunks[c].count - s0);
-                cb[c * NP + q] = cnt > 0 ? box(p->cchunks[c].start + s0, cnt) : Box{1e300, 1e300, 1e300, 1e300, 0.0, 1e300, 0.0};
-            }
+        }
         p->dom_points.assign((size_t)p->n_dom, 0);
         for (int v = 0; v < bemk::ASM_VARIANTS; ++v) {
             p->noff[v] = (int)p->npairs.size() / 3;
@@ -482,24 +486,27 @@ bem_status bem_create(const bem_desc* desc, bem_problem** out)
                 const double ak = std::abs(p->k[d]);
                 const double rs = std::max(bemk::XS_SERIES_F64, bemk::XS_SERIES_F32) / ak;
                 const double longest = bemk::EXP_KA_MAX / ((1.0 + 1e-6) * ak), shortest = bemk::EXP_KA_MIN * (1.0 + 1e-6) / ak;
+                auto no_expansion = [&](const Box& b) { return b.hh > longest || b.hmin < shortest; };
+                auto near = [&](const Box& a, const Box& b) {
+                    const double dx = std::max(0.0, std::max(a.x0 - b.x1, b.x0 - a.x1));
+                    const double dy = std::max(0.0, std::max(a.y0 - b.y1, b.y0 - a.y1));
+                    const double lim = std::max(no_expansion(b) ? rs + b.hh : rs, b.reach) * (1.0 + 1e-6);
+                    return dx * dx + dy * dy < lim * lim;
+                };
+                for (size_t c = 0; c < p->cchunks.size(); ++c) {
+                    if (p->sigma[(size_t)d * p->n_if + p->cchunks[c].iface] == 0) continue;
+                    if (no_expansion(wb[c])) p->vpoints[v] = p->dom_points[d] = 1;
+                }
                 for (int w = 0; w < NW && 64 * w < p->rtiles[t].count; ++w)
                     for (size_t c = 0; c < p->cchunks.size(); ++c) {
-                        if (p->sigma[(size_t)d * p->n_if + p->cchunks[c].iface] == 0) continue;
-                        for (int q = 0; q < NP; ++q) {
-                            if (q * bemk::NEAR_PART >= p->cchunks[c].count) break;
-                            const Box &a = rb[t * NW + w], &b = cb[c * NP + q];
-                            const double dx = std::max(0.0, std::max(a.x0 - b.x1, b.x0 - a.x1));
-                            const double dy = std::max(0.0, std::max(a.y0 - b.y1, b.y0 - a.y1));
-                            const bool points = b.hh > longest || b.hmin < shortest;
-                            p->vpoints[v] |= points;
-                            p->dom_points[d] |= points;
-                            const double lim = std::max(points ? rs + b.hh : rs, b.reach) * (1.0 + 1e-6);
-                            if (dx * dx + dy * dy < lim * lim) {
+                        const Box& a = rb[t * NW + w];
+                        if (p->sigma[(size_t)d * p->n_if + p->cchunks[c].iface] == 0 || !near(a, wb[c])) continue;
+                        for (int q = 0; q < NP && q * bemk::NEAR_PART < p->cchunks[c].count; ++q)
+                            if (near(a, cb[c * NP + q])) {
                                 p->npairs.push_back(t * NW + w);
                                 p->npairs.push_back((int)c);
                                 p->npairs.push_back(q);
                             }
-                        }
                     }
             }
             p->ncount[v] = (int)p->npairs.size() / 3 - p->noff[v];
