@@ -203,7 +203,7 @@ __device__ cd int_h0_long(cd z)
         for (int i = 0; i < 16 * steps; ++i) {
             const double r = 4.0 + half * (2 * (i / 16) + 1 + GAUSS_X[15][i % 16]);
             cd h0, h1;
-            hankel01<true, true>(W, r, r * r, 1.0 / r, sqrt(1.0 / r), h0, h1);
+            hankel01<true>(W, r, r * r, 1.0 / r, sqrt(1.0 / r), h0, h1);
             const double w = half * GAUSS_W[15][i % 16];
             sum = {fma(w, h0.re, sum.re), fma(w, h0.im, sum.im)};
         }
@@ -706,7 +706,7 @@ __device__ __forceinline__ void near_part(const AsmArgs<T2>& P, int side, const 
                     sqrt_rsqrt(r2, r, rinv);
                     const double rlo = sqrt_error(rx, ry, diff_error(xi, cx, rx), diff_error(yi, cy, ry), r, rinv);
                     cd h0, h1;
-                    hankel01<CPLX, true>(W, r, r2, rinv, rsqrt_nr(r), h0, h1, rlo);
+                    hankel01<CPLX>(W, r, r2, rinv, rsqrt_nr(r), h0, h1, rlo);
                     const double c1 = fma(rx, tx, ry * ty) * rinv, s1 = fma(ry, tx, -rx * ty) * rinv;
                     const PairSums sums = expand<CPLX, BM, 8>(rec + EXP_HEAD, cw, Lo, h0, h1, c1, s1,
                                                               {tk.re * rinv, CPLX ? tk.im * rinv : 0.0});
@@ -750,7 +750,7 @@ __device__ __forceinline__ void near_part(const AsmArgs<T2>& P, int side, const 
             double r, rinv;
             sqrt_rsqrt(r2, r, rinv);
             cd h0, h1;
-            hankel01<CPLX, true>(W, r, r2, rinv, rsqrt_nr(r), h0, h1);
+            hankel01<CPLX>(W, r, r2, rinv, rsqrt_nr(r), h0, h1);
             const double wr = w * rinv;
             const double wd = wr * fma(rx, Ej.nx, ry * Ej.ny);
             part[0][lane] = w * h0.re;

@@ -41,11 +41,6 @@ __device__ __forceinline__ T poly_n(const C& c, T x)
     for (int m = N - 2; m >= 0; --m) acc = fma(acc, x, (T)c[m]);
     return acc;
 }
-template <int N, class T>
-__device__ __forceinline__ T poly_real(const T (&c)[N], T x)
-{
-    return poly_n<N>(c, x);
-}
 
 // sum_m c[m] z^m at complex z = x + i y for real c: with R = 2x, S = |z|^2,
 // b_{N-1} = c_{N-1}, b_{N-2} = c_{N-2} + R b_{N-1}, b_m = c_m + R b_{m+1} - S b_{m+2},
@@ -64,16 +59,11 @@ __device__ __forceinline__ void poly_cplx_n(const C& c, T x, T y, T R, T S, T& p
     pr = fma(x, b1, fma(-S, b2, (T)c[0]));
     pi = y * b1;
 }
-template <int N, class T>
-__device__ __forceinline__ void poly_cplx(const T (&c)[N], T x, T y, T R, T S, T& pr, T& pi)
-{
-    poly_cplx_n<N>(c, x, y, R, S, pr, pi);
-}
 
 // The ascending-series coefficients as one object in device memory.  The
-// general evaluator can read them through a pointer the compiler must reload
-// on each call (scalar loads, nothing held in registers across a loop), for
-// paths that run rarely and would otherwise keep 88 coefficients resident.
+// general evaluator reads them through a pointer the compiler must reload on
+// each call (scalar loads, nothing held in registers across a loop): its paths
+// run rarely and would otherwise keep 88 coefficients resident.
 struct HankelTabs {
     double j0[SERIES_NC], e0[SERIES_NC], j1[SERIES_NC], e1[SERIES_NC];
 };
@@ -190,14 +180,12 @@ __device__ __forceinline__ double hankel01_far(const WaveConst& W, double rx, do
 }
 
 // H0(k r), H1(k r).  r2 = r^2, rinv = 1/r, srinv = r^{-1/2}, rlo as above.  Below XS the
-// ascending series (MEM: its coefficients from g_hankel_tabs by scalar loads
-// instead of immediates), above it hankel_asym.
-template <bool CPLX, bool MEM = false>
+// ascending series, above it hankel_asym.
+template <bool CPLX>
 __device__ __forceinline__ void hankel01(const WaveConst& W, double r, double r2, double rinv, double srinv, cd& h0,
                                          cd& h1, double rlo = 0.0)
 {
-    HankelTabsPtr T = nullptr;
-    if (MEM) T = hankel_tabs_fresh();
+    const HankelTabsPtr T = hankel_tabs_fresh();
     constexpr double TWO_OVER_PI = 0.63661977236758134308;
     constexpr double EULER = 0.57721566490153286061;
     // both branches set these scalars and h0, h1 are written once after the
@@ -209,11 +197,11 @@ __device__ __forceinline__ void hankel01(const WaveConst& W, double r, double r2
         const double lnr = log(r);
         if (!CPLX) {
             const double t = W.tr * r2;
-            const double j0 = MEM ? poly_n<SERIES_NC>(T->j0, t) : poly_real(SERIES_J0, t);
-            const double e0 = MEM ? poly_n<SERIES_NC>(T->e0, t) : poly_real(SERIES_E0, t);
+            const double j0 = poly_n<SERIES_NC>(T->j0, t);
+            const double e0 = poly_n<SERIES_NC>(T->e0, t);
             const double zh = W.hr * r;
-            const double j1 = zh * (MEM ? poly_n<SERIES_NC>(T->j1, t) : poly_real(SERIES_J1, t));
-            const double e1 = MEM ? poly_n<SERIES_NC>(T->e1, t) : poly_real(SERIES_E1, t);
+            const double j1 = zh * poly_n<SERIES_NC>(T->j1, t);
+            const double e1 = poly_n<SERIES_NC>(T->e1, t);
             const double lz = lnr + W.lkr;
             const double y0 = fma(TWO_OVER_PI * (lz + EULER), j0, e0);
             const double y1 = fma(W.y1r, rinv, fma(TWO_OVER_PI * lz, j1, zh * e1));
@@ -225,22 +213,10 @@ __device__ __forceinline__ void hankel01(const WaveConst& W, double r, double r2
             const double x = W.tr * r2, y = W.ti * r2;
             const double R = 2.0 * x, S = fma(x, x, y * y);
             cd j0, e0, p1, e1;
-            if (MEM)
-                poly_cplx_n<SERIES_NC>(T->j0, x, y, R, S, j0.re, j0.im);
-            else
-                poly_cplx(SERIES_J0, x, y, R, S, j0.re, j0.im);
-            if (MEM)
-                poly_cplx_n<SERIES_NC>(T->e0, x, y, R, S, e0.re, e0.im);
-            else
-                poly_cplx(SERIES_E0, x, y, R, S, e0.re, e0.im);
-            if (MEM)
-                poly_cplx_n<SERIES_NC>(T->j1, x, y, R, S, p1.re, p1.im);
-            else
-                poly_cplx(SERIES_J1, x, y, R, S, p1.re, p1.im);
-            if (MEM)
-                poly_cplx_n<SERIES_NC>(T->e1, x, y, R, S, e1.re, e1.im);
-            else
-                poly_cplx(SERIES_E1, x, y, R, S, e1.re, e1.im);
+            poly_cplx_n<SERIES_NC>(T->j0, x, y, R, S, j0.re, j0.im);
+            poly_cplx_n<SERIES_NC>(T->e0, x, y, R, S, e0.re, e0.im);
+            poly_cplx_n<SERIES_NC>(T->j1, x, y, R, S, p1.re, p1.im);
+            poly_cplx_n<SERIES_NC>(T->e1, x, y, R, S, e1.re, e1.im);
             const cd zh = {W.hr * r, W.hi * r};
             const cd j1 = cmul(zh, p1);
             const cd lz = {lnr + W.lkr, W.lki};
@@ -261,15 +237,6 @@ __device__ __forceinline__ void hankel01(const WaveConst& W, double r, double r2
     }
     h0 = {h0r, h0i};
     h1 = {h1r, h1i};
-}
-
-// H1 only (end-point terms of the hypersingular operator).
-template <bool CPLX, bool MEM = false>
-__device__ __forceinline__ cd hankel1_only(const WaveConst& W, double r, double r2, double rinv, double srinv)
-{
-    cd h0, h1;
-    hankel01<CPLX, MEM>(W, r, r2, rinv, srinv, h0, h1);
-    return h1;
 }
 
 }  // namespace bemk

@@ -226,8 +226,6 @@ hipError_t launch_xupdate(const double2* V, size_t ldv, int nr, int n, int m, co
                           double2* X, size_t ldx, hipStream_t s);
 hipError_t launch_xupdate(const float2* V, size_t ldv, int nr, int n, int m, const double2* y, const int* kdim,
                           double2* X, size_t ldx, hipStream_t s);
-hipError_t launch_axpby_res(const double2* B, size_t ldb, const double2* AX, size_t ldax, int n, int nr,
-                            double2* R, size_t ldr, hipStream_t s);
 // X += D on the columns with add[r] != 0 (host)
 hipError_t launch_add_f64(const double2* D, size_t ldd, int n, int nr, double2* X, size_t ldx, const int* add,
                           hipStream_t s);

@@ -857,16 +857,6 @@ __global__ void k_xupdate(const TV* __restrict__ V, size_t ldv, int nr, int n, i
     X[(size_t)r * ldx + q] = x;
 }
 
-__global__ void k_axpby_res(const double2* __restrict__ B, size_t ldb, const double2* __restrict__ AX, size_t ldax,
-                            int n, double2* __restrict__ R, size_t ldr)
-{
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    const int r = blockIdx.y;
-    if (q >= n) return;
-    const double2 b = B[(size_t)r * ldb + q], a = AX[(size_t)r * ldax + q];
-    R[(size_t)r * ldr + q] = make_double2(b.x - a.x, b.y - a.y);
-}
-
 __global__ void k_add_64(const double2* __restrict__ D, size_t ldd, int n, int r0, double2* __restrict__ X, size_t ldx,
                          unsigned long long add)
 {
@@ -1296,13 +1286,6 @@ hipError_t launch_xupdate(const float2* V, size_t ldv, int nr, int n, int m, con
 {
     hipLaunchKernelGGL((k_xupdate<float2>), dim3((n + BS - 1) / BS, nr), dim3(BS), 0, s, V, ldv, nr, n, m, y, kdim, X,
                        ldx);
-    return hipGetLastError();
-}
-
-hipError_t launch_axpby_res(const double2* B, size_t ldb, const double2* AX, size_t ldax, int n, int nr,
-                            double2* R, size_t ldr, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_axpby_res, dim3((n + BS - 1) / BS, nr), dim3(BS), 0, s, B, ldb, AX, ldax, n, R, ldr);
     return hipGetLastError();
 }
 

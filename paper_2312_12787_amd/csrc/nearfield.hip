@@ -124,7 +124,7 @@ __device__ __forceinline__ void close_term(const WaveConst& W, cd k, const ElemR
     double r, rinv;
     sqrt_rsqrt(r2, r, rinv);
     cd h0, h1;
-    hankel01<CPLX, true>(W, r, r2, rinv, rsqrt_nr(r), h0, h1);
+    hankel01<CPLX>(W, r, r2, rinv, rsqrt_nr(r), h0, h1);
     const double wg = half * wt;
     if (C.far) {
         S = {wg * h0.re, wg * h0.im};
@@ -224,7 +224,7 @@ __device__ __forceinline__ PairSums rule_sums(const WaveConst& W, const ElemRec&
         double r, rinv;
         sqrt_rsqrt(r2, r, rinv);
         cd h0, h1;
-        hankel01<CPLX, true>(W, r, r2, rinv, rsqrt_nr(r), h0, h1);
+        hankel01<CPLX>(W, r, r2, rinv, rsqrt_nr(r), h0, h1);
         add_scaled(Q.S, w, 1.0, h0);
         add_scaled(Q.Gn, w * rinv, fma(px, E.nx, py * E.ny), h1);
     }
@@ -281,7 +281,7 @@ __global__ __launch_bounds__(64 * NF_WAVES, RB > 4 ? 2 : 3) void k_nearfield(con
                     sqrt_rsqrt(r2, r, rinv);
                     const double rlo = sqrt_error(rx, ry, diff_error(x, cx, rx), diff_error(y, cy, ry), r, rinv);
                     cd h0, h1;
-                    hankel01<CPLX, true>(W, r, r2, rinv, rsqrt_nr(r), h0, h1, rlo);
+                    hankel01<CPLX>(W, r, r2, rinv, rsqrt_nr(r), h0, h1, rlo);
                     Q = expand<CPLX, false, 8>(rec + EXP_HEAD, cw, Lo, h0, h1, fma(rx, tx, ry * ty) * rinv,
                                                fma(ry, tx, -rx * ty) * rinv,
                                                {W.tkr * rinv, CPLX ? W.tki * rinv : 0.0});
