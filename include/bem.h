@@ -125,7 +125,8 @@ typedef struct {
  * BEM_E_ARG: k[0] not real-positive, Im k < 0, a lossy wavenumber with
  * arg k > 10 degrees (Im k > tan(10 deg) Re k: the device's large-argument
  * Hankel form continues real-axis amplitude fits to complex arguments, with a
- * relative error of 1e-14 at arg k = 3.2 deg and 1.7e-12 at 10 deg), quad out
+ * relative error of at most 8e-15 at arg k = 3 deg, 3e-14 at 4 deg, 2e-14 at 10
+ * deg), quad out
  * of range, or max |k| times the diameter of the nodes' bounding box >= 2^29
  * (the device reduces phases k r by pi/2 exactly only below 2^30).           */
 bem_status bem_create(const bem_desc *desc, bem_problem **out);

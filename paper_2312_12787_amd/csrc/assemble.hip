@@ -88,7 +88,8 @@ __device__ void build_wave(cd k, WaveConst& W)
     const double ak = hypot(k.re, k.im);
     W.kr = k.re;
     W.ki = k.im;
-    W.r2_small = (HANKEL_XS_F64 / ak) * (HANKEL_XS_F64 / ak);
+    const double rs = series_radius(k.re, k.im) / ak;
+    W.r2_small = rs * rs;
     const cd xk = cdiv({HANKEL_XS_F64, 0.0}, k);  // XS / k
     W.ur = xk.re;
     W.ui = xk.im;
@@ -291,7 +292,8 @@ __device__ __forceinline__ void setup_expansion(char* g, const GeomLayout& L, in
         auto lim = [&](double x, double kamax) { return expansion_limit(a, ak, x, kamax); };
         ExpHead* H = reinterpret_cast<ExpHead*>(rec);
         H->close2 = lim(EXP_X20, EXP_KA_MAX);
-        H->near64 = fmax(H->close2, sq(HANKEL_XS_F64 / ak));
+        const double rs = series_radius(k.re, k.im) / ak;
+        H->near64 = fmax(H->close2, sq(rs));
         H->lim8 = lim(EXP_X8, EXP_KA8);
         H->lim10 = lim(EXP_X10, EXP_KA10);
         H->lim12 = lim(EXP_X12, EXP_KA12);
@@ -300,7 +302,7 @@ __device__ __forceinline__ void setup_expansion(char* g, const GeomLayout& L, in
         H->lim32_4 = lim(EXP32_X4, EXP32_KA4);
         H->lim32_6 = lim(EXP32_X6, EXP32_KA6);
         H->lim32_8 = lim(EXP32_X8, EXP32_KA8);
-        H->take64 = expanded(H->close2) ? H->near64 : sq(HANKEL_XS_F64 / ak + a);
+        H->take64 = expanded(H->close2) ? H->near64 : sq(rs + a);
         H->take32 = expanded(H->close2) ? H->near32 : sq(HANKEL_XS_F32 / ak + a);
     }
     const int cw = L.exp_cplx ? 2 : 1;  // doubles per coefficient
@@ -494,8 +496,11 @@ struct AsmArgs {
 // entries' error against 32-digit values 2 to 5 times smaller; 777 elements at
 // k h = 0.8 288 -> 68 us (50 in the single launch below); three sectors,
 // 1900 elements, 1005 -> 185 us (154).
-// Entries in FP64 are as close to 32-digit values as before (the phase k r,
-// once averaged over q points, is formed from a compensated distance).
+// Entries in FP64 are as close to 32-digit values as point-by-point sums, which
+// averaged the rounding of q evaluations (standard rows, w columns, rms: disk of
+// 256 elements 2.2e-16 both, kite of 512 6.9e-16 -> 5.2e-16, of 300 at arg k = 5.7
+// degrees 3.2e-15 -> 7.0e-16): the phase k r is formed from a compensated
+// distance, the series below |k r| = 6 do not cancel (hankel_dev.h).
 // ---------------------------------------------------------------------------
 template <bool CPLX, bool BM, class T2>
 __device__ __forceinline__ void far_part(const AsmArgs<T2>& P, int side, int tile, int li, int col_part, int per)

@@ -484,7 +484,7 @@ bem_status bem_create(const bem_desc* desc, bem_problem** out)
                 const IfacePlan& P = p->iface[p->rtiles[t].iface];
                 const int d = side ? P.dr : P.dl;
                 const double ak = std::abs(p->k[d]);
-                const double rs = std::max(bemk::XS_SERIES_F64, bemk::XS_SERIES_F32) / ak;
+                const double rs = std::max(bemk::series_radius(p->k[d].real(), p->k[d].imag()), bemk::XS_SERIES_F32) / ak;
                 const double longest = bemk::EXP_KA_MAX / ((1.0 + 1e-6) * ak), shortest = bemk::EXP_KA_MIN * (1.0 + 1e-6) / ak;
                 auto no_expansion = [&](const Box& b) { return b.hh > longest || b.hmin < shortest; };
                 auto near = [&](const Box& a, const Box& b) {

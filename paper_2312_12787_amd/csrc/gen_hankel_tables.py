@@ -21,7 +21,15 @@ mpmath.mp.dps = 60
 
 XS64 = 6.0      # FP64 path: series below, fit above
 DEG64 = 14
-NSER64 = 22     # ascending-series terms (|z| < 6 in FP64)
+# Below XS64 the four entire functions of t = (z/2)^2: ascending series about t = 0
+# for |z| < ZLOW, Taylor series about TMID beyond (to |z| = 6 the ascending series
+# would add terms 60 times its sum), NMID terms for the range of real z, NWIDE for
+# that of lossy wavenumbers (to |z| = 7)
+ZLOW = 3.0
+NLOW = 15
+TMID = 5.5
+NMID = 16
+NWIDE = 19
 XS32 = 4.0      # FP32 path
 DEG32 = 6
 
@@ -117,6 +125,12 @@ def series_constants(nterms):
     return j0, e0, j1, e1
 
 
+def about(c, t0, nterms):
+    """The first coefficients in t - t0 of sum_m c_m t^m."""
+    return [mpmath.fsum(c[m] * mpmath.binomial(m, k) * mpmath.mpf(t0) ** (m - k) for m in range(k, len(c)))
+            for k in range(nterms)]
+
+
 def main():
     out = ['/* Generated by gen_hankel_tables.py -- do not edit.\n'
            ' * Monomial coefficients (ascending powers of w = (XS/z)^2) of the fitted\n'
@@ -134,15 +148,14 @@ def main():
             out.append(fmt(f"HANKEL_M{nu}_{tag}", mco, ctype))
             out.append(fmt(f"HANKEL_N{nu}_{tag}", nco, ctype))
             print(tag, nu, f"{err:.2e}")
-    j0, e0, j1, e1 = series_constants(NSER64)
-    out.append("/* Ascending series in t = (z/2)^2 (DLMF 10.2.2, 10.8.1, 10.8.2):\n"
-               " * J0 = sum J0_m t^m, Y0 = (2/pi)(ln(z/2) + gamma) J0 + sum E0_m t^m,\n"
-               " * J1 = (z/2) sum J1_m t^m, Y1 = -(2/pi)/z + (2/pi) ln(z/2) J1 + (z/2) sum E1_m t^m. */\n")
-    out.append(f"static constexpr int SERIES_NC = {NSER64};\n")
-    out.append(fmt("SERIES_J0", j0, "double"))
-    out.append(fmt("SERIES_E0", e0, "double"))
-    out.append(fmt("SERIES_J1", j1, "double"))
-    out.append(fmt("SERIES_E1", e1, "double"))
+    out.append("/* J0, Y0 = (2/pi)(ln(z/2) + gamma) J0 + E0, J1 = (z/2) J1', Y1 = -(2/pi)/z + (2/pi) ln(z/2) J1 + (z/2) E1\n"
+               " * (DLMF 10.2.2, 10.8.1, 10.8.2); J0, E0, J1', E1 as series in t = (z/2)^2 for |z| < SERIES_ZLOW,\n"
+               " * in t - SERIES_TMID up to |z| = HANKEL_XS_F64 (SERIES_NMID terms) or 7 (SERIES_NWIDE). */\n")
+    out.append(f"static constexpr double SERIES_ZLOW = {ZLOW!r}, SERIES_TMID = {TMID!r};\n")
+    out.append(f"static constexpr int SERIES_NLOW = {NLOW}, SERIES_NMID = {NMID}, SERIES_NWIDE = {NWIDE};\n")
+    for name, c in zip(("J0", "E0", "J1", "E1"), series_constants(60)):
+        out.append(fmt(f"LOW_{name}", c[:NLOW], "double"))
+        out.append(fmt(f"MID_{name}", about(c, TMID, NWIDE), "double"))
     path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "hankel_tables.h")
     with open(path, "w") as f:
         f.write("".join(out))

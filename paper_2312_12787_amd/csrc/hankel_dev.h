@@ -5,11 +5,14 @@
 // Every polynomial has compile-time real coefficients (hankel_tables.h); the
 // wavenumber enters only through the argument, so a launch keeps a handful
 // of per-wavenumber constants (WaveConst) instead of coefficient tables.
-//  * |k r| < XS: ascending series (DLMF 10.2.2, 10.8.1, 10.8.2) in
-//    t = (k r / 2)^2 = (k/2)^2 r^2:
+//  * |k r| < XS: in t = (k r / 2)^2 = (k/2)^2 r^2 (DLMF 10.2.2, 10.8.1, 10.8.2)
 //        J0 = J0(t),  Y0 = (2/pi)(ln(kr/2) + gamma) J0 + E0(t),
 //        J1 = (kr/2) J1(t),  Y1 = -(2/pi)/(k r) + (2/pi) ln(kr/2) J1 + (kr/2) E1(t),
-//    with ln(kr/2) = ln r + ln(k/2) (a real logarithm per lane);
+//    with ln(kr/2) = ln r + ln(k/2) (a real logarithm per lane) and the entire
+//    functions J0, E0, J1, E1 from their ascending series for |k r| < 3, beyond
+//    from their Taylor series about t = 5.5 (relative error of H0, real k, kr
+//    from 0 to 6 in steps of 1, ascending series throughout / so: 0.8, 0.9, 2, 5,
+//    15, 42 / 0.8, 0.9, 2, 2, 2, 2 1e-16);
 //  * |k r| >= XS: H_nu = sqrt(2/(pi k)) r^{-1/2} e^{i(k r - nu pi/2 - pi/4)} P_nu,
 //    P_nu = m_nu(w) + i (XS/(k r)) n_nu(w),  w = (XS/k)^2 / r^2, with m, n the
 //    fitted amplitude polynomials.
@@ -60,21 +63,32 @@ __device__ __forceinline__ void poly_cplx_n(const C& c, T x, T y, T R, T S, T& p
     pi = y * b1;
 }
 
-// The ascending-series coefficients as one object in device memory.  The
-// general evaluator reads them through a pointer the compiler must reload on
-// each call (scalar loads, nothing held in registers across a loop): its paths
-// run rarely and would otherwise keep 88 coefficients resident.
+// The series coefficients as one object in device memory.  The general evaluator
+// reads them through a pointer the compiler must reload on each call (scalar
+// loads, nothing held in registers across a loop): its paths run rarely and
+// would otherwise keep all of them resident.
+template <int N>
+struct SeriesTabs {
+    double j0[N], e0[N], j1[N], e1[N];
+};
 struct HankelTabs {
-    double j0[SERIES_NC], e0[SERIES_NC], j1[SERIES_NC], e1[SERIES_NC];
+    SeriesTabs<SERIES_NLOW> low;
+    SeriesTabs<SERIES_NWIDE> mid;
 };
 constexpr HankelTabs make_hankel_tabs()
 {
     HankelTabs t{};
-    for (int m = 0; m < SERIES_NC; ++m) {
-        t.j0[m] = SERIES_J0[m];
-        t.e0[m] = SERIES_E0[m];
-        t.j1[m] = SERIES_J1[m];
-        t.e1[m] = SERIES_E1[m];
+    for (int m = 0; m < SERIES_NLOW; ++m) {
+        t.low.j0[m] = LOW_J0[m];
+        t.low.e0[m] = LOW_E0[m];
+        t.low.j1[m] = LOW_J1[m];
+        t.low.e1[m] = LOW_E1[m];
+    }
+    for (int m = 0; m < SERIES_NWIDE; ++m) {
+        t.mid.j0[m] = MID_J0[m];
+        t.mid.e0[m] = MID_E0[m];
+        t.mid.j1[m] = MID_J1[m];
+        t.mid.e1[m] = MID_E1[m];
     }
     return t;
 }
@@ -179,8 +193,31 @@ __device__ __forceinline__ double hankel01_far(const WaveConst& W, double rx, do
     return rinv;
 }
 
+// The four entire functions of the series at t (N terms).
+struct Entire {
+    cd j0, e0, j1, e1;
+};
+template <bool CPLX, int N, int NTAB>
+__device__ __forceinline__ Entire entire(const __attribute__((address_space(4))) SeriesTabs<NTAB>* c, double x, double y)
+{
+    Entire E;
+    if (!CPLX) {
+        E.j0.re = poly_n<N>(c->j0, x);
+        E.e0.re = poly_n<N>(c->e0, x);
+        E.j1.re = poly_n<N>(c->j1, x);
+        E.e1.re = poly_n<N>(c->e1, x);
+    } else {
+        const double R = 2.0 * x, S = fma(x, x, y * y);
+        poly_cplx_n<N>(c->j0, x, y, R, S, E.j0.re, E.j0.im);
+        poly_cplx_n<N>(c->e0, x, y, R, S, E.e0.re, E.e0.im);
+        poly_cplx_n<N>(c->j1, x, y, R, S, E.j1.re, E.j1.im);
+        poly_cplx_n<N>(c->e1, x, y, R, S, E.e1.re, E.e1.im);
+    }
+    return E;
+}
+
 // H0(k r), H1(k r).  r2 = r^2, rinv = 1/r, srinv = r^{-1/2}, rlo as above.  Below XS the
-// ascending series, above it hankel_asym.
+// series, above it hankel_asym.
 template <bool CPLX>
 __device__ __forceinline__ void hankel01(const WaveConst& W, double r, double r2, double rinv, double srinv, cd& h0,
                                          cd& h1, double rlo = 0.0)
@@ -188,6 +225,7 @@ __device__ __forceinline__ void hankel01(const WaveConst& W, double r, double r2
     const HankelTabsPtr T = hankel_tabs_fresh();
     constexpr double TWO_OVER_PI = 0.63661977236758134308;
     constexpr double EULER = 0.57721566490153286061;
+    constexpr double LOW2 = (HANKEL_XS_F64 / SERIES_ZLOW) * (HANKEL_XS_F64 / SERIES_ZLOW);
     // both branches set these scalars and h0, h1 are written once after the
     // join: stores to different fields at the ends of the two branches would
     // be merged into one store through a selected address, which keeps the
@@ -195,35 +233,27 @@ __device__ __forceinline__ void hankel01(const WaveConst& W, double r, double r2
     double h0r, h0i, h1r, h1i;
     if (r2 < W.r2_small) {
         const double lnr = log(r);
+        Entire E;
+        if (LOW2 * r2 < W.r2_small)
+            E = entire<CPLX, SERIES_NLOW>(&T->low, W.tr * r2, W.ti * r2);
+        else
+            E = entire<CPLX, CPLX ? SERIES_NWIDE : SERIES_NMID>(&T->mid, fma(W.tr, r2, -SERIES_TMID), W.ti * r2);
         if (!CPLX) {
-            const double t = W.tr * r2;
-            const double j0 = poly_n<SERIES_NC>(T->j0, t);
-            const double e0 = poly_n<SERIES_NC>(T->e0, t);
             const double zh = W.hr * r;
-            const double j1 = zh * poly_n<SERIES_NC>(T->j1, t);
-            const double e1 = poly_n<SERIES_NC>(T->e1, t);
+            const double j1 = zh * E.j1.re;
             const double lz = lnr + W.lkr;
-            const double y0 = fma(TWO_OVER_PI * (lz + EULER), j0, e0);
-            const double y1 = fma(W.y1r, rinv, fma(TWO_OVER_PI * lz, j1, zh * e1));
-            h0r = j0;
-            h0i = y0;
+            h0r = E.j0.re;
+            h0i = fma(TWO_OVER_PI * (lz + EULER), E.j0.re, E.e0.re);
             h1r = j1;
-            h1i = y1;
+            h1i = fma(W.y1r, rinv, fma(TWO_OVER_PI * lz, j1, zh * E.e1.re));
         } else {
-            const double x = W.tr * r2, y = W.ti * r2;
-            const double R = 2.0 * x, S = fma(x, x, y * y);
-            cd j0, e0, p1, e1;
-            poly_cplx_n<SERIES_NC>(T->j0, x, y, R, S, j0.re, j0.im);
-            poly_cplx_n<SERIES_NC>(T->e0, x, y, R, S, e0.re, e0.im);
-            poly_cplx_n<SERIES_NC>(T->j1, x, y, R, S, p1.re, p1.im);
-            poly_cplx_n<SERIES_NC>(T->e1, x, y, R, S, e1.re, e1.im);
             const cd zh = {W.hr * r, W.hi * r};
-            const cd j1 = cmul(zh, p1);
+            const cd j1 = cmul(zh, E.j1);
             const cd lz = {lnr + W.lkr, W.lki};
-            const cd y0 = cadd(cmul({TWO_OVER_PI * (lz.re + EULER), TWO_OVER_PI * lz.im}, j0), e0);
-            const cd y1 = cadd(cadd(cscale({W.y1r, W.y1i}, rinv), cmul(cscale(lz, TWO_OVER_PI), j1)), cmul(zh, e1));
-            h0r = j0.re - y0.im;
-            h0i = j0.im + y0.re;
+            const cd y0 = cadd(cmul({TWO_OVER_PI * (lz.re + EULER), TWO_OVER_PI * lz.im}, E.j0), E.e0);
+            const cd y1 = cadd(cadd(cscale({W.y1r, W.y1i}, rinv), cmul(cscale(lz, TWO_OVER_PI), j1)), cmul(zh, E.e1));
+            h0r = E.j0.re - y0.im;
+            h0i = E.j0.im + y0.re;
             h1r = j1.re - y1.im;
             h1i = j1.im + y1.re;
         }
