@@ -19,7 +19,7 @@
 // per (side, element), made with the geometry tables.  Orders up to L leave a
 // relative remainder of (h/(2r))^L (and (kh/4)^L/(L+1)! for large r); each
 // record holds the distances beyond which L = 8, 10, 12, 16 and 20 leave less
-// than 4e-17.
+// than 4e-17 (real k; internal.h).
 #pragma once
 
 #include "hankel_dev.h"

@@ -56,7 +56,7 @@ __host__ __device__ constexpr int exp_pos(int m)
 }
 static_assert(exp_pos(EXP_LMAX) + 3 == EXP_NCOEF, "coefficients of the orders 0 .. EXP_LMAX");
 struct ExpHead {
-    double close2;                     // below it: no expansion (order 20 leaves more than 4e-17)
+    double close2;                     // below it: no expansion (order 20 leaves too much)
     double near64;                     // below it: near launch of the FP64 assembly (close2, series radius)
     double lim8, lim10, lim12, lim16;  // beyond it: order 8, 10, 12, 16 suffices
     double near32;                     // the same for the FP32 assembly (remainder 1e-9)
@@ -70,7 +70,9 @@ static_assert(sizeof(ExpHead) == EXP_HEAD * sizeof(double), "head of an expansio
 // With x = (h/2)/r the remainder of order L is about x^L, and about
 // (kh/4)^L / (L+1)! where kr is large: the largest x and |k| h/2 at which the
 // remainder of every sum, relative to its leading term, stays below 4e-17
-// (FP32: 1e-9), found by evaluating the dropped terms over r, phi and k h.
+// (FP32: 1e-9) for real k (gen_expansion_limits.py).  At arg k = 10 degrees the
+// vector sums leave up to 1.4e-16, the end-point differences 2.3e-16 (1e-9 and
+// 1.7e-9).
 constexpr double EXP_X8 = 0.0087, EXP_X10 = 0.0223, EXP_X12 = 0.0415, EXP_X16 = 0.0855, EXP_X20 = 0.128;
 constexpr double EXP_KA8 = 0.074, EXP_KA10 = 0.228, EXP_KA12 = 0.495, EXP_KA16 = 1.36, EXP_KA_MAX = 2.55;
 constexpr double EXP32_X4 = 0.0054, EXP32_X6 = 0.0306, EXP32_X8 = 0.0725, EXP32_X16 = 0.2;
