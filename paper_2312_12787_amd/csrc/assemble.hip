@@ -477,6 +477,7 @@ struct AsmArgs {
     T2* A;
     float2* A32;  // FP32 copy of an FP64 matrix, or null
     size_t lda;
+    bool point_launch;  // elements without expansion have a launch of their own
 };
 
 // ---------------------------------------------------------------------------
@@ -692,6 +693,7 @@ __device__ __forceinline__ void near_part(const AsmArgs<T2>& P, int side, const 
         const double xi = el[i].cx, yi = el[i].cy, tix = el[i].tx, tiy = el[i].ty;
         const cd tk = {W.tkr, W.tki};
         const int cw = P.L.exp_cplx ? 2 : 1;
+        const int take = P.point_launch ? (LOW ? EXP_H_TAKE32 : EXP_H_TAKE64) : LOW ? EXP_H_NEAR32 : EXP_H_NEAR64;
         for (int jj = 0; jj < cnt; ++jj) {
             const int j = cc.start + j0 + jj;
             ScalarPtr Ej = (ScalarPtr)(el + j);
@@ -699,7 +701,7 @@ __device__ __forceinline__ void near_part(const AsmArgs<T2>& P, int side, const 
             const double cx = Ej[E_CX], cy = Ej[E_CY], tx = Ej[E_TX], ty = Ej[E_TY];
             const double rx = xi - cx, ry = yi - cy;
             const double r2 = pair_r2(rx, ry);
-            if (__builtin_amdgcn_ballot_w64(valid && r2 < rec[LOW ? EXP_H_TAKE32 : EXP_H_TAKE64]) == 0) continue;
+            if (__builtin_amdgcn_ballot_w64(valid && r2 < rec[take]) == 0) continue;
             const bool close = valid && r2 < rec[EXP_H_CLOSE];
             const bool rest = valid && !close;
             if (__builtin_amdgcn_ballot_w64(rest) != 0) {
@@ -969,19 +971,19 @@ bool assemble_one_launch(int N) { return 2 * (long long)N * N <= 1 << 24; }
 
 hipError_t launch_assemble_f64(const char* g, const GeomLayout& L, int N, int n_if, int n_cchunks, int q,
                                const int* const* lists, const int* counts, const int* const* pairs,
-                               const int* pair_counts, const int* points, double2* A, size_t lda, float2* A32,
+                               const int* pair_counts, const int* points, bool point_launch, double2* A, size_t lda, float2* A32,
                                hipStream_t s, hipStream_t s1)
 {
-    return launch_variants(AsmArgs<double2>{g, L, N, n_if, q, A, A32, lda}, n_cchunks, lists, counts, pairs,
+    return launch_variants(AsmArgs<double2>{g, L, N, n_if, q, A, A32, lda, point_launch}, n_cchunks, lists, counts, pairs,
                            pair_counts, points, s, s1);
 }
 
 hipError_t launch_assemble_f32(const char* g, const GeomLayout& L, int N, int n_if, int n_cchunks, int q,
                                const int* const* lists, const int* counts, const int* const* pairs,
-                               const int* pair_counts, const int* points, float2* A, size_t lda, hipStream_t s,
+                               const int* pair_counts, const int* points, bool point_launch, float2* A, size_t lda, hipStream_t s,
                                hipStream_t s1)
 {
-    return launch_variants(AsmArgs<float2>{g, L, N, n_if, q, A, nullptr, lda}, n_cchunks, lists, counts, pairs,
+    return launch_variants(AsmArgs<float2>{g, L, N, n_if, q, A, nullptr, lda, point_launch}, n_cchunks, lists, counts, pairs,
                            pair_counts, points, s, s1);
 }
 

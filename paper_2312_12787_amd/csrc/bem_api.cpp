@@ -109,6 +109,7 @@ struct bem_problem {
     // 1: some element of the variant's domains, of the domain has no expansion
     int vpoints[bemk::ASM_VARIANTS] = {0};
     std::vector<int> dom_points;
+    bool point_launch = false;  // those elements have a launch of their own
     std::vector<int> elif;          // interface of each element
     std::vector<int> elnodes;       // (a, b) node indices per element
     bemk::DomIn dummy{};
@@ -433,11 +434,11 @@ bem_status bem_create(const bem_desc* desc, bem_problem** out)
         // elements of the chunk -- whose bounding boxes (collocation points,
         // element midpoints) come within the near radius of the part in the
         // rows' domain (relative margin 1e-6): the series radius XS/|k_d| or
-        // the expansion's reach of the part's longest element, and half that
-        // element's length more than the series radius where one is too long or
-        // too short for the expansion.  Only these can hold an element that the
-        // far launch (and that of the elements without expansion) leaves, so the
-        // near launch runs over them alone, one wave per item.
+        // the expansion's reach of the part's longest element; where one is too
+        // long or too short for the expansion, half that element's length more than
+        // the series radius, or any distance if those elements have no launch of
+        // their own.  Only these can hold an element that the other launches leave,
+        // so the near launch runs over them alone, one wave per item.
         struct Box {
             double x0, x1, y0, y1, hh, hmin;  // midpoints, largest and smallest half length
             double reach;                     // the expansion's, of the longest element
@@ -476,27 +477,52 @@ bem_status bem_create(const bem_desc* desc, bem_problem** out)
                         std::max(u.hh, b.hh), std::min(u.hmin, b.hmin), std::max(u.reach, b.reach)};
             }
         }
+        // Elements without expansion.  A launch of their own passes over all (64-row
+        // wave, element) pairs again and costs 10 us; the near launch takes any number
+        // of them without, but evaluates a pair at a third of the rate: it keeps them
+        // unless they make 1000 pairs and a third of all.  Assembly, one of two
+        // domains, us (near launch / own): 128 elements, all without expansion 19 /
+        // 30, 256 33 / 31, 400 64 / 37, 1500 275 / 209, 5000 2384 / 1665; 30 % of
+        // them: 400 37 / 33, 1500 164 / 185, 3000 536 / 583, 5000 1392 / 1222.
         p->dom_points.assign((size_t)p->n_dom, 0);
+        long long pairs = 0, point_pairs = 0;
+        auto no_expansion = [&](const Box& b, double ak) {
+            return b.hh > bemk::EXP_KA_MAX / ((1.0 + 1e-6) * ak) || b.hmin < bemk::EXP_KA_MIN * (1.0 + 1e-6) / ak;
+        };
+        for (int d = 0; d < p->n_dom; ++d) {
+            const double ak = std::abs(p->k[d]);
+            long long waves = 0, parts = 0, points = 0;
+            for (const Tile& t : p->rtiles)
+                if (p->iface[t.iface].dl == d || p->iface[t.iface].dr == d) waves += (t.count + 63) / 64;
+            for (size_t c = 0; c < p->cchunks.size(); ++c) {
+                if (p->sigma[(size_t)d * p->n_if + p->cchunks[c].iface] == 0) continue;
+                const int np = (p->cchunks[c].count + bemk::NEAR_PART - 1) / bemk::NEAR_PART;
+                parts += np;
+                if (no_expansion(wb[c], ak))
+                    for (int q = 0; q < np; ++q) points += no_expansion(cb[c * NP + q], ak);
+            }
+            p->dom_points[d] = points > 0;
+            pairs += waves * parts * bemk::NEAR_PART;
+            point_pairs += waves * points * bemk::NEAR_PART;
+        }
+        p->point_launch = point_pairs > 1000 && 3 * point_pairs > pairs;
         for (int v = 0; v < bemk::ASM_VARIANTS; ++v) {
             p->noff[v] = (int)p->npairs.size() / 3;
             const int side = v >> 2 & 1;
             for (int t : lists[v]) {
                 const IfacePlan& P = p->iface[p->rtiles[t].iface];
                 const int d = side ? P.dr : P.dl;
+                p->vpoints[v] |= p->point_launch && p->dom_points[d];
                 const double ak = std::abs(p->k[d]);
                 const double rs = std::max(bemk::series_radius(p->k[d].real(), p->k[d].imag()), bemk::XS_SERIES_F32) / ak;
-                const double longest = bemk::EXP_KA_MAX / ((1.0 + 1e-6) * ak), shortest = bemk::EXP_KA_MIN * (1.0 + 1e-6) / ak;
-                auto no_expansion = [&](const Box& b) { return b.hh > longest || b.hmin < shortest; };
                 auto near = [&](const Box& a, const Box& b) {
                     const double dx = std::max(0.0, std::max(a.x0 - b.x1, b.x0 - a.x1));
                     const double dy = std::max(0.0, std::max(a.y0 - b.y1, b.y0 - a.y1));
-                    const double lim = std::max(no_expansion(b) ? rs + b.hh : rs, b.reach) * (1.0 + 1e-6);
+                    const bool points = no_expansion(b, ak);
+                    if (points && !p->point_launch) return true;
+                    const double lim = std::max(points ? rs + b.hh : rs, b.reach) * (1.0 + 1e-6);
                     return dx * dx + dy * dy < lim * lim;
                 };
-                for (size_t c = 0; c < p->cchunks.size(); ++c) {
-                    if (p->sigma[(size_t)d * p->n_if + p->cchunks[c].iface] == 0) continue;
-                    if (no_expansion(wb[c])) p->vpoints[v] = p->dom_points[d] = 1;
-                }
                 for (int w = 0; w < NW && 64 * w < p->rtiles[t].count; ++w)
                     for (size_t c = 0; c < p->cchunks.size(); ++c) {
                         const Box& a = rb[t * NW + w];
@@ -692,10 +718,10 @@ bem_status bem_assemble(bem_problem* p, int prec, void* A_dev, size_t lda, hipSt
     }
     if (prec == BEM_F32)
         HIP_OK(bemk::launch_assemble_f32(p->geom, p->L, p->N, p->n_if, ncc, p->quad, lists, p->vcount, pairs,
-                                         p->ncount, p->vpoints, static_cast<float2*>(A_dev), lda, stream, side));
+                                         p->ncount, p->vpoints, p->point_launch, static_cast<float2*>(A_dev), lda, stream, side));
     else
         HIP_OK(bemk::launch_assemble_f64(p->geom, p->L, p->N, p->n_if, ncc, p->quad, lists, p->vcount, pairs,
-                                         p->ncount, p->vpoints, static_cast<double2*>(A_dev), lda, A32, stream, side));
+                                         p->ncount, p->vpoints, p->point_launch, static_cast<double2*>(A_dev), lda, A32, stream, side));
     if (side != stream) {
         HIP_OK(hipEventRecord(p->asm_ev[1], side));
         HIP_OK(hipStreamWaitEvent(stream, p->asm_ev[1], 0));

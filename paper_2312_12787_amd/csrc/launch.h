@@ -41,17 +41,18 @@ constexpr int ASM_VARIANTS = 8;
 // lists[v] / counts[v]: row tiles of variant v (device list / host count);
 // pairs[v] / pair_counts[v]: its (row tile, column chunk, part of NEAR_PART
 // elements) triples that may hold near element pairs (device list / host count);
-// points[v]: its domains have elements without expansion.
+// points[v]: its domains have elements without expansion which, with point_launch,
+// have a launch of their own beyond the near radius.
 // Systems of assemble_one_launch(N) elements go to s in one launch; otherwise
 // variants go alternately to s and s1 (they write disjoint rows; s1 may be s).
 bool assemble_one_launch(int N);
 hipError_t launch_assemble_f64(const char* g, const GeomLayout& L, int N, int n_if, int n_cchunks, int q,
                                const int* const* lists, const int* counts, const int* const* pairs,
-                               const int* pair_counts, const int* points, double2* A, size_t lda, float2* A32,
+                               const int* pair_counts, const int* points, bool point_launch, double2* A, size_t lda, float2* A32,
                                hipStream_t s, hipStream_t s1);
 hipError_t launch_assemble_f32(const char* g, const GeomLayout& L, int N, int n_if, int n_cchunks, int q,
                                const int* const* lists, const int* counts, const int* const* pairs,
-                               const int* pair_counts, const int* points, float2* A, size_t lda, hipStream_t s,
+                               const int* pair_counts, const int* points, bool point_launch, float2* A, size_t lda, hipStream_t s,
                                hipStream_t s1);
 
 // angles / dirs are HOST arrays: they travel to the kernels by value in

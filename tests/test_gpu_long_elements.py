@@ -1,8 +1,9 @@
 """Elements without expansion: |k| h/2 above 2.55 or below 1e-13.
 
 Their Gauss points are evaluated one by one, by the near launch within the series
-radius and half a length, by a launch of their own beyond: both sides of the
-size up to which one launch takes the rest of an assembly (N = 2896), real and
+radius and half a length, beyond by the same or, where they are many, by a launch
+of their own: both sides of the size up to which one launch takes the rest of an
+assembly (N = 2896), few and many of them, real and
 complex wavenumbers, one domain or both, rules of an odd and an even number of
 points, lengths that differ along the boundary so that both kinds of element
 stand beside each other in one wave.  The matrix is filled with NaN first.
@@ -21,7 +22,8 @@ pytestmark = pytest.mark.gpu
 
 # elements, |k0| h/2, |k1| h/2, loss, rule
 CASES = [(70, 3.0, 2.4, 0.0, 8), (131, 2.4, 6.0, 0.15, 7), (300, 4.0, 5.0, 0.05, 10), (257, 0.02, 12.0, 0.1, 8),
-         (65, 0.9e-13, 1.1e-13, 0.0, 8), (96, 4e-14, 5e-14, 0.1, 5), (2900, 3.0, 4.0, 0.0, 8), (2897, 0.05, 5.0, 0.1, 3)]
+         (65, 0.9e-13, 1.1e-13, 0.0, 8), (96, 4e-14, 5e-14, 0.1, 5), (2900, 3.0, 4.0, 0.0, 8), (2897, 0.05, 5.0, 0.1, 3),
+         (600, 0.02, 2.2, 0.0, 8), (600, 2.9, 6.0, 0.05, 8), (2900, 2.2, 2.3, 0.05, 8)]
 
 
 def _uneven(n):
