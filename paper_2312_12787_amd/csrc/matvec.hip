@@ -882,9 +882,10 @@ int split_limit(int n, int ng)
 // in flight, column splits, 3-product form, for one group of 16 right-hand
 // sides and for 2-4 groups per pass.
 //
-// One group (bem_matvec, 16 right-hand sides, us).  FP64, 8 splits at every
-// size / group_splits: n 4400 88.6 / 65.3, 5400 115 / 88.2, 8192 189 / 172, 10000
-// 308 / 263, 12000 393 / 385, 16384 703 / 655.  FP32 keeps 8 splits (fewer are
+// One group (bem_matvec, 16 right-hand sides, us).  FP64, ten calls back to back, 8
+// splits at every size / group_splits: n 4400 91 / 80, 5400 119 / 104, 8192 195 /
+// 192 (a call among others 187 / 174), 10000 311 / 274, 12000 394 / 392, 16384
+// 702 / 657.  FP32 keeps 8 splits (fewer are
 // up to 15 % faster, but long FP32 sums lose accuracy), 8 / 4 column steps in
 // flight: n 6800 90.2 / 86.7, 8192 106 / 104, 12000 232 / 218, 16384 412 / 405.
 //

@@ -33,7 +33,7 @@
 //    the elements; where a point has close elements they are evaluated and
 //    added to its value.
 // Bound by FP64 VALU issue.  Measured, 101 x 101 points, 1024 elements: 805 us
-// with every Gauss point evaluated and one wave per point; now 227 us (2 x 100 us
+// with every Gauss point evaluated and one wave per point; now 229 us (2 x 100 us
 // and, the close pairs, 41 us, which took 94 us with one pair per lane).
 #include <hip/hip_runtime.h>
 

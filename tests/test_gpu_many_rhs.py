@@ -50,3 +50,17 @@ def test_batch_of_unequal_counts():
     for (g, B), (X, info) in zip(items, P.solve_batch([g for g, _ in items], [B for _, B in items], **opts)):
         Xa, ia = g.solve(B, **opts)
         assert info.converged.all() and torch.equal(X, Xa) and (info.iters == ia.iters).all()
+
+
+def test_served_request_of_more_than_64():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2312_12787_amd as P
+    from paper_2312_12787_amd import serve as S
+    spec, angles = W.disk(64, 2.0, 3.0), W.equispaced_angles(70)
+    with S.Server(1 << 30, slots=2, prec=P.MIXED, dirs=W.equispaced_angles(36)) as srv:
+        ids = [srv.submit(spec, a) for a in (angles, angles[:64], angles[64:])]
+        res = {r.id: r for r in srv.drain()}
+    whole, first, rest = (res[i] for i in ids)
+    assert all(r.status == 0 for r in res.values()) and whole.nrhs == 70
+    assert (whole.far_field[:64] == first.far_field).all() and (whole.far_field[64:] == rest.far_field).all()
